@@ -120,19 +120,27 @@ __device__ __forceinline__ void split_flux(const R u[5], const PrimV& p, R Fp[5]
 }
 
 // ---------------------------------------------------------------------------
-// WENO7 value at x_{i+1/2} from the left, a0..a6 = a_{i-3}..a_{i+3}.
-// The candidates q_k of the 4-point stencils enter as 35 d_k (q_k - a_{i}),
-// d = (1, 12, 18, 4)/35, written with the first differences, and the result
-// is a_i + sum w_k 35 d_k (q_k - a_i) / sum w_k 35 d_k.  Smoothness indicators (Jiang-Shu: the
-// integral over cell i of the squared derivatives of stencil k's cubic) are
-// evaluated from the nested differences D1, D2, D3 of the stencil values:
-//   b_k = s_k^2 + 13/12 c_k^2 + 781/720 D3_k^2 + eps,
-//   s_k = D1_k + h_k D2_k + m_k D3_k   (h = 5/2, 3/2, 1/2, -1/2;
-//                                        m = 11/6, 1/3, -1/6, 1/3),
-//   c_k = D2_k + g_k D3_k             (g = 2, 1, 0, -1),
-// so they vanish exactly on flat stencils.  WENO-Z (p = 2):
-// w_k = 1 + (tau/b_k)^2, tau = |b0 - b3 + 3(b1 - b2)|; Jiang-Shu: w_k = 1/b_k^2;
-// the result is sum w_k d_k q_k / sum w_k d_k.
+// WENO7 value at x_{i+1/2} from the left, a0..a6 = a_{i-3}..a_{i+3}, from
+// nested differences e (first), f (second) and g (third) of the values, each
+// formed once per point and shared by every face of a line.
+//
+// Stencil k's cubic enters through three numbers: its slope
+// s_k (with a 24th of the third derivative), curvature c_k and third derivative
+// g_k at the centre of cell i, in cell widths:
+//   s0 = e2 + f1/2 + g0/3, s1 = e2 + f2/2 - g1/6, s2 = e2 + f2/2 - g2/6,
+//   s3 = e3 - f3/2 + g3/3,  c0 = f1 + g0, c1 = c2 = f2, c3 = f3 - g3.
+// Its value at the face is q_k = a_i + s_k/2 + c_k/12 (p(1/2) = p(0) + s/2 +
+// c/8 and p(0) = a_i - c/24), so a candidate costs one fma beside its
+// indicator b_k = s_k^2 + 13/12 c_k^2 + 781/720 g_k^2 + eps (Jiang-Shu: the
+// integral over the cell of the squared derivatives), and it holds values of
+// its own stencil only: a stencil across a jump, whose weight vanishes, leaves
+// no rounding of the jump behind.  f is kept scaled by sqrt(13/12), so c_k^2
+// needs no factor; G = 781/780 g^2 + eps is shared.  Indicators vanish exactly
+// on flat stencils.  WENO-Z (p = 2): w_k = 1 + (tau/b_k)^2, tau = |b0 - b3 +
+// 3(b1 - b2)|; Jiang-Shu: w_k = 1/b_k^2; the result is sum w_k d_k q_k /
+// sum w_k d_k, 35 d = (1, 12, 18, 4).
+//
+// Bound by VALU issue.
 template <class R>
 __device__ __forceinline__ R rcp_approx(R x);
 template <>
@@ -144,179 +152,190 @@ __device__ __forceinline__ double rcp_approx<double>(double x) {
   return 1.0 / x;
 }
 
-template <class R>
-__device__ __forceinline__ R smoothness(R D1, R D2, R D3, R h, R m, R g, R eps) {
-  const R sk = fma(m, D3, fma(h, D2, D1));
-  const R ck = (g == R(0)) ? D2 : fma(g, D3, D2);  // g is a literal: no select survives
-  return fma(sk, sk, fma(R(13.0 / 12.0) * ck, ck, fma(R(781.0 / 720.0) * D3, D3, eps)));
+// num / den: with the estimate r = (1 - d) / den, d = 1 - den r (~2^-23),
+// num r (1 + d + d^2) leaves d^3, below the rounding.
+__device__ __forceinline__ double quot(double num, double den) {
+  const double r = __builtin_amdgcn_rcp(den);
+  const double d = fma(-den, r, 1.0);
+  const double q = num * r;
+  return fma(q, fma(d, d, d), q);
 }
+__device__ __forceinline__ float quot(float num, float den) { return num * __builtin_amdgcn_rcpf(den); }
 
-// WENO5 value at x_{i+1/2} from the left, b0..b4 = a_{i-2}..a_{i+2}, in the
-// same form as weno7: candidates d_k (q_k - a_i) from first differences
-// (d = (1, 6, 3)/10), Jiang-Shu indicators b_k = c1^2 + 13/12 D2^2 + eps with
-// c1 = D1 + h_k D2 (h = 3/2, 1/2, -1/2), WENO-Z tau = |b0 - b2|.
+constexpr double kCurv = 1.0408329997330663;  // sqrt(13/12)
+
+// One WENO7 face from its differences: ai = a_i, e2, e3; f1, f2, f3; g, G =
+// four third differences and their indicator terms.
 template <class R, int S>
-__device__ __forceinline__ R weno5(R b0, R b1, R b2, R b3, R b4, R eps) {
-  const R e0 = b1 - b0, e1 = b2 - b1, e2 = b3 - b2, e3 = b4 - b3;
-  // candidates as 10 d_k (q_k - b2) (the 10 cancels against sum 10 w_k d_k)
-  const R r0 = fma(R(5.0 / 6.0), e1, R(-1.0 / 3.0) * e0);
-  const R r1 = fma(R(2.0), e2, e1);
-  const R r2 = fma(R(-0.5), e3, R(2.0) * e2);
-  if (S == kWeno5Linear) return fma((r0 + r1) + r2, R(0.1), b2);
-  const R f0 = e1 - e0, f1 = e2 - e1, f2 = e3 - e2;
-  const R s0 = fma(R(1.5), f0, e0), s1 = fma(R(0.5), f1, e1), s2 = fma(R(-0.5), f2, e2);
-  const R be0 = fma(s0, s0, fma(R(13.0 / 12.0) * f0, f0, eps));
-  const R be1 = fma(s1, s1, fma(R(13.0 / 12.0) * f1, f1, eps));
-  const R be2 = fma(s2, s2, fma(R(13.0 / 12.0) * f2, f2, eps));
-  if (sizeof(R) == 8) {
-    // common denominator: with B_k = b_k^2, WENO-Z d_k (B_k + tau^2) prod_{j!=k} B_j,
-    // Jiang-Shu d_k prod_{j!=k} B_j
-    // (WENO-Z: (B_0 + tau^2) B_1 = B_0 B_1 + tau^2 B_1, and so on.)
-    const R B0 = be0 * be0, B1 = be1 * be1, B2 = be2 * be2;
-    const R P01 = B0 * B1;
-    R A0, A1, A2;
-    if (S == kWeno5Z) {
-      const R tau = fabs(be0 - be2);
-      const R t2 = tau * tau;
-      A0 = fma(t2, B1, P01) * B2;
-      A1 = fma(t2, B0, P01) * B2;
-      A2 = (B2 + t2) * P01;
-    } else {
-      A0 = B1 * B2;
-      A1 = B0 * B2;
-      A2 = P01;
-    }
-    const R num = fma(A2, r2, fma(A1, r1, A0 * r0));
-    const R den = fma(A2, R(3.0), fma(A1, R(6.0), A0));
-    return b2 + (R)div_nr((double)num, (double)den);
-  } else {
-    const R i0 = rcp_approx<R>(be0), i1 = rcp_approx<R>(be1), i2 = rcp_approx<R>(be2);
-    R w0, w1, w2;
-    if (S == kWeno5Z) {
-      const R tau = fabs(be0 - be2);
-      const R s0z = tau * i0, s1z = tau * i1, s2z = tau * i2;
-      w0 = fma(s0z, s0z, R(1));
-      w1 = fma(s1z, s1z, R(1));
-      w2 = fma(s2z, s2z, R(1));
-    } else {
-      w0 = i0 * i0;
-      w1 = i1 * i1;
-      w2 = i2 * i2;
-    }
-    const R num = fma(w2, r2, fma(w1, r1, w0 * r0));
-    const R den = fma(w2, R(3.0), fma(w1, R(6.0), w0));
-    return fma(num, rcp_approx<R>(den), b2);
-  }
-}
-
-// Schemes kWeno5*: the 5th-order reconstruction from the middle five values
-// (a_{i-2}..a_{i+2}) of the same 7-point window.
-// The WENO7 value in two parts: the front (candidates and smoothness
-// indicators) and the back (weights and the normalised combination).
-template <class R>
-struct W7Front {
-  R a3, r0, r1, r2, r3, b0, b1, b2, b3;
-};
-
-template <class R, int S>
-__device__ __forceinline__ W7Front<R> weno7_front(R a0, R a1, R a2, R a3, R a4, R a5, R a6, R eps) {
-  W7Front<R> w;
-  w.a3 = a3;
-  // nested differences of the seven values
-  const R e0 = a1 - a0, e1 = a2 - a1, e2 = a3 - a2, e3 = a4 - a3, e4 = a5 - a4, e5 = a6 - a5;
-  // candidates as 35 d_k (q_k - a3), from the differences (the factor 35
-  // cancels against the weights' denominator sum 35 w_k d_k)
-  w.r0 = fma(R(13.0 / 12.0), e2, fma(R(-10.0 / 12.0), e1, R(3.0 / 12.0) * e0));
-  w.r1 = fma(R(3.0), e3, fma(R(4.0), e2, -e1));
-  w.r2 = fma(R(-1.5), e4, fma(R(9.0), e3, R(1.5) * e2));
-  w.r3 = fma(R(1.0 / 3.0), e5, fma(R(-4.0 / 3.0), e4, R(3.0) * e3));
-  if (S == kWenoLinear) return w;
-
-  const R f0 = e1 - e0, f1 = e2 - e1, f2 = e3 - e2, f3 = e4 - e3, f4 = e5 - e4;
-  const R g0 = f1 - f0, g1 = f2 - f1, g2 = f3 - f2, g3 = f4 - f3;
-  w.b0 = smoothness<R>(e0, f0, g0, R(2.5), R(11.0 / 6.0), R(2), eps);
-  w.b1 = smoothness<R>(e1, f1, g1, R(1.5), R(1.0 / 3.0), R(1), eps);
-  w.b2 = smoothness<R>(e2, f2, g2, R(0.5), R(-1.0 / 6.0), R(0), eps);
-  w.b3 = smoothness<R>(e3, f3, g3, R(-0.5), R(1.0 / 3.0), R(-1), eps);
-  return w;
-}
-
-template <class R, int S>
-__device__ __forceinline__ R weno7_back(const W7Front<R>& w) {
-  const R a3 = w.a3, r0 = w.r0, r1 = w.r1, r2 = w.r2, r3 = w.r3;
-  if (S == kWenoLinear) return fma((r0 + r1) + (r2 + r3), R(1.0 / 35.0), a3);
-  const R b0 = w.b0, b1 = w.b1, b2 = w.b2, b3 = w.b3;
+__device__ __forceinline__ R weno7_face(R ai, R e2, R e3, R f1, R f2, R f3, const R* g, const R* G) {
+  const R sm = fma(R(0.5 / kCurv), f2, e2);
+  const R s0 = fma(R(1.0 / (3.0 * kCurv)), g[0], fma(R(0.5 / kCurv), f1, e2));
+  const R s1 = fma(R(-1.0 / (6.0 * kCurv)), g[1], sm);
+  const R s2 = fma(R(-1.0 / (6.0 * kCurv)), g[2], sm);
+  const R s3 = fma(R(1.0 / (3.0 * kCurv)), g[3], fma(R(-0.5 / kCurv), f3, e3));
+  const R c0 = f1 + g[0], c3 = f3 - g[3];
+  // candidates as 12 sqrt(13/12) (q_k - a_i)
+  const R r0 = fma(R(6.0 * kCurv), s0, c0), r1 = fma(R(6.0 * kCurv), s1, f2), r2 = fma(R(6.0 * kCurv), s2, f2),
+          r3 = fma(R(6.0 * kCurv), s3, c3);
+  if (S == kWenoLinear)
+    return fma(R(1.0 / (35.0 * 12.0 * kCurv)), fma(R(4), r3, fma(R(18), r2, fma(R(12), r1, r0))), ai);
+  const R b0 = fma(s0, s0, fma(c0, c0, G[0]));
+  const R b1 = fma(s1, s1, fma(f2, f2, G[1]));
+  const R b2 = fma(s2, s2, fma(f2, f2, G[2]));
+  const R b3 = fma(s3, s3, fma(c3, c3, G[3]));
+  const R tau = fma(R(3), b1 - b2, b0 - b3);  // enters squared
+  R num, den;
   if (sizeof(R) == 8) {
     // Weights over a common denominator: with B_k = b_k^2 the WENO-Z weight
-    // d_k (1 + tau^2/B_k) is proportional to d_k (B_k + tau^2) prod_{j!=k} B_j,
-    // the Jiang-Shu weight d_k/B_k to d_k prod_{j!=k} B_j.  One division.
+    // 1 + tau^2/B_k is proportional to (B_k + tau^2) prod_{j!=k} B_j, the
+    // Jiang-Shu weight 1/B_k to prod_{j!=k} B_j; w0 and w1 share the factor
+    // B_2 B_3, w2 and w3 the factor B_0 B_1.  One division.
     // (WENO-Z: (B_0 + tau^2) B_1 = B_0 B_1 + tau^2 B_1, and so on, one fma each.)
     const R B0 = b0 * b0, B1 = b1 * b1, B2 = b2 * b2, B3 = b3 * b3;
     const R P01 = B0 * B1, P23 = B2 * B3;
-    R A0, A1, A2, A3;
+    R a0, a1, a2, a3;
     if (S == kWenoZ) {
-      const R tau = fabs(fma(R(3), b1 - b2, b0 - b3));
       const R t2 = tau * tau;
-      A0 = fma(t2, B1, P01) * P23;
-      A1 = fma(t2, B0, P01) * P23;
-      A2 = fma(t2, B3, P23) * P01;
-      A3 = fma(t2, B2, P23) * P01;
+      a0 = fma(t2, B1, P01);
+      a1 = fma(t2, B0, P01);
+      a2 = fma(t2, B3, P23);
+      a3 = fma(t2, B2, P23);
     } else {
-      A0 = B1 * P23;
-      A1 = B0 * P23;
-      A2 = P01 * B3;
-      A3 = P01 * B2;
+      a0 = B1;
+      a1 = B0;
+      a2 = B3;
+      a3 = B2;
     }
-    const R num = fma(A3, r3, fma(A2, r2, fma(A1, r1, A0 * r0)));
-    const R den = fma(A3, R(4.0), fma(A2, R(18.0), fma(A1, R(12.0), A0)));
-    return a3 + (R)div_nr((double)num, (double)den);
+    const R P = R(4) * P01;  // 18 and 4 as 4 times 4.5 and 1
+    num = fma(P23, fma(R(12), a1 * r1, a0 * r0), P * fma(R(4.5), a2 * r2, a3 * r3));
+    den = fma(P23, fma(R(12), a1, a0), P * fma(R(4.5), a2, a3));
   } else {
     const R i0 = rcp_approx<R>(b0), i1 = rcp_approx<R>(b1), i2 = rcp_approx<R>(b2), i3 = rcp_approx<R>(b3);
     R w0, w1, w2, w3;
     if (S == kWenoZ) {
-      const R tau = fabs(fma(R(3), b1 - b2, b0 - b3));
-      const R s0 = tau * i0, s1 = tau * i1, s2 = tau * i2, s3 = tau * i3;
-      w0 = fma(s0, s0, R(1));
-      w1 = fma(s1, s1, R(1));
-      w2 = fma(s2, s2, R(1));
-      w3 = fma(s3, s3, R(1));
+      const R z0 = tau * i0, z1 = tau * i1, z2 = tau * i2, z3 = tau * i3;
+      w0 = fma(z0, z0, R(1));
+      w1 = fma(z1, z1, R(1));
+      w2 = fma(z2, z2, R(1));
+      w3 = fma(z3, z3, R(1));
     } else {
       w0 = i0 * i0;
       w1 = i1 * i1;
       w2 = i2 * i2;
       w3 = i3 * i3;
     }
-    const R num = fma(w3, r3, fma(w2, r2, fma(w1, r1, w0 * r0)));
-    const R den = fma(w3, R(4.0), fma(w2, R(18.0), fma(w1, R(12.0), w0)));
-    return fma(num, rcp_approx<R>(den), a3);
+    num = fma(R(4), w3 * r3, fma(R(18), w2 * r2, fma(R(12), w1 * r1, w0 * r0)));
+    den = fma(R(4), w3, fma(R(18), w2, fma(R(12), w1, w0)));
+  }
+  return fma(R(1.0 / (12.0 * kCurv)), quot(num, den), ai);
+}
+
+// One WENO5 face (quadratics through three cells) in the same form: s0 = e1 +
+// f0/2, s1 = e1 + f1/2, s2 = e2 - f2/2, c_k = f_k, q_k = a_i + s_k/2 + f_k/12,
+// b_k = s_k^2 + F_k with F = 13/12 f^2 + eps, 10 d = (1, 6, 3), WENO-Z tau =
+// |b0 - b2|.  e1, e2: the differences left and right of cell i.
+template <class R, int S>
+__device__ __forceinline__ R weno5_face(R ai, R e1, R e2, const R* f, const R* F) {
+  const R s0 = fma(R(0.5), f[0], e1), s1 = fma(R(0.5), f[1], e1), s2 = fma(R(-0.5), f[2], e2);
+  const R r0 = fma(R(6), s0, f[0]), r1 = fma(R(6), s1, f[1]), r2 = fma(R(6), s2, f[2]);  // 12 (q_k - a_i)
+  if (S == kWeno5Linear) return fma(R(1.0 / 120.0), fma(R(3), r2, fma(R(6), r1, r0)), ai);
+  const R b0 = fma(s0, s0, F[0]), b1 = fma(s1, s1, F[1]), b2 = fma(s2, s2, F[2]);
+  const R tau = b0 - b2;  // enters squared
+  R num, den;
+  if (sizeof(R) == 8) {
+    // common denominator, as in weno7_face
+    const R B0 = b0 * b0, B1 = b1 * b1, B2 = b2 * b2;
+    const R P01 = B0 * B1;
+    R a0, a1, a2;
+    if (S == kWeno5Z) {
+      const R t2 = tau * tau;
+      a0 = fma(t2, B1, P01);
+      a1 = fma(t2, B0, P01);
+      a2 = (B2 + t2) * P01;
+    } else {
+      a0 = B1;
+      a1 = B0;
+      a2 = P01;
+    }
+    num = fma(B2, fma(R(6), a1 * r1, a0 * r0), R(3) * (a2 * r2));
+    den = fma(B2, fma(R(6), a1, a0), R(3) * a2);
+  } else {
+    const R i0 = rcp_approx<R>(b0), i1 = rcp_approx<R>(b1), i2 = rcp_approx<R>(b2);
+    R w0, w1, w2;
+    if (S == kWeno5Z) {
+      const R z0 = tau * i0, z1 = tau * i1, z2 = tau * i2;
+      w0 = fma(z0, z0, R(1));
+      w1 = fma(z1, z1, R(1));
+      w2 = fma(z2, z2, R(1));
+    } else {
+      w0 = i0 * i0;
+      w1 = i1 * i1;
+      w2 = i2 * i2;
+    }
+    num = fma(R(3), w2 * r2, fma(R(6), w1 * r1, w0 * r0));
+    den = fma(R(3), w2, fma(R(6), w1, w0));
+  }
+  return fma(R(1.0 / 12.0), quot(num, den), ai);
+}
+
+// L neighbouring faces of one line: put(k, R(a_k..a_{k+6})), k = 0..L-1, from
+// the values get(0..L+5); schemes kWeno5* use the middle five of each window.
+// Differences are formed as the faces reach them and every face by the same
+// operations whatever L is, so that all splits of a line give the same bits.
+// The scheduling barriers keep the live set at one face.
+template <class R, int S, int L, class Get, class Put>
+__device__ __forceinline__ void weno_line(Get get, R eps, Put put) {
+  if constexpr (S >= kWeno5Z) {
+    R a[L + 4], e[L + 3], f[L + 2], F[L + 2];
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+#pragma unroll
+      for (int m = (k == 0 ? 0 : k + 4); m <= k + 4; ++m) {
+        a[m] = get(m + 1);
+        if (m >= 1) e[m - 1] = a[m] - a[m - 1];
+        if (m >= 2) {
+          f[m - 2] = e[m - 1] - e[m - 2];
+          F[m - 2] = fma(R(13.0 / 12.0) * f[m - 2], f[m - 2], eps);
+        }
+      }
+      put(k, weno5_face<R, S>(a[k + 2], e[k + 1], e[k + 2], f + k, F + k));
+      if (L > 1) __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    R a[L + 6], e[L + 5], f[L + 4], g[L + 3], G[L + 3];
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+#pragma unroll
+      for (int m = (k == 0 ? 0 : k + 6); m <= k + 6; ++m) {
+        a[m] = get(m);
+        if (m >= 1) e[m - 1] = a[m] - a[m - 1];
+        if (m >= 2) f[m - 2] = R(kCurv) * (e[m - 1] - e[m - 2]);
+        if (m >= 3) {
+          g[m - 3] = f[m - 2] - f[m - 3];
+          G[m - 3] = fma(R(781.0 / 780.0) * g[m - 3], g[m - 3], eps);
+        }
+      }
+      put(k, weno7_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f[k + 1], f[k + 2], f[k + 3], g + k, G + k));
+      if (L > 1) __builtin_amdgcn_sched_barrier(0);
+    }
   }
 }
 
 template <class R, int S>
 __device__ __forceinline__ R weno7(R a0, R a1, R a2, R a3, R a4, R a5, R a6, R eps) {
-  if (S >= kWeno5Z) return weno5<R, S>(a1, a2, a3, a4, a5, eps);
-  return weno7_back<R, S>(weno7_front<R, S>(a0, a1, a2, a3, a4, a5, a6, eps));
+  const R v[7] = {a0, a1, a2, a3, a4, a5, a6};
+  R r;
+  weno_line<R, S, 1>([&](int m) { return v[m]; }, eps, [&](int, R x) { r = x; });
+  return r;
 }
 
 // Two neighbouring reconstructions from the eight values v0..v7: lo from
-// v0..v6, hi from v1..v7, each by exactly the arithmetic of weno7.  Their
-// shared differences are formed once; the fronts of both come first and the
-// backs one after the other, which keeps fewer values live than interleaving
-// the two.
+// v0..v6, hi from v1..v7.
 template <class R, int S>
 __device__ __forceinline__ void weno7_pair(R v0, R v1, R v2, R v3, R v4, R v5, R v6, R v7, R eps, R& lo,
                                            R& hi) {
-  if (S >= kWeno5Z) {
-    lo = weno5<R, S>(v1, v2, v3, v4, v5, eps);
-    hi = weno5<R, S>(v2, v3, v4, v5, v6, eps);
-    return;
-  }
-  const W7Front<R> wl = weno7_front<R, S>(v0, v1, v2, v3, v4, v5, v6, eps);
-  const W7Front<R> wh = weno7_front<R, S>(v1, v2, v3, v4, v5, v6, v7, eps);
-  __builtin_amdgcn_sched_barrier(0);
-  lo = weno7_back<R, S>(wl);
-  __builtin_amdgcn_sched_barrier(0);
-  hi = weno7_back<R, S>(wh);
+  const R v[8] = {v0, v1, v2, v3, v4, v5, v6, v7};
+  weno_line<R, S, 2>([&](int m) { return v[m]; }, eps, [&](int k, R x) { (k == 0 ? lo : hi) = x; });
 }
 
 // Face flux from the 8-point window Fp/Fm[m] = split fluxes at i-3+m:
