@@ -955,6 +955,7 @@ template <class R, int S>
 void launch_adj_axis_t(int AX, const AdjArgs<R>& a0, hipStream_t st) {
   AdjArgs<R> a = a0;
   a.inv_d = R(1.0 / a.g.dx[AX]);
+  a.eps = R(4) * a.eps;  // indicators of the doubled split fluxes; the partials dR/da do not change
   const long long nl = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
   // The outflow face n-1/2 adds to G: before the line kernel when that one

@@ -223,7 +223,7 @@ hipError_t stage_impl(hydro_ctx* ctx, const R* W, const R* Un, R* out, int stage
     ProfScope p(ctx, HYDRO_K_XFACE, st);
     e = launch_face_kernel<R>(ctx->x_tile ? 6 : 0, a, scheme, ctx->seg, st);
   }
-  if (e == hipSuccess && c.bc[0] == HYDRO_BC_OUTFLOW && !ctx->x_tile) {
+  if (e == hipSuccess && c.bc[0] == HYDRO_BC_OUTFLOW && !ctx->x_tile && !line_scheme(scheme)) {
     ProfScope p(ctx, HYDRO_K_XBOUND, st);
     e = launch_face_kernel<R>(1, a, scheme, ctx->seg, st);
   }

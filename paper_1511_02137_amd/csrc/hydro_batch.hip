@@ -45,8 +45,8 @@ struct hydro_batch {
   long long blocks[3] = {0, 0, 0}; // workgroups per axis launch (0: one per item)
   int xrows = 0;                   // x pass: 0 LDS tiles, 1 groups of whole rows (+ boundary faces)
   int tile_a[3] = {0, 0, 0};       // per axis: the tile length every event shares (31, 32), else 0
-  int xtb = 256;                   // x-row workgroup size
-  long long xlds = 0;              // its dynamic LDS
+  int xtb = 256;                   // x-row workgroup size (limiter, MUSTA-FORCE)
+  long long xlds = 0;              // dynamic LDS of the x-row launch
   int use_graph = 1;
   hipStream_t cap = nullptr;       // capture stream (never runs work)
   hipGraphExec_t exec = nullptr;
@@ -396,7 +396,7 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
     v.deposit = c.deposit;
     for (int a = 0; a < 5; ++a)
       b->off[(size_t)a * (n_events + 1) + i + 1] =
-          b->off[(size_t)a * (n_events + 1) + i] + batch_items(a, v.g, b->xtb, (int)elem_size(&c));
+          b->off[(size_t)a * (n_events + 1) + i] + batch_items(a, v.g, face_scheme(c), b->xtb, (int)elem_size(&c));
   }
   std::vector<DevScalars> zero(n_events);
   std::memset(zero.data(), 0, sizeof(DevScalars) * n_events);

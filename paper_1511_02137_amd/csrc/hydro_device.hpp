@@ -45,17 +45,14 @@ __device__ __forceinline__ double div_nr(double num, double den) {
   return fma(fma(-den, q, num), r, q);
 }
 
-// sqrt(x) for normal x > 0: reciprocal square root estimate, two coupled
-// Newton iterations for sqrt(x) and 1/(2 sqrt(x)), one residual correction.
+// sqrt(x) for normal x > 0: from the reciprocal square root estimate (~23
+// bits) one Newton step for sqrt(x) (~45 bits) and one residual correction,
+// whose factor 1/(2 sqrt(x)) need not be better than the estimate.
 __device__ __forceinline__ double sqrt_nr(double x) {
   const double y = __builtin_amdgcn_rsq(x);
-  double g = x * y, h = 0.5 * y;
-  double r = fma(-g, h, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
-  r = fma(-g, h, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
+  double g = x * y;
+  const double h = 0.5 * y;
+  g = fma(g, fma(-g, h, 0.5), g);
   return fma(fma(-g, g, x), h, g);
 }
 
@@ -76,17 +73,19 @@ __device__ __forceinline__ PrimV c2p(double E, double Mx, double My, double Mz, 
     r.v[0] = r.v[1] = r.v[2] = 0.0;
     return r;
   }
-  double M2 = Mx * Mx + My * My + Mz * Mz;
-  if (M2 >= kVCap * kVCap * E * E) {
+  const double E2 = E * E;
+  double M2 = fma(Mz, Mz, fma(My, My, Mx * Mx));
+  if (M2 >= kVCap * kVCap * E2) {
     ++fix;
     const double sc = kVCap * E / sqrt(M2);
     Mx = Mx * sc;
     My = My * sc;
     Mz = Mz * sc;
-    M2 = Mx * Mx + My * My + Mz * Mz;
+    M2 = fma(Mz, Mz, fma(My, My, Mx * Mx));
   }
-  const double e = div_nr(3.0 * (E * E - M2), E + sqrt_nr(4.0 * E * E - 3.0 * M2));
-  const double iW = rcp_nr(E + e * (1.0 / 3.0));
+  const double n = 3.0 * (E2 - M2);  // 4E^2 - 3M^2 = E^2 + n
+  const double e = div_nr(n, E + sqrt_nr(E2 + n));
+  const double iW = rcp_nr(fma(e, 1.0 / 3.0, E));
   r.e = e;
   r.v[0] = Mx * iW;
   r.v[1] = My * iW;
@@ -99,23 +98,25 @@ __device__ __forceinline__ PrimV c2p(const R u[5], unsigned& fix) {
   return c2p((double)u[0], (double)u[1], (double)u[2], (double)u[3], fix);
 }
 
-// Physical flux along axis AX and its Lax-Friedrichs split (alpha = 1):
+// Physical flux along axis AX and twice its Lax-Friedrichs split (alpha = 1),
+// f + u and f - u (FP64: products in fmas, one rounding fewer each):
 // f = (M_AX, M_x v_AX + p d_{x,AX}, M_y v_AX + p d_{y,AX}, M_z v_AX + p d_{z,AX}, N v_AX).
 template <class R, int AX>
 __device__ __forceinline__ void split_flux(const R u[5], const PrimV& p, R Fp[5], R Fm[5]) {
   const R vd = (R)p.v[AX];
   const R pr = (R)(p.e * (1.0 / 3.0));
-  R f[5];
-  f[0] = u[1 + AX];
-  f[1] = (AX == 0) ? u[1] * vd + pr : u[1] * vd;
-  f[2] = (AX == 1) ? u[2] * vd + pr : u[2] * vd;
-  f[3] = (AX == 2) ? u[3] * vd + pr : u[3] * vd;
-  f[4] = u[4] * vd;
+  Fp[0] = u[1 + AX] + u[0];
+  Fm[0] = u[1 + AX] - u[0];
 #pragma unroll
-  for (int c = 0; c < 5; ++c) {  // (f +- u)/2 with one rounding: u/2 is exact
-    const R hu = R(0.5) * u[c];
-    Fp[c] = fma(R(0.5), f[c], hu);
-    Fm[c] = fma(R(0.5), f[c], -hu);
+  for (int c = 1; c < 5; ++c) {
+    if (sizeof(R) == 8 && c != 1 + AX) {
+      Fp[c] = fma(u[c], vd, u[c]);
+      Fm[c] = fma(u[c], vd, -u[c]);
+    } else {
+      const R f = sizeof(R) == 8 ? fma(u[c], vd, pr) : (c == 1 + AX ? u[c] * vd + pr : u[c] * vd);
+      Fp[c] = f + u[c];
+      Fm[c] = f - u[c];
+    }
   }
 }
 
@@ -279,26 +280,27 @@ __device__ __forceinline__ R weno5_face(R ai, R e1, R e2, const R* f, const R* F
 }
 
 // L neighbouring faces of one line: put(k, R(a_k..a_{k+6})), k = 0..L-1, from
-// the values get(0..L+5); schemes kWeno5* use the middle five of each window.
+// the values get(0..L+5), taken in this order, value k + 6 before face k;
+// schemes kWeno5* use the middle five of each window.
 // Differences are formed as the faces reach them and every face by the same
 // operations whatever L is, so that all splits of a line give the same bits.
 // The scheduling barriers keep the live set at one face.
 template <class R, int S, int L, class Get, class Put>
 __device__ __forceinline__ void weno_line(Get get, R eps, Put put) {
   if constexpr (S >= kWeno5Z) {
-    R a[L + 4], e[L + 3], f[L + 2], F[L + 2];
+    R a[L + 6], e[L + 4], f[L + 3], F[L + 3];  // a[0] and a[k + 6] are read, not used
 #pragma unroll
     for (int k = 0; k < L; ++k) {
 #pragma unroll
-      for (int m = (k == 0 ? 0 : k + 4); m <= k + 4; ++m) {
-        a[m] = get(m + 1);
-        if (m >= 1) e[m - 1] = a[m] - a[m - 1];
-        if (m >= 2) {
-          f[m - 2] = e[m - 1] - e[m - 2];
-          F[m - 2] = fma(R(13.0 / 12.0) * f[m - 2], f[m - 2], eps);
+      for (int m = (k == 0 ? 0 : k + 6); m <= k + 6; ++m) {
+        a[m] = get(m);
+        if (m >= 3) e[m - 2] = a[m - 1] - a[m - 2];
+        if (m >= 4) {
+          f[m - 3] = e[m - 2] - e[m - 3];
+          F[m - 3] = fma(R(13.0 / 12.0) * f[m - 3], f[m - 3], eps);
         }
       }
-      put(k, weno5_face<R, S>(a[k + 2], e[k + 1], e[k + 2], f + k, F + k));
+      put(k, weno5_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f + k + 1, F + k + 1));
       if (L > 1) __builtin_amdgcn_sched_barrier(0);
     }
   } else {
@@ -327,15 +329,6 @@ __device__ __forceinline__ R weno7(R a0, R a1, R a2, R a3, R a4, R a5, R a6, R e
   R r;
   weno_line<R, S, 1>([&](int m) { return v[m]; }, eps, [&](int, R x) { r = x; });
   return r;
-}
-
-// Two neighbouring reconstructions from the eight values v0..v7: lo from
-// v0..v6, hi from v1..v7.
-template <class R, int S>
-__device__ __forceinline__ void weno7_pair(R v0, R v1, R v2, R v3, R v4, R v5, R v6, R v7, R eps, R& lo,
-                                           R& hi) {
-  const R v[8] = {v0, v1, v2, v3, v4, v5, v6, v7};
-  weno_line<R, S, 2>([&](int m) { return v[m]; }, eps, [&](int k, R x) { (k == 0 ? lo : hi) = x; });
 }
 
 // Face flux from the 8-point window Fp/Fm[m] = split fluxes at i-3+m:
@@ -420,7 +413,9 @@ __device__ __forceinline__ void musta_face(At at, R eps, int k, R F[5], unsigned
 // N >= kPPEps in the half state on each side of the face.  The split fluxes
 // of the two cells give u = F+ - F-, f = F+ + F- and F_LF = F+_i + F-_{i+1}.
 // FP64 in every form; a face that needs no limiting keeps its flux bit for bit.
-constexpr double kPPEps = 1e-13;
+// All of it is in the doubled units of split_flux (face values, half states
+// and the bound: exact powers of two).
+constexpr double kPPEps = 2.0 * 1e-13;
 
 // Largest theta in [0, 1] with h(theta) >= 0 for h concave: 1 if h(1) >= 0,
 // 0 if h(0) <= 0, else the root of the chord from (0, h0) to (1, h1), below

@@ -90,6 +90,16 @@ __host__ __device__ constexpr int tile_len(int n) {
   return ((n + 30) / 31) * 31 * 100 < 112 * (((n + 31) / 32) * 32) ? 31 : 32;
 }
 
+// Schemes whose faces are taken along lines (line_body, xline_body): plain
+// WENO fluxes, without the limiter or MUSTA-FORCE.
+__host__ __device__ constexpr bool line_scheme(int scheme) { return (scheme & (kPP | kMusta)) == 0; }
+
+// Line tiles: 16 lines of A + 8 points for each (field, split).
+constexpr int kLineX = 16;
+__host__ __device__ constexpr size_t line_lds_bytes(int AX, int A, int elem) {
+  return (size_t)10 * (A + 8) * (AX == 0 ? kLineX + 1 : kLineX) * elem;
+}
+
 // x-row kernels: workgroup of TB lanes holding TB / nx whole rows.  LDS per
 // row: max(10 (nx + 8), 5 nx) words.  xrow_block picks TB in {256, 384, 512,
 // 1024} for a set of row lengths: every nx <= TB, the LDS of TB / nx rows
@@ -159,7 +169,7 @@ struct BatchArgs {
   R eps;
   int xtb;                // workgroup size of the x-row launch (rows per item: xtb / nx)
   int tile_a;             // 31 or 32: every event's tile length along the launched axis (0: they differ)
-  long long xlds;         // its dynamic LDS bytes (the largest event)
+  long long xlds;         // dynamic LDS bytes of the x-row launch (the largest event)
 };
 
 // Arguments of the line adjoint kernels (device pointers).

@@ -8,18 +8,20 @@
 //   combine: Shu-Osher SSP-RK3.
 //
 // Work split (all kernels of a stage run on one stream):
-//   k_xface   one workgroup per group of whole x-rows.  Each lane recovers
-//             primitives for its cell, stores the split x-fluxes of the row
-//             plus 4+4 ghost cells in LDS, reconstructs one split of two
-//             neighbouring faces (or both splits of its left face) and
-//             writes the x-divergence.
-//   k_xbound  the right boundary face of every row (outflow x only).
+//   k_line    x, y or z faces of plain WENO fluxes from LDS tiles of 16 lines:
+//             one lane per point recovers it, lanes then march over runs of
+//             faces.  x assigns its divergence to D, y adds, z adds its own,
+//             does the RK combine and writes the stage output.
+//   k_xface   x faces with the limiter or MUSTA-FORCE, one workgroup per group
+//             of whole x-rows: each lane recovers its cell, stores the split
+//             x-fluxes of the row plus 4+4 ghost cells in LDS, takes its left
+//             face and writes the x-divergence;
+//   k_xbound  the right boundary face of those rows (outflow x only);
+//   k_tile    y and z faces with the limiter or MUSTA-FORCE from LDS tiles.
 //   k_march   lanes along x (coalesced), each lane marches along y or z over
 //             a segment, keeping the split fluxes of the 8-point stencil in
 //             registers: one new cell and one face per step, no halo recompute.
-//             The y-march adds its divergence to D; the z-march adds its own,
-//             then does the RK combine and writes the stage output.
-//   k_jet     the source at the jet cells (between the y- and z-march).
+//   k_jet     the source at the jet cells (between the y and z faces).
 // All recovery of primitives is FP64; the flux and WENO arithmetic is in the
 // field type R (double or float).  FP contraction is off: every fma is
 // explicit, so every face is computed by the same sequence of roundings.
@@ -32,17 +34,16 @@
 namespace hydro {
 
 // ---------------------------------------------------------------------------
-// x-faces: a workgroup owns rpi = blockDim / nx whole rows (row0, row0 + 1,
-// ...; fewer at the end of the grid).  LDS per row: the split fluxes of its nx
-// cells and 8 ghost slots (slot j holds padded position j - 4), then the face
-// values.  One lane per cell: it recovers its cell, stores the split fluxes
-// (also into every ghost slot that copies the cell), reconstructs faces
-// (rows of even length: lane 2q + h the split h of faces 2q - 1/2 and
-// 2q + 1/2; otherwise the cell's left face) and forms the divergence; the
-// outflow right face of the last cell is added by k_xbound.
-// What the face kernels keep per point: the Lax-Friedrichs split fluxes
-// (F+, F-), or with MUSTA-FORCE the conserved values themselves (in the F+
-// slots; no recovery needed).
+// x-faces (limiter, MUSTA-FORCE): a workgroup owns rpi = blockDim / nx whole
+// rows (row0, row0 + 1, ...; fewer at the end of the grid).  LDS per row: the
+// split fluxes of its nx cells and 8 ghost slots (slot j holds padded position
+// j - 4), then the face values.  One lane per cell: it recovers its cell,
+// stores the split fluxes (also into every ghost slot that copies the cell),
+// reconstructs the cell's left face and forms the divergence; the outflow
+// right face of the last cell is added by k_xbound.
+// What the face kernels keep per point: twice the Lax-Friedrichs split fluxes
+// (F+, F-; face_scale sets what that changes), or with MUSTA-FORCE the
+// conserved values themselves (in the F+ slots; no recovery needed).
 template <class R, int S, int AX>
 __device__ __forceinline__ void point_values(const R u[5], R Fp[5], R Fm[5], unsigned& fix) {
   if constexpr ((S & kMusta) != 0) {
@@ -55,6 +56,16 @@ __device__ __forceinline__ void point_values(const R u[5], R Fp[5], R Fm[5], uns
     const PrimV pv = c2p(u, fix);
     split_flux<R, AX>(u, pv, Fp, Fm);
   }
+}
+
+// Weights' epsilon and 1/dx for the point values above: with doubled split
+// fluxes the indicators are four times as large and the face fluxes twice
+// (powers of two: every value scales exactly).
+template <class R, int S>
+__host__ __device__ __forceinline__ void face_scale(StageArgs<R>& a, double inv_d) {
+  constexpr bool twice = (S & kMusta) == 0;
+  a.inv_d = (R)((twice ? 0.5 : 1.0) * inv_d);
+  if (twice) a.eps = R(4) * a.eps;
 }
 
 // SSP-RK3 combine of the last face kernel of a stage (z).  With L = Dxy + Dz
@@ -85,7 +96,7 @@ __device__ __forceinline__ R rk_out_v(int stage, R p, R dz, R dt, R un) {
   return R(1.0 / 3.0) * un + R(2.0 / 3.0) * v;
 }
 
-template <class R, int S, bool PAIRS>
+template <class R, int S>
 __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0, int rpi, R* s) {
   const int nx = a.g.n[0];
   const int P = nx + 8;
@@ -99,12 +110,6 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
   R* sFp = s + (size_t)r * 10 * P;
   R* sFm = sFp + 5 * P;
   unsigned fix = 0;
-  // Plain WENO faces of rows with an even number of cells are taken in
-  // pairs (as in the y/z tiles); the F- points are then stored in reverse
-  // slot order.
-  const bool pair = PAIRS && (S & (kPP | kMusta)) == 0 && (nx & 1) == 0;
-  const int mrev = pair ? P - 1 : 0, msgn = pair ? -1 : 1;  // F- slot j at mrev + msgn j
-
   if (act) {
     R u[5];
     load5(a.W, nc, rowbase + x, u);
@@ -113,7 +118,7 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       sFp[c * P + x + 4] = Fp[c];
-      sFm[c * P + mrev + msgn * (x + 4)] = Fm[c];
+      sFm[c * P + x + 4] = Fm[c];
     }
     // ghost slots 0..3 and nx+4..nx+7, each filled by the lane whose cell it
     // copies: outflow, the edge lanes; periodic, the lanes four from the far
@@ -122,7 +127,7 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         sFp[c * P + j] = Fp[c];
-        sFm[c * P + mrev + msgn * j] = Fm[c];
+        sFm[c * P + j] = Fm[c];
       }
     };
     if (nx >= 8) {
@@ -142,44 +147,6 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
   }
   __syncthreads();
 
-  if (pair) {
-    // lane (q, h) = (x >> 1, x & 1): split h of the faces x' - 1/2, x' = 2q,
-    // 2q + 1, one field at a time; the two split values go into the field's
-    // own F+ and F- areas once every lane of the workgroup is past it
-    const int q = x >> 1, h = x & 1;
-    const R* b = h ? sFm + (P - 9 - 2 * q) : sFp + 2 * q;
-    R* dst = h ? sFm : sFp;
-    const int fa = 2 * q + h, fb = 2 * q + 1 - h;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      R lo, hi;
-      if (act) {
-        const R* v = b + c * P;
-        weno7_pair<R, (S & 7)>(v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], a.eps, lo, hi);
-      }
-      __syncthreads();
-      if (act) {
-        dst[c * P + fa] = lo;
-        dst[c * P + fb] = hi;
-      }
-    }
-    __syncthreads();
-    if (act) {
-      const int xr = (x + 1 == nx) ? 0 : x + 1;  // periodic: the right face of cell nx-1 is face -1/2
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        const R l = sFp[c * P + x] + sFm[c * P + x];
-        R* d = a.D + c * nc + rowbase + x;
-        if (x + 1 < nx || a.g.bc[0]) {
-          *d = (l - (sFp[c * P + xr] + sFm[c * P + xr])) * a.inv_d;
-        } else {
-          *d = l;  // finished by k_xbound
-        }
-      }
-    }
-    add_fixups(a.fixups, fix);
-    return;
-  }
   R Fh[5];
   if (act) {
     // face x - 1/2: F+ at x-4..x+2 (slots x..x+6), F- at x-3..x+3 (slots x+1..x+7)
@@ -221,7 +188,7 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
 template <class R, int S, int TB>
 __global__ void __launch_bounds__(TB) k_xface(StageArgs<R> a, int rpi) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  xrows_body<R, S, true>(a, (long long)blockIdx.x * rpi, rpi, reinterpret_cast<R*>(smem_raw));
+  xrows_body<R, S>(a, (long long)blockIdx.x * rpi, rpi, reinterpret_cast<R*>(smem_raw));
 }
 
 // Right boundary face of every row (outflow x): points nx-4..nx+3 (the last
@@ -403,11 +370,10 @@ __global__ void __launch_bounds__(256) k_march(StageArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// y- or z-faces from an LDS tile (AX = 1 or 2).  A workgroup of 512 lanes
+// y- or z-faces from an LDS tile (AX = 1 or 2; limiter, MUSTA-FORCE).  A workgroup of 512 lanes
 // owns 16 cells along x (coalesced 128-byte rows) by 31 cells along AX at one
 // value of the remaining axis, so that its 32 face rows are exactly one face
-// per lane (or, in pairs, one split of two faces per lane).  It stores the
-// split AX-fluxes of its 16 x 39 points (4 ghost rows on each side) in LDS,
+// per lane.  It stores the split AX-fluxes of its 16 x 39 points (4 ghost rows on each side) in LDS,
 // reconstructs the face rows and forms the divergence; each lane's D is
 // loaded before the reconstructions to hide its latency.
 // LAST (z): adds D, does the RK combine (rk_pre, rk_out) and writes the
@@ -426,15 +392,9 @@ __device__ __forceinline__ void tile_limit(R H[5], const R* sFp, const R* sFm, i
       H, [&](int c, int k) { return ((k & 1) ? sFm : sFp)[(c * kP + f + 3 + (k >> 1)) * kPitch + col]; }, mu);
 }
 
-template <class R, int S, int AX, bool LAST, int kTileA, bool PAIRS>
+template <class R, int S, int AX, bool LAST, int kTileA>
 __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
   constexpr int kTileP = kTileA + 8;  // points along AX
-  // Plain WENO faces are taken in pairs (see below); then the F- points are
-  // stored in reverse slot order, so that both splits read increasing slots.
-  // FP64 32-cell y tiles keep one face per lane: their 33rd face row on top
-  // of a pair takes them to 84 VGPRs, one workgroup per CU fewer (slower).
-  constexpr bool kPair = PAIRS && (S & (kPP | kMusta)) == 0 && (sizeof(R) == 4 || kTileA == 31 || LAST);
-  auto ms = [](int j) { return kPair ? kTileP - 1 - j : j; };
   R* sFp = s;                              // [5][kTileP][kTileXP]
   R* sFm = s + 5 * kTileP * kTileXP;       // [5][kTileP][kTileXP]
   const int nx = a.g.n[0], ny = a.g.n[1];
@@ -474,7 +434,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         sFp[(c * kTileP + ta + 4) * kTileXP + tx] = Fp[c];
-        sFm[(c * kTileP + ms(ta + 4)) * kTileXP + tx] = Fm[c];
+        sFm[(c * kTileP + ta + 4) * kTileXP + tx] = Fm[c];
       }
       if (LAST && own_ok) {
 #pragma unroll
@@ -499,7 +459,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         sFp[(c * kTileP + j) * kTileXP + tx] = Fp[c];
-        sFm[(c * kTileP + ms(j)) * kTileXP + tx] = Fm[c];
+        sFm[(c * kTileP + j) * kTileXP + tx] = Fm[c];
       }
     }
   }
@@ -510,49 +470,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
   R Fh[5], Fh2[5];
   const bool has1 = xin && ta < nf;
   const bool has2 = (kTileA + 1) * kTileX > 512 && xin && threadIdx.x < kTileX && kTileA < nf;
-  // Pairs: lane (q, h) = (ta >> 1, ta & 1) reconstructs split h (0: F+, 1: F-)
-  // of the face rows 2q and 2q + 1 from the 8 points they span, read in
-  // increasing slot order v0..v7: windows v0..v6 and v1..v7 share their
-  // differences and third-difference terms.  F+: v_j = slot 2q + j, the
-  // windows give rows 2q, 2q + 1; F- (mirrored stencils, reversed storage):
-  // v_j = F- at slot 2q + 8 - j, the windows give rows 2q + 1, 2q.  One field
-  // at a time: once every lane is past field c, its two split values per face
-  // row go into field c's own F+ and F- areas (rows in natural order), so a
-  // lane holds two results, not ten.
-  const int pq = ta >> 1, ph = ta & 1;
-  const bool hasp = kPair && xin && 2 * pq < nf;
-  if constexpr (kPair) {
-    const R* b = (ph ? sFm + (kTileP - 9 - 2 * pq) * kTileXP : sFp + 2 * pq * kTileXP) + tx;
-    R* dst = (ph ? sFm : sFp) + tx;
-    const int fa = 2 * pq + ph, fb = 2 * pq + 1 - ph;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      R lo, hi, f2p, f2m;
-      if (hasp) {
-        const R* v = b + c * kTileP * kTileXP;
-        const R v0 = v[0], v1 = v[kTileXP], v2 = v[2 * kTileXP], v3 = v[3 * kTileXP], v4 = v[4 * kTileXP],
-                v5 = v[5 * kTileXP], v6 = v[6 * kTileXP], v7 = v[7 * kTileXP];
-        weno7_pair<R, (S & 7)>(v0, v1, v2, v3, v4, v5, v6, v7, a.eps, lo, hi);
-      }
-      if (has2) {  // row kTileA: F+ at slots kTileA..kTileA+6, F- at kTileA+7..kTileA+1 (reversed: 0..6)
-        const R* fp = sFp + (c * kTileP + kTileA) * kTileXP + tx;
-        const R* fm = sFm + c * kTileP * kTileXP + tx;
-        f2p = weno7<R, (S & 7)>(fp[0], fp[kTileXP], fp[2 * kTileXP], fp[3 * kTileXP], fp[4 * kTileXP],
-                                fp[5 * kTileXP], fp[6 * kTileXP], a.eps);
-        f2m = weno7<R, (S & 7)>(fm[0], fm[kTileXP], fm[2 * kTileXP], fm[3 * kTileXP], fm[4 * kTileXP],
-                                fm[5 * kTileXP], fm[6 * kTileXP], a.eps);
-      }
-      __syncthreads();
-      if (hasp) {
-        dst[(c * kTileP + fa) * kTileXP] = lo;
-        dst[(c * kTileP + fb) * kTileXP] = hi;
-      }
-      if (has2) {
-        sFp[(c * kTileP + kTileA) * kTileXP + tx] = f2p;
-        sFm[(c * kTileP + kTileA) * kTileXP + tx] = f2m;
-      }
-    }
-  } else if constexpr ((S & kMusta) != 0) {  // face row f: points in slots f..f+7
+  if constexpr ((S & kMusta) != 0) {  // face row f: points in slots f..f+7
     auto at = [&](int f) {
       return [=](int c, int m) { return sFp[(c * kTileP + f + m) * kTileXP + tx]; };
     };
@@ -569,7 +487,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
                           fm[2 * kTileXP], fm[kTileXP], a.eps);
     }
   }
-  if ((S & kMusta) == 0 && !kPair && has2) {
+  if ((S & kMusta) == 0 && has2) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const R* fp = sFp + (c * kTileP + kTileA) * kTileXP + tx;
@@ -585,23 +503,16 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
     if (has2) tile_limit<R, kTileP, kTileXP>(Fh2, sFp, sFm, kTileA, tx, a.pp_mu);
   }
   __syncthreads();
-  // face values: pairs keep the two splits apart in the F+ and F- areas
-  // ([5][kTileP][kTileXP], rows 0..kTileA) and form the face flux F+ + F-
-  // where it is used; otherwise sF [5][kTileA + 1][kTileXP] holds it
-  constexpr int kFP = kPair ? kTileP : kTileA + 1;
-  R* sF = s;
-  R* sG = sFm;
-  if (!kPair) {
-    if (has1) {
+  R* sF = s;  // [5][kTileA + 1][kTileXP]
+  if (has1) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) sF[(c * kFP + ta) * kTileXP + tx] = Fh[c];
-    }
-    if (has2) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sF[(c * kFP + kTileA) * kTileXP + tx] = Fh2[c];
-    }
-    __syncthreads();
+    for (int c = 0; c < 5; ++c) sF[(c * (kTileA + 1) + ta) * kTileXP + tx] = Fh[c];
   }
+  if (has2) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) sF[(c * (kTileA + 1) + kTileA) * kTileXP + tx] = Fh2[c];
+  }
+  __syncthreads();
 
   if (own_ok) {
     // LAST, stages 2 and 3: the five U^n values are read before any output
@@ -614,10 +525,8 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
     }
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-      const int i0 = (c * kFP + ta) * kTileXP + tx, i1 = i0 + kTileXP;
-      const R fl = kPair ? sF[i0] + sG[i0] : sF[i0];
-      const R fr = kPair ? sF[i1] + sG[i1] : sF[i1];
-      const R div = (fl - fr) * a.inv_d;
+      const int i0 = (c * (kTileA + 1) + ta) * kTileXP + tx;
+      const R div = (sF[i0] - sF[i0 + kTileXP]) * a.inv_d;
       if (!LAST) {
         a.D[c * nc + cell] = dpre[c] + div;
       } else {
@@ -634,7 +543,183 @@ __global__ void __launch_bounds__(512) k_tile(StageArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int by = a.order ? blockIdx.z : blockIdx.y;  // tile along AX
   const int bz = a.order ? blockIdx.y : blockIdx.z;  // transverse index
-  tile_body<R, S, AX, LAST, A, true>(a, blockIdx.x, by, bz, reinterpret_cast<R*>(smem_raw));
+  tile_body<R, S, AX, LAST, A>(a, blockIdx.x, by, bz, reinterpret_cast<R*>(smem_raw));
+}
+
+// ---------------------------------------------------------------------------
+// Faces taken along lines (plain WENO fluxes; the limiter and MUSTA-FORCE use
+// the bodies above).  A lane marches over neighbouring faces of one split of
+// one field of its line, so that the differences and their indicator terms of
+// a point serve every face of the run (weno_line).  A workgroup has eight
+// waves, which the hardware deals evenly over the four SIMDs; the ten (field,
+// split) areas are shared out so that all have the same work: wave w marches
+// over area w, and the eight waves take the N field's two areas in short runs,
+// whose results stay in registers until a barrier.  (One wave per area: 24.0
+// ms for three steps at 256^3 FP64, two SIMDs with three waves and two with
+// two; four (field, split, half) units for some waves and six for others: 18.9
+// ms.)  F- is stored in reverse slot order, so that both splits march upwards.
+//
+// A run reads its values one ahead and stores each result, one face late, in
+// the place of its first value: the lanes of a wave execute their LDS
+// operations in order, and result j of a run follows the read of value j + 8,
+// the last that the run before it (8 faces back) needs from that place.
+constexpr int kLineBlock = 512;
+
+template <class R, int S, int L, class Idx>
+__device__ __forceinline__ void line_faces(R* area, Idx idx, R eps) {
+  R next = area[idx(0)], last = R(0);
+  weno_line<R, S, L>(
+      [&](int m) {
+        const R v = next;
+        if (m + 1 < L + 6) next = area[idx(m + 1)];
+        __asm__ __volatile__("" ::: "memory");
+        return v;
+      },
+      eps,
+      [&](int k, R x) {
+        if (k > 0) area[idx(k - 1)] = last;
+        last = x;
+        __asm__ __volatile__("" ::: "memory");
+      });
+  area[idx(L - 1)] = last;
+}
+
+// Line tiles: a workgroup owns A = 31 or 32 cells along AX by 16 lines (y and
+// z: 16 cells along x; x: 16 rows along y) at one value of the remaining axis.
+// One lane per own cell, and 128 lanes for the 4 ghost slots on each side,
+// recover the points and store their split AX-fluxes in LDS; four lane groups
+// of a wave march over the 32 face rows in runs of kLineRun, and with A = 32
+// lanes 0..159 take the 33rd row, one face each; each own cell's lane forms
+// its divergence.  D is loaded before the march (LAST: folded into the
+// combine's p = w + dt D, rk_pre), to hide its latency; x is the first axis
+// and assigns D.  x tiles load along x (coalesced) and keep a pitch of 17
+// words, so that their stores do not meet in a bank.
+constexpr int kLineRun = 8;
+
+template <class R, int S, int AX, bool LAST, int A>
+__device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
+  constexpr int kP = A + 8;  // points of a line
+  constexpr int kRow = AX == 0 ? kLineX + 1 : kLineX;
+  constexpr int kArea = kP * kRow;  // one (field, split): area 2 field + split
+  const int nx = a.g.n[0], ny = a.g.n[1];
+  const int n = a.g.n[AX];
+  const int no = a.g.n[AX == 0 ? 1 : 0];  // extent over the lines
+  const int bc = a.g.bc[AX];
+  const long long nc = a.g.nc;
+  const int stride = AX == 0 ? 1 : (AX == 1 ? nx : nx * ny);
+  const int t = threadIdx.x;
+  const int w = t >> 6;
+  const int a0 = by * A;
+  const int len = min(A, n - a0);
+  const long long base = AX == 0 ? ((long long)bz * ny + bx * kLineX) * nx
+                                 : (AX == 1 ? (long long)bz * nx * ny + bx * kLineX : (long long)bz * nx + bx * kLineX);
+  const int lstep = AX == 0 ? nx : 1;  // cells between lines
+  unsigned fix = 0;
+
+  // own cell of the lane: line tx, cell ta of the tile (lanes run along x in memory)
+  const int tx = AX == 0 ? t >> 5 : t & (kLineX - 1);
+  const int ta = AX == 0 ? t & 31 : t >> 4;
+  const bool own = bx * kLineX + tx < no && ta < len;
+  const long long cell = base + tx * lstep + (long long)(a0 + ta) * stride;
+  R dpre[5];
+  auto point = [&](int line, int slot, const R u[5]) {
+    R Fp[5], Fm[5];
+    point_values<R, S, AX>(u, Fp, Fm, fix);
+    R* sp = s + slot * kRow + line;
+    R* sm = s + kArea + (kP - 1 - slot) * kRow + line;
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      sp[2 * c * kArea] = Fp[c];
+      sm[2 * c * kArea] = Fm[c];
+    }
+  };
+  // waves 6 and 7 also take ghost slots 0..3 and len + 4..len + 7; their loads
+  // go first, so that their latency overlaps the own cells' recovery
+  const int gq = t - 384;
+  const int gl = AX == 0 ? gq >> 3 : gq & (kLineX - 1);
+  const int gh = AX == 0 ? gq & 7 : gq >> 4;
+  const int gslot = gh < 4 ? gh : gh + len;
+  const bool ghost = w >= 6 && bx * kLineX + gl < no;
+  R ug[5];
+  if (ghost) {
+    int p = a0 - 4 + gslot;
+    if ((unsigned)p >= (unsigned)n) p = map_idx(p, n, bc);
+    load5(a.W, nc, base + gl * lstep + (long long)p * stride, ug);
+  }
+  if (own) {
+    R u[5];
+    load5(a.W, nc, cell, u);
+    if (AX != 0) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) dpre[c] = a.D[c * nc + cell];
+    }
+    point(tx, ta + 4, u);
+    if (LAST) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) dpre[c] = rk_pre(a.stage, u[c], dpre[c], a.dt);
+    }
+  }
+  if (ghost) point(gl, gslot, ug);
+  __syncthreads();
+  // face row f: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, its result in
+  // row f; F- at slots f+7..f+1, stored from row A - f on, its result there
+  const int xl = t & (kLineX - 1), grp = (t >> 4) & 3;
+  {
+    R* area = s + w * kArea + grp * kLineRun * kRow + xl;
+#pragma unroll 1
+    for (int u = 0; u < 32; u += 4 * kLineRun, area += 4 * kLineRun * kRow)
+      line_faces<R, S, kLineRun>(area, [](int m) { return m * kRow; }, a.eps);
+  }
+  // N: split w & 1, rows 2q and 2q + 1, q = 4 (w >> 1) + grp
+  R* const nrow = s + (8 + (w & 1)) * kArea + ((w >> 1) * 8 + grp * 2) * kRow + xl;
+  R nf[2];
+  weno_line<R, S, 2>([&](int m) { return nrow[m * kRow]; }, a.eps, [&](int k, R v) { nf[k] = v; });
+  R ex = R(0);
+  const bool extra = A == 32 && t < 160;  // row 32 of area t / 16
+  R* const xrow = s + (t >> 4) * kArea + 32 * kRow + xl;
+  if (extra) {
+    weno_line<R, S, 1>([&](int m) { return xrow[m * kRow]; }, a.eps, [&](int, R v) { ex = v; });
+  }
+  __syncthreads();  // the points of N and of row 32 are no longer read
+  nrow[0] = nf[0];
+  nrow[kRow] = nf[1];
+  if (extra) *xrow = ex;
+  __syncthreads();
+  if (own) {
+    // LAST, stages 2 and 3: the five U^n values are read before any output
+    // is stored (out may be U^n itself, so the compiler would otherwise keep
+    // each read behind the previous field's store: five round trips)
+    R unv[5];
+    if (LAST && a.stage >= 2) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) unv[c] = a.Un[c * nc + cell];
+    }
+    const R* sp = s + ta * kRow + tx;
+    const R* sm = s + kArea + (A - 1 - ta) * kRow + tx;  // F- of the right face; the left face's follows
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      const R fl = sp[2 * c * kArea] + sm[2 * c * kArea + kRow];
+      const R fr = sp[2 * c * kArea + kRow] + sm[2 * c * kArea];
+      const R div = (fl - fr) * a.inv_d;
+      if (AX == 0) {
+        a.D[c * nc + cell] = div;
+      } else if (!LAST) {
+        a.D[c * nc + cell] = dpre[c] + div;
+      } else {
+        a.out[c * nc + cell] = rk_out_v(a.stage, dpre[c], div, a.dt, unv[c]);
+      }
+    }
+  }
+  add_fixups(a.fixups, fix);
+}
+
+template <class R, int S, int AX, bool LAST, int A>
+__global__ void __launch_bounds__(kLineBlock, 6) k_line(StageArgs<R> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  // blockIdx.x: 16 lines; tile along AX and transverse index in either order
+  const int by = a.order ? blockIdx.z : blockIdx.y;
+  const int bz = a.order ? blockIdx.y : blockIdx.z;
+  line_body<R, S, AX, LAST, A>(a, blockIdx.x, by, bz, reinterpret_cast<R*>(smem_raw));
 }
 
 // ---------------------------------------------------------------------------
@@ -969,7 +1054,7 @@ __device__ __forceinline__ int batch_event_of(const long long* off, int n, long 
   return lo;
 }
 
-template <class R>
+template <class R, int S>
 __device__ __forceinline__ StageArgs<R> batch_stage_args(const BatchEvent& ev, int stage, R eps, int AX) {
   StageArgs<R> a;
   R* U = static_cast<R*>(ev.U);
@@ -981,9 +1066,9 @@ __device__ __forceinline__ StageArgs<R> batch_stage_args(const BatchEvent& ev, i
   a.D = static_cast<R*>(ev.D);
   a.g = ev.g;
   a.order = 0;
-  a.inv_d = (R)ev.inv_d[AX];
   a.dt = (R)ev.dt;
   a.eps = eps;
+  face_scale<R, S>(a, ev.inv_d[AX]);
   a.stage = stage;
   a.seg = 0;
   a.fixups = &ev.dev->fixups;
@@ -1007,7 +1092,7 @@ __global__ void __launch_bounds__(512) k_btile(BatchArgs<R> b) {
     const int e = batch_event_of(b.off, b.n_events, it);
     const BatchEvent& ev = b.ev[e];
     const long long local = it - b.off[e];
-    const StageArgs<R> a = batch_stage_args<R>(ev, b.stage, b.eps, AX);
+    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
     const int A = tile_len(ev.g.n[AX]);
     if (AX == 0) {
       const int gx = (ev.g.n[0] + A - 1) / A, gy = (ev.g.n[1] + kXTileY - 1) / kXTileY;
@@ -1017,25 +1102,23 @@ __global__ void __launch_bounds__(512) k_btile(BatchArgs<R> b) {
     } else {
       const int gx = (ev.g.n[0] + kTileX - 1) / kTileX, ga = (ev.g.n[AX] + A - 1) / A;
       const int bx = (int)(local % gx), by = (int)((local / gx) % ga), bz = (int)(local / ((long long)gx * ga));
-      if (A == 31) tile_body<R, S, AX, AX == 2, 31, false>(a, bx, by, bz, s);
-      else tile_body<R, S, AX, AX == 2, 32, false>(a, bx, by, bz, s);
+      if (A == 31) tile_body<R, S, AX, AX == 2, 31>(a, bx, by, bz, s);
+      else tile_body<R, S, AX, AX == 2, 32>(a, bx, by, bz, s);
     }
     __syncthreads();  // the next item overwrites the LDS tile
   }
 }
 
 // The same when every event has the tile length A along the axis (the
-// launcher checks): one tile body instead of two, so the y/z faces are taken
-// in pairs as in the single-event kernels (same bits either way).  PERSIST:
-// workgroups walk items blockIdx.x, blockIdx.x + gridDim.x, ...; otherwise
-// one item per workgroup (the loop's live state costs ~20 VGPRs, a
-// workgroup per CU).
+// launcher checks): one tile body instead of two.  PERSIST: workgroups walk
+// items blockIdx.x, blockIdx.x + gridDim.x, ...; otherwise one item per
+// workgroup (the loop's live state costs ~20 VGPRs, a workgroup per CU).
 template <class R, int S, int AX, int A>
 __device__ __forceinline__ void btile_item(const BatchArgs<R>& b, long long it, R* s) {
   const int e = batch_event_of(b.off, b.n_events, it);
   const BatchEvent& ev = b.ev[e];
   const long long local = it - b.off[e];
-  const StageArgs<R> a = batch_stage_args<R>(ev, b.stage, b.eps, AX);
+  const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
   if (AX == 0) {
     const int gx = (ev.g.n[0] + A - 1) / A, gy = (ev.g.n[1] + kXTileY - 1) / kXTileY;
     const int bx = (int)(local % gx), by = (int)((local / gx) % gy), bz = (int)(local / ((long long)gx * gy));
@@ -1043,7 +1126,7 @@ __device__ __forceinline__ void btile_item(const BatchArgs<R>& b, long long it, 
   } else {
     const int gx = (ev.g.n[0] + kTileX - 1) / kTileX, ga = (ev.g.n[AX] + A - 1) / A;
     const int bx = (int)(local % gx), by = (int)((local / gx) % ga), bz = (int)(local / ((long long)gx * ga));
-    tile_body<R, S, AX, AX == 2, A, true>(a, bx, by, bz, s);
+    tile_body<R, S, AX, AX == 2, A>(a, bx, by, bz, s);
   }
 }
 
@@ -1061,6 +1144,43 @@ __global__ void __launch_bounds__(512) k_btile_u(BatchArgs<R> b) {
   }
 }
 
+// Plain WENO faces: line tiles of every event (line_body; tile length 31 or
+// 32 by event).  PERSIST as above.
+template <class R, int S, int AX, int A>
+__device__ __forceinline__ void bline_item(const BatchArgs<R>& b, const BatchEvent& ev, long long local, R* s) {
+  const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
+  const int T = (ev.g.n[AX] + A - 1) / A;
+  const int gx = (ev.g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX;
+  const int bx = (int)(local % gx), by = (int)((local / gx) % T), bz = (int)(local / ((long long)gx * T));
+  line_body<R, S, AX, AX == 2, A>(a, bx, by, bz, s);
+}
+
+// A: the tile length of every event along the axis, 0 where they differ.
+template <class R, int S, int AX, int A, bool PERSIST>
+__global__ void __launch_bounds__(kLineBlock) k_bline(BatchArgs<R> b) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  R* s = reinterpret_cast<R*>(smem_raw);
+  auto item = [&](long long it) {
+    const int e = batch_event_of(b.off, b.n_events, it);
+    const BatchEvent& ev = b.ev[e];
+    const long long local = it - b.off[e];
+    if constexpr (A != 0) {
+      bline_item<R, S, AX, A>(b, ev, local, s);
+    } else {
+      if (tile_len(ev.g.n[AX]) == 31) bline_item<R, S, AX, 31>(b, ev, local, s);
+      else bline_item<R, S, AX, 32>(b, ev, local, s);
+    }
+  };
+  if constexpr (PERSIST) {
+    for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
+      item(it);
+      __syncthreads();  // the next item overwrites the LDS tile
+    }
+  } else {
+    if ((long long)blockIdx.x < b.items) item(blockIdx.x);  // uniform
+  }
+}
+
 // x rows of every event: items are groups of TB / nx rows (xrows_body).
 template <class R, int S, int TB>
 __global__ void __launch_bounds__(TB) k_bxrows(BatchArgs<R> b) {
@@ -1070,8 +1190,8 @@ __global__ void __launch_bounds__(TB) k_bxrows(BatchArgs<R> b) {
     const int e = batch_event_of(b.off, b.n_events, it);
     const BatchEvent& ev = b.ev[e];
     const int rpi = xrow_rows(ev.g.n[0], TB, (int)sizeof(R));
-    const StageArgs<R> a = batch_stage_args<R>(ev, b.stage, b.eps, 0);
-    xrows_body<R, S, sizeof(R) == 4>(a, (it - b.off[e]) * rpi, rpi, s);  // FP64 pairs cost 18 VGPRs here
+    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, 0);
+    xrows_body<R, S>(a, (it - b.off[e]) * rpi, rpi, s);
     __syncthreads();  // the next item overwrites the LDS rows
   }
 }
@@ -1083,7 +1203,7 @@ __global__ void __launch_bounds__(kXBoundRows * 10) k_bxbound(BatchArgs<R> b) {
   for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
     const int e = batch_event_of(b.off, b.n_events, it);
     const BatchEvent& ev = b.ev[e];
-    const StageArgs<R> a = batch_stage_args<R>(ev, b.stage, b.eps, 0);
+    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, 0);
     xbound_body<R, S>(a, it - b.off[e]);
     __syncthreads();
   }
@@ -1129,11 +1249,27 @@ __global__ void k_bstep(long long* step) {
 
 // ---------------------------------------------------------------------------
 // Host-side launchers (called from hydro_api.hip).
+// Line tiles along AX.
+template <class R, int S, int AX>
+void launch_line_t(const StageArgs<R>& base, hipStream_t st) {
+  StageArgs<R> a = base;
+  face_scale<R, S>(a, 1.0 / a.g.dx[AX]);
+  const int n = a.g.n[AX];
+  const int A = tile_len(n);
+  a.order = AX == 0 ? 0 : (base.order >> (AX - 1)) & 1;
+  const int no = AX == 2 ? a.g.n[1] : a.g.n[2];
+  dim3 grid((a.g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX, (n + A - 1) / A, no);
+  if (a.order) grid = dim3(grid.x, no, grid.y);
+  const size_t lds = line_lds_bytes(AX, A, (int)sizeof(R));
+  if (A == 31) hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 31>), grid, dim3(kLineBlock), lds, st, a);
+  else hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 32>), grid, dim3(kLineBlock), lds, st, a);
+}
+
 template <class R, int S>
 void launch_xface_t(const StageArgs<R>& base, hipStream_t st) {
   StageArgs<R> a = base;
   const int nx = a.g.n[0];
-  a.inv_d = R(1.0 / a.g.dx[0]);
+  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
   const int n1 = nx;
   const int TB = xrow_block(&n1, 1, (int)sizeof(R));
   const int rpi = xrow_rows(nx, TB, (int)sizeof(R));
@@ -1151,7 +1287,7 @@ void launch_xface_t(const StageArgs<R>& base, hipStream_t st) {
 template <class R, int S>
 void launch_xbound_t(const StageArgs<R>& base, hipStream_t st) {
   StageArgs<R> a = base;
-  a.inv_d = R(1.0 / a.g.dx[0]);
+  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
   const long long rows = (long long)a.g.n[1] * a.g.n[2];
   const unsigned nb = (unsigned)((rows + kXBoundRows - 1) / kXBoundRows);
   hipLaunchKernelGGL((k_xbound<R, S>), dim3(nb), dim3(kXBoundRows * 10), 0, st, a);
@@ -1162,7 +1298,7 @@ void launch_march_t(const StageArgs<R>& base, int seg, hipStream_t st) {
   StageArgs<R> a = base;
   const int nx = a.g.n[0], ny = a.g.n[1], nz = a.g.n[2];
   a.seg = seg;
-  a.inv_d = R(1.0 / a.g.dx[AX]);
+  face_scale<R, S>(a, 1.0 / a.g.dx[AX]);
   const int n = (AX == 1) ? ny : nz;
   const int no = (AX == 1) ? nz : ny;
   dim3 grid((nx + 63) / 64, (no + 3) / 4, (n + seg - 1) / seg);
@@ -1173,7 +1309,7 @@ template <class R, int S, int AX>
 void launch_tile_t(const StageArgs<R>& base, hipStream_t st) {
   StageArgs<R> a = base;
   const int nx = a.g.n[0];
-  a.inv_d = R(1.0 / a.g.dx[AX]);
+  face_scale<R, S>(a, 1.0 / a.g.dx[AX]);
   const int n = a.g.n[AX];
   const int no = (AX == 1) ? a.g.n[2] : a.g.n[1];
   const int A = tile_len(n);
@@ -1188,7 +1324,7 @@ void launch_tile_t(const StageArgs<R>& base, hipStream_t st) {
 template <class R, int S>
 void launch_xtile_t(const StageArgs<R>& base, hipStream_t st) {
   StageArgs<R> a = base;
-  a.inv_d = R(1.0 / a.g.dx[0]);
+  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
   const int A = tile_len(a.g.n[0]);
   const size_t lds = (size_t)2 * 5 * (A + 8) * kXTileY * sizeof(R);
   dim3 grid((a.g.n[0] + A - 1) / A, (a.g.n[1] + kXTileY - 1) / kXTileY, a.g.n[2]);
@@ -1202,13 +1338,24 @@ template <class R>
 hipError_t launch_face_kernel(int kernel, const StageArgs<R>& a, int scheme, int seg, hipStream_t st) {
 #define HYDRO_DISPATCH(S)                                  \
   switch (kernel) {                                        \
-    case 0: launch_xface_t<R, S>(a, st); break;            \
-    case 1: launch_xbound_t<R, S>(a, st); break;           \
     case 2: launch_march_t<R, S, 1>(a, seg, st); break;    \
     case 3: launch_march_t<R, S, 2>(a, seg, st); break;    \
-    case 4: launch_tile_t<R, S, 1>(a, st); break;          \
-    case 5: launch_tile_t<R, S, 2>(a, st); break;          \
-    default: launch_xtile_t<R, S>(a, st); break;           \
+    default:                                               \
+      if constexpr (line_scheme(S)) {                      \
+        switch (kernel) {                                  \
+          case 4: launch_line_t<R, S, 1>(a, st); break;    \
+          case 5: launch_line_t<R, S, 2>(a, st); break;    \
+          default: launch_line_t<R, S, 0>(a, st); break;   \
+        }                                                  \
+      } else {                                             \
+        switch (kernel) {                                  \
+          case 0: launch_xface_t<R, S>(a, st); break;      \
+          case 1: launch_xbound_t<R, S>(a, st); break;     \
+          case 4: launch_tile_t<R, S, 1>(a, st); break;    \
+          case 5: launch_tile_t<R, S, 2>(a, st); break;    \
+          default: launch_xtile_t<R, S>(a, st); break;     \
+        }                                                  \
+      }                                                    \
   }
   switch (scheme) {
     case kWenoJS: HYDRO_DISPATCH(kWenoJS) break;
@@ -1259,20 +1406,20 @@ hipError_t launch_primitives(const R* U, R* prim, long long nc, double g, double
 }
 
 // Work items of one event for the batched launches: 0 x tiles, 1 and 2 y/z
-// tiles, 3 x-row groups of xrow_rows(nx, xtb) rows, 4 groups of kXBoundRows
-// rows for the outflow x face (none for periodic x).  An x pass is either 0
-// or 3 + 4.
-long long batch_items(int AX, const Grid& g, int xtb, int elem) {
+// tiles, 3 x-row groups, 4 groups of kXBoundRows rows for the outflow x face
+// (none for periodic x).  An x pass is either 0 or 3 + 4; plain WENO faces
+// take x tiles always (3: the same tiles, 4: none).
+long long batch_items(int AX, const Grid& g, int scheme, int xtb, int elem) {
   const long long rows = (long long)g.n[1] * g.n[2];
+  const bool lines = line_scheme(scheme);
+  if (lines && AX == 3) AX = 0;
   if (AX == 3) {
     const int rpi = xrow_rows(g.n[0], xtb, elem);
     return (rows + rpi - 1) / rpi;
   }
-  if (AX == 4) return g.bc[0] ? 0 : (rows + kXBoundRows - 1) / kXBoundRows;
-  const int A = tile_len(g.n[AX]);
-  if (AX == 0) return (long long)((g.n[0] + A - 1) / A) * ((g.n[1] + kXTileY - 1) / kXTileY) * g.n[2];
-  const int no = AX == 1 ? g.n[2] : g.n[1];
-  return (long long)((g.n[0] + kTileX - 1) / kTileX) * ((g.n[AX] + A - 1) / A) * no;
+  if (AX == 4) return g.bc[0] || lines ? 0 : (rows + kXBoundRows - 1) / kXBoundRows;
+  const int A = tile_len(g.n[AX]), no = AX == 2 ? g.n[1] : g.n[2];
+  return (long long)((g.n[AX] + A - 1) / A) * ((g.n[AX == 0 ? 1 : 0] + 15) / 16) * no;
 }
 
 // blocks: workgroups of the launch (0: one per item).
@@ -1289,53 +1436,83 @@ void launch_btile_u(int AX, int A, bool persist, dim3 grid, const BatchArgs<R>& 
 #undef HYDRO_BTU
 }
 
+// Plain WENO faces.
+template <class R, int S, int AX>
+void launch_bline_ax(bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
+  const dim3 tb(kLineBlock);
+  const size_t lds = line_lds_bytes(AX, b.tile_a == 31 ? 31 : 32, (int)sizeof(R));
+  if (b.tile_a == 31) {
+    if (persist) hipLaunchKernelGGL((k_bline<R, S, AX, 31, true>), grid, tb, lds, st, b);
+    else hipLaunchKernelGGL((k_bline<R, S, AX, 31, false>), grid, tb, lds, st, b);
+  } else if (b.tile_a == 32) {
+    if (persist) hipLaunchKernelGGL((k_bline<R, S, AX, 32, true>), grid, tb, lds, st, b);
+    else hipLaunchKernelGGL((k_bline<R, S, AX, 32, false>), grid, tb, lds, st, b);
+  } else {
+    hipLaunchKernelGGL((k_bline<R, S, AX, 0, true>), grid, tb, lds, st, b);
+  }
+}
+
+template <class R, int S>
+void launch_bline(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
+  if (AX == 0 || AX == 3) launch_bline_ax<R, S, 0>(persist, grid, b, st);
+  if (AX == 1) launch_bline_ax<R, S, 1>(persist, grid, b, st);
+  if (AX == 2) launch_bline_ax<R, S, 2>(persist, grid, b, st);
+}
+
+// The limiter and MUSTA-FORCE.
+template <class R, int S>
+void launch_bface(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
+  const size_t lds = (size_t)2 * 5 * (32 + 8) * 16 * sizeof(R);  // the largest tile (A = 32)
+  const dim3 tb(512);
+  const size_t xl = (size_t)b.xlds;
+  if (AX == 3) {
+    switch (b.xtb) {
+      case 256: hipLaunchKernelGGL((k_bxrows<R, S, 256>), grid, dim3(256), xl, st, b); break;
+      case 384: hipLaunchKernelGGL((k_bxrows<R, S, 384>), grid, dim3(384), xl, st, b); break;
+      case 512: hipLaunchKernelGGL((k_bxrows<R, S, 512>), grid, dim3(512), xl, st, b); break;
+      default: hipLaunchKernelGGL((k_bxrows<R, S, 1024>), grid, dim3(1024), xl, st, b); break;
+    }
+    return;
+  }
+  if (AX == 4) {
+    hipLaunchKernelGGL((k_bxbound<R, S>), grid, dim3(kXBoundRows * 10), 0, st, b);
+    return;
+  }
+  // the uniform-tile-length kernels for WENO7-Z with the limiter (the other
+  // limited schemes and MUSTA-FORCE keep the general one)
+  if constexpr (S == (kWenoZ | kPP)) {
+    if (b.tile_a == 31 || b.tile_a == 32) {
+      launch_btile_u<R, S>(AX, b.tile_a, persist, grid, b, st);
+      return;
+    }
+  }
+  if (AX == 0) hipLaunchKernelGGL((k_btile<R, S, 0>), grid, tb, lds, st, b);
+  else if (AX == 1) hipLaunchKernelGGL((k_btile<R, S, 1>), grid, tb, lds, st, b);
+  else hipLaunchKernelGGL((k_btile<R, S, 2>), grid, tb, lds, st, b);
+}
+
 template <class R>
 hipError_t launch_batch_axis(int AX, const BatchArgs<R>& b, int scheme, long long blocks, hipStream_t st) {
   const long long nb = (blocks <= 0 || blocks > b.items) ? b.items : blocks;
   if (nb <= 0) return hipSuccess;
-  const size_t lds = (size_t)2 * 5 * (32 + 8) * 16 * sizeof(R);  // the largest y/z tile (A = 32)
-  const dim3 grid((unsigned)nb), tb(512);
-  const size_t xl = (size_t)b.xlds;
-  // the uniform-tile-length kernels for plain WENO faces and WENO7-Z with the
-  // limiter (the other limited schemes and MUSTA-FORCE keep the general one)
-  const bool uni = (scheme & (kPP | kMusta)) == 0 || scheme == (kWenoZ | kPP);
-#define HYDRO_BAXIS(S)                                                                                      \
-  if (AX == 3) {                                                                                            \
-    switch (b.xtb) {                                                                                        \
-      case 256: hipLaunchKernelGGL((k_bxrows<R, S, 256>), grid, dim3(256), xl, st, b); break;                 \
-      case 384: hipLaunchKernelGGL((k_bxrows<R, S, 384>), grid, dim3(384), xl, st, b); break;                 \
-      case 512: hipLaunchKernelGGL((k_bxrows<R, S, 512>), grid, dim3(512), xl, st, b); break;                 \
-      default: hipLaunchKernelGGL((k_bxrows<R, S, 1024>), grid, dim3(1024), xl, st, b); break;                \
-    }                                                                                                       \
-  } else if (AX == 4) {                                                                                     \
-    hipLaunchKernelGGL((k_bxbound<R, S>), grid, dim3(kXBoundRows * 10), 0, st, b);                          \
-  } else if (uni && (b.tile_a == 31 || b.tile_a == 32)) {                                                  \
-    if ((S & kPP) != 0) launch_btile_u<R, (kWenoZ | kPP)>(AX, b.tile_a, nb < b.items, grid, b, st);         \
-    else launch_btile_u<R, (S & 7)>(AX, b.tile_a, nb < b.items, grid, b, st);                                \
-  } else if (AX == 0) {                                                                                     \
-    hipLaunchKernelGGL((k_btile<R, S, 0>), grid, tb, lds, st, b);                                          \
-  } else if (AX == 1) {                                                                                     \
-    hipLaunchKernelGGL((k_btile<R, S, 1>), grid, tb, lds, st, b);                                          \
-  } else {                                                                                                  \
-    hipLaunchKernelGGL((k_btile<R, S, 2>), grid, tb, lds, st, b);                                          \
-  }
+  const dim3 grid((unsigned)nb);
+  const bool persist = nb < b.items;
   switch (scheme) {
-    case kWenoJS: HYDRO_BAXIS(kWenoJS) break;
-    case kWenoLinear: HYDRO_BAXIS(kWenoLinear) break;
-    case kWeno5Z: HYDRO_BAXIS(kWeno5Z) break;
-    case kWeno5JS: HYDRO_BAXIS(kWeno5JS) break;
-    case kWeno5Linear: HYDRO_BAXIS(kWeno5Linear) break;
-    case kWenoZ | kPP: HYDRO_BAXIS(kWenoZ | kPP) break;
-    case kWenoJS | kPP: HYDRO_BAXIS(kWenoJS | kPP) break;
-    case kWenoLinear | kPP: HYDRO_BAXIS(kWenoLinear | kPP) break;
-    case kWeno5Z | kPP: HYDRO_BAXIS(kWeno5Z | kPP) break;
-    case kWeno5JS | kPP: HYDRO_BAXIS(kWeno5JS | kPP) break;
-    case kWeno5Linear | kPP: HYDRO_BAXIS(kWeno5Linear | kPP) break;
-    case kWenoZ | kMusta: HYDRO_BAXIS(kWenoZ | kMusta) break;
-    case kWeno5Z | kMusta: HYDRO_BAXIS(kWeno5Z | kMusta) break;
-    default: HYDRO_BAXIS(kWenoZ) break;
+    case kWenoJS: launch_bline<R, kWenoJS>(AX, persist, grid, b, st); break;
+    case kWenoLinear: launch_bline<R, kWenoLinear>(AX, persist, grid, b, st); break;
+    case kWeno5Z: launch_bline<R, kWeno5Z>(AX, persist, grid, b, st); break;
+    case kWeno5JS: launch_bline<R, kWeno5JS>(AX, persist, grid, b, st); break;
+    case kWeno5Linear: launch_bline<R, kWeno5Linear>(AX, persist, grid, b, st); break;
+    case kWenoZ | kPP: launch_bface<R, (kWenoZ | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoJS | kPP: launch_bface<R, (kWenoJS | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoLinear | kPP: launch_bface<R, (kWenoLinear | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5Z | kPP: launch_bface<R, (kWeno5Z | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5JS | kPP: launch_bface<R, (kWeno5JS | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5Linear | kPP: launch_bface<R, (kWeno5Linear | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoZ | kMusta: launch_bface<R, (kWenoZ | kMusta)>(AX, persist, grid, b, st); break;
+    case kWeno5Z | kMusta: launch_bface<R, (kWeno5Z | kMusta)>(AX, persist, grid, b, st); break;
+    default: launch_bline<R, kWenoZ>(AX, persist, grid, b, st); break;
   }
-#undef HYDRO_BAXIS
   return hipGetLastError();
 }
 
