@@ -1,0 +1,100 @@
+"""Faces along lines (tiles of 31 or 32 cells by 16 lines, runs of eight
+faces; plain WENO fluxes) at the edges of tiles, runs and line groups: one
+right-hand side of a rough admissible state against the oracle, and the same
+step through the batch.
+
+Bar: a face value is a few dozen roundings of numbers up to max |U|, and L
+divides a difference of two of them by dx on each axis, so with u = 2^-53
+(FP32: 2^-24) |dL| <= 128 u max |U| sum 1/dx.  The WENO-Z weights of a rough
+state are O(1) functions of the indicators, whose relative rounding they
+return undiminished; that is inside the factor.
+"""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1511_02137_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+# edges of a tile (31 | 32 cells), of a run (8 faces), of a line group (16)
+SHAPES = [(1, 1, 1), (2, 17, 31), (31, 16, 1), (32, 15, 8), (33, 7, 32), (7, 62, 33), (63, 3, 9), (9, 64, 16),
+          (16, 32, 65), (124, 2, 5)]
+
+
+@pytest.fixture(scope="module", autouse=True)
+def need_gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+
+
+def H():
+    from paper_1511_02137_amd import hydro
+    return hydro
+
+
+def rough_state(n, seed):
+    rng = np.random.default_rng(seed)
+    nx, ny, nz = n
+    U = np.empty((5, nz, ny, nx))
+    U[0] = rng.uniform(1.0, 3.0, (nz, ny, nx))
+    U[1:4] = U[0] * rng.uniform(-0.4, 0.4, (3, nz, ny, nx))
+    U[4] = rng.uniform(0.1, 1.0, (nz, ny, nx))
+    return U
+
+
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", SHAPES)
+def test_rhs_at_tile_edges(n, bc):
+    w = W.small_event(1, n=n, with_jet=False)
+    for precision, weno, u in (("f64", "z", 2.0 ** -53), ("f64", "z5", 2.0 ** -53), ("f64", "js", 2.0 ** -53),
+                               ("f32", "z", 2.0 ** -24)):
+        U = rough_state(n, sum(n))
+        if precision == "f32":
+            U = U.astype(np.float32).astype(np.float64)
+        pb = O.Problem(n=w.n, bc=(bc,) * 3, weno=weno)
+        Lo, _, _ = O.rhs(pb, U, 1.0, [])
+        h = H().from_workload(w, precision=precision, weno=weno, bc=(bc,) * 3)
+        L = h.rhs(torch.from_numpy(U).to("cuda", h.dtype), 1.0).double().cpu().numpy()
+        bar = 128 * u * np.abs(U).max() * 30.0
+        err = np.abs(L - Lo).max()
+        print(n, bc, precision, weno, "max |dL| %.2e bar %.2e" % (err, bar), flush=True)
+        assert err <= bar
+        h.close()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batch_of_mixed_tile_lengths_is_bitwise(precision):
+    # tile lengths 31 and 32 in one batch (no common one), persistent and not
+    ws = [W.small_event(k, n=n) for k, n in enumerate([(31, 64, 20), (32, 31, 33), (5, 40, 62)])]
+    single = []
+    for w in ws:
+        h = H().from_workload(w, precision=precision)
+        h.step(2)
+        torch.cuda.synchronize()
+        single.append(h.U.cpu().numpy())
+        h.close()
+    b = H().batch_from_workloads(ws, precision=precision)
+    b.run(2)
+    torch.cuda.synchronize()
+    for e, U in enumerate(single):
+        assert np.array_equal(b.U[e].cpu().numpy(), U), e
+
+
+def test_freezeout_range_of_p_t():
+    """p_T from 1e-3 to where every exponential is subnormal or zero: rows
+    within 1e-12 of their largest value (an exponent x carries x 2^-53, 6e-14
+    at 570), a row beyond the range exactly zero with zero harmonics."""
+    w = W.small_event(1, n=(21, 18, 13), steps=0)
+    h = H().from_workload(w)
+    pt = [1e-3, 1.0, 200.0, 1e4]
+    spec, harm = h.freezeout(n_phi=48, pt=pt, n_harm=4)
+    spec, harm = spec.cpu().numpy(), harm.cpu().numpy()
+    pb = O.Problem(n=w.n, dx=w.dx, t0=w.t0, dt=w.dt)
+    rs, _, _ = O.freezeout(pb, h.U.cpu().numpy(), n_phi=48, pt=pt, T_min=0.0, dof=1.0, n_harm=4)
+    for r in range(4):
+        assert np.abs(spec[r] - rs[r]).max() <= 1e-12 * np.abs(rs[r]).max(), r
+    assert np.all(rs[4] == 0.0) and np.all(spec[4] == 0.0) and np.all(harm[4] == 0.0)
+    h.close()
