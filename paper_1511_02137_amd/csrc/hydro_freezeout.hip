@@ -16,7 +16,7 @@
 // each, so the pass is arithmetic, not traffic: each workgroup recovers the
 // primitives of 256 cells at a time (FP64, coalesced loads of the five
 // fields), keeps per cell (w = g dV 2 T^3/gamma^3 / (2 pi hbar c)^3, vx, vy,
-// gamma/T, g dV/(2 pi hbar c)^3) in LDS, and each lane then adds those cells
+// gamma/T) in LDS, and each lane then adds those cells
 // to the outputs it owns, reading the cell values as LDS broadcasts.  Up to
 // 256 azimuths a lane owns one azimuth in every row (D and gamma D/T once per
 // cell and azimuth; the p_T rows' exponentials by a table-driven exp), and
@@ -131,43 +131,47 @@ __global__ void __launch_bounds__(kFoThreads) k_fo_partial(FreezeArgs<R> a) {
   }
 }
 
-// e^x for x <= 0 in FP64 by a table-driven reduction (Tang's method):
-// x = (32 k + j) ln2/32 + r with |r| <= ln2/64, e^x = 2^k 2^(j/32) e^r, e^r
-// from its Taylor polynomial of degree 6 (remainder below r^7/7! < 2e-18),
-// 2^(j/32) from the table `tab` (32 entries), ln2/32 split in a 32-bit high
-// part (exact products t * hi) and a low part.  Within 2 ulp of e^x (checked
-// against extended-precision exp on 2e7 points of [-745, 0]); 0 below -745.2,
-// where e^x rounds to zero.
-__device__ __forceinline__ double exp_neg(double x, const double* tab) {
-  const double xc = fmax(x, -746.0);  // keeps t within int (below -745.2 the result is 0 anyway)
-  const double t = rint(xc * 46.16624130844683);  // x 32/ln2
-  const int n = (int)t;
-  const int j = n & 31, k = n >> 5;
-  const double r = fma(-t, -0x1.718432a1b0e26p-40, fma(-t, 0x1.62e42ff000000p-6, xc));
-  double p = fma(r, 1.0 / 720.0, 1.0 / 120.0);
-  p = fma(r, p, 1.0 / 24.0);
-  p = fma(r, p, 1.0 / 6.0);
-  p = fma(r, p, 0.5);
-  p = fma(r, p, 1.0);
-  p = fma(r, p, 1.0);
-  const double v = ldexp(tab[j] * p, k);
-  return x < -745.2 ? 0.0 : v;
+// e^-p s' for p s' >= 0 in FP64 by a table-driven reduction (Tang's method), s
+// = s' kExpN / ln2 given: p s = -(kExpN k + j) - r with |r| <= 1/2, e^-ps' =
+// 2^k 2^(j/kExpN) e^(r ln2/kExpN).  Adding and subtracting 1.5 2^52 rounds -p s
+// to the integer, whose two's complement is in the low word of the sum, and r
+// is one fma's rounding of the exact remainder.  With kExpN = 2048 entries a
+// cubic is enough (remainder below (ln2/4096)^4/24 = 3.5e-17) and the table is
+// 16 KiB of LDS.  smax = 2^30 / p keeps the integer in range; the result there
+// is 0, as for every p s' above 745.2.
+constexpr int kExpN = 2048;
+constexpr double kExpMagic = 6755399441055744.0;           // 1.5 2^52
+constexpr double kExpScale = 2954.6394437405970706;        // kExpN / ln2
+constexpr double kExpC1 = 3.3845077175778579561e-4;        // ln2 / kExpN
+constexpr double kExpC2 = kExpC1 * kExpC1 / 2.0, kExpC3 = kExpC1 * kExpC1 * kExpC1 / 6.0;
+__device__ __forceinline__ double exp_neg(double p, double s, double smax, const double* tab) {
+  const double sc = fmin(s, smax);
+  const double t = fma(-p, sc, kExpMagic);
+  const int n = __double2loint(t);
+  const double r = fma(-p, sc, kExpMagic - t);
+  const double q = r * fma(r, fma(r, kExpC3, kExpC2), kExpC1);
+  const double v = tab[n & (kExpN - 1)];
+  return ldexp(fma(v, q, v), n >> 11);
 }
 
 // The spectra with lanes owning azimuths (n_phi <= 256): lane tid is in group
 // tid / n_phi (groups = 256 / n_phi split the chunk's cells) and owns azimuth
 // tid % n_phi in every row, so D = 1 - vx cos phi - vy sin phi and gamma D / T
 // are formed once per cell and azimuth for all rows.  Row r > 0 adds
-// g dV/(2 pi hbar c)^3 p_T exp(-p_T gamma D / T) with exp_neg; the rows' sums
-// are reduced over the groups one row at a time, in group order.  MP >= n_pt
-// bounds the rows at compile time (the accumulators stay in registers).
+// exp(-p_T gamma D / T) with exp_neg, its factor g dV/(2 pi hbar c)^3 p_T at
+// the end; the rows' sums are reduced over the groups one row at a time, in
+// group order.  MP >= n_pt bounds the rows at compile time (the accumulators
+// stay in registers).  Bound by FP64 issue: 12 operations per cell, azimuth
+// and p_T row (a 32-entry table with a degree-6 polynomial, rint and range
+// selects: 21; 256^3, 64 azimuths, five p_T rows: 5.15 ms).
 template <class R, int MP>
 __global__ void __launch_bounds__(kFoThreads) k_fo_phi(FreezeArgs<R> a) {
-  __shared__ double s_w[kFoThreads], s_vx[kFoThreads], s_vy[kFoThreads], s_gt[kFoThreads], s_wp[kFoThreads];
+  __shared__ double4 s_cell[kFoThreads];  // w, vx, vy, gamma/T (scaled; 0: left out)
   __shared__ double s_red[kFoThreads];
-  __shared__ double s_tab[32];
+  __shared__ double s_tab[MP > 0 ? kExpN : 1];
   const int tid = threadIdx.x;
-  if (tid < 32) s_tab[tid] = exp2((double)tid / 32.0);
+  if (MP > 0)
+    for (int j = tid; j < kExpN; j += kFoThreads) s_tab[j] = exp2((double)j / kExpN);
   const int grp = tid / a.n_phi;
   const int k = tid % a.n_phi;
   const bool active = grp < a.groups;
@@ -181,7 +185,7 @@ __global__ void __launch_bounds__(kFoThreads) k_fo_phi(FreezeArgs<R> a) {
   const long long nchunk = (a.nc + kFoThreads - 1) / kFoThreads;
   for (long long ch = blockIdx.x; ch < nchunk; ch += gridDim.x) {
     const long long cell = ch * kFoThreads + tid;
-    double w = 0.0, wp = 0.0, vx = 0.0, vy = 0.0, gt = 0.0;
+    double4 cv = {0.0, 0.0, 0.0, 0.0};
     if (cell < a.nc) {
       R u[5];
       load5(a.U, a.nc, cell, u);
@@ -190,36 +194,29 @@ __global__ void __launch_bounds__(kFoThreads) k_fo_phi(FreezeArgs<R> a) {
       if (T >= a.T_min) {
         const double v2 = pv.v[0] * pv.v[0] + pv.v[1] * pv.v[1] + pv.v[2] * pv.v[2];
         const double ig = sqrt_nr(1.0 - v2);  // 1/gamma
-        w = a.pref_dV * 2.0 * (T * ig) * (T * ig) * (T * ig);
-        wp = a.pref_dV;
-        gt = div_nr(1.0, ig * T);
-        vx = pv.v[0];
-        vy = pv.v[1];
+        cv.x = a.pref_dV * 2.0 * (T * ig) * (T * ig) * (T * ig);
+        cv.y = pv.v[0];
+        cv.z = pv.v[1];
+        cv.w = div_nr(kExpScale, ig * T);
       }
     }
     __syncthreads();  // the previous chunk is no longer read
-    s_w[tid] = w;
-    s_wp[tid] = wp;
-    s_vx[tid] = vx;
-    s_vy[tid] = vy;
-    s_gt[tid] = gt;
+    s_cell[tid] = cv;
     __syncthreads();
     const int ncell = (int)min((long long)kFoThreads, a.nc - ch * kFoThreads);
     if (active) {
       for (int c = grp; c < ncell; c += a.groups) {
-        const double cwp = s_wp[c];
-        if (cwp == 0.0) continue;  // below T_min (or past the grid): contributes nothing
-        const double cw = s_w[c], cvx = s_vx[c], cvy = s_vy[c], cgt = s_gt[c];
-        const double D = fma(-cvy, sph, fma(-cvx, cph, 1.0));
-        const double q = rcp_nr(D);
-        acc[0] = fma(cw, q * q * q, acc[0]);
-        const double aD = cgt * D;
+        const double4 v = s_cell[c];
+        if (v.w == 0.0) continue;  // below T_min: contributes nothing
+        const double D = fma(-v.z, sph, fma(-v.y, cph, 1.0));
+        const double i0 = __builtin_amdgcn_rcp(D);
+        const double d = fma(-D, i0, 1.0);
+        const double q = fma(i0, fma(d, d, d), i0);
+        acc[0] = fma(v.x, q * q * q, acc[0]);
+        const double aD = v.w * D;
 #pragma unroll
         for (int r = 1; r <= MP; ++r) {
-          if (r <= npt) {  // uniform
-            const double ptv = a.pt[r - 1];
-            acc[r] = fma(cwp * ptv, exp_neg(-ptv * aD, s_tab), acc[r]);
-          }
+          if (r <= npt) acc[r] += exp_neg(a.pt[r - 1], aD, a.smax[r - 1], s_tab);  // uniform
         }
       }
     }
@@ -230,7 +227,7 @@ __global__ void __launch_bounds__(kFoThreads) k_fo_phi(FreezeArgs<R> a) {
   for (int r = 0; r <= MP; ++r) {
     if (r <= npt) {  // uniform
       __syncthreads();
-      s_red[tid] = acc[r];
+      s_red[tid] = r == 0 ? acc[0] : a.pref_dV * a.pt[r > 0 ? r - 1 : 0] * acc[r];
       __syncthreads();
       if (tid < a.n_phi) {
         double t = s_red[tid];
@@ -297,6 +294,7 @@ hipError_t launch_freezeout(const FreezeArgs<R>& a, double* spectra, double* har
     // lanes own azimuths: groups of n_phi lanes split the cells
     FreezeArgs<R> b = a;
     b.groups = kFoThreads / a.n_phi;
+    for (int r = 0; r < a.rows - 1; ++r) b.smax[r] = 1073741824.0 / a.pt[r];
     const int npt = a.rows - 1;
     static_assert(kFoMaxPt == 15, "row bounds 0, 2, 5, 10, 15");
     if (npt == 0) hipLaunchKernelGGL((k_fo_phi<R, 0>), dim3(kFoBlocks), dim3(kFoThreads), 0, st, b);

@@ -244,6 +244,7 @@ struct FreezeArgs {
   int n_out;             // rows * n_phi
   int groups;            // lane groups sharing one set of outputs (n_out <= kFoThreads / groups)
   double pt[kFoMaxPt];   // p_T of rows 1..
+  double smax[kFoMaxPt]; // 2^30 / p_T (set by the launcher)
   double T_min;          // cells with T < T_min are left out
   double pref_dV;        // g dV / (2 pi hbar c)^3
   double eos_dof, hbarc; // T(e) of the fluid
