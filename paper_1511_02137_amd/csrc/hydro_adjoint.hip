@@ -9,12 +9,14 @@
 //   -> adjoints of the split fluxes at each point
 //   -> (F+- = (f +- W)/2, f through the FP64 conserved->primitive recovery)
 //   -> adjoint of W at the point; ghost points pass theirs to the cell they copy.
-// A workgroup owns a whole line along the axis, so every face that touches a
-// cell of the line is handled in the same workgroup: each lane reverses its
-// face, writes the seven partials to LDS, and each lane gathers the partials
-// of its own point in a fixed order (deterministic, no atomics).
+// A workgroup owns whole lines along the axis, so every face that touches a
+// cell of a line is handled in the same workgroup: each lane reverses a run of
+// neighbouring faces, and the runs' contributions to a point are added in a
+// fixed order (deterministic, no atomics).
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "hydro_device.hpp"
 #include "hydro_internal.hpp"
@@ -81,31 +83,6 @@ __device__ __forceinline__ PrimJ c2p_jac(double E, double Mx, double My, double 
   return J;
 }
 
-// The same Jacobian for an admissible cell (no fix-up) whose e is known from
-// the recovery: sqrt(4E^2 - 3M^2) = E + e, one division.
-__device__ __forceinline__ PrimJ c2p_jac_known(double E, double Mx, double My, double Mz, double e) {
-  PrimJ J;
-  J.E = E;
-  J.vac = false;
-  J.cap = false;
-  J.capf = 1.0;
-  const double M[3] = {Mx, My, Mz};
-  const double s = E + e;
-  const double W = E + e * (1.0 / 3.0);
-  const double inv = rcp_nr(s * W);
-  const double is = W * inv;
-  J.e = e;
-  J.iW = s * inv;
-  for (int k = 0; k < 3; ++k) {
-    J.Mc[k] = M[k];
-    J.Mh[k] = 0.0;
-    J.v[k] = M[k] * J.iW;
-    J.eM[k] = -3.0 * M[k] * is;
-  }
-  J.eE = 4.0 * E * is - 1.0;
-  return J;
-}
-
 // Given adjoints eb of e and vb of v, the adjoints of (E, M):
 // with Q = (vb . v)/(E + p) and kappa = eb - Q/3:
 //   Eb = kappa de/dE - Q,  Mb_k = kappa de/dM_k + vb_k/(E + p),
@@ -160,154 +137,209 @@ __device__ __forceinline__ void split_flux_vjp(const R u[5], const PrimJ& J, con
   for (int k = 0; k < 3; ++k) ub[1 + k] += Mb[k];
 }
 
-// ---------------------------------------------------------------------------
-// Reverse mode of weno7: ab[m] = phi * dR/da_m for the reconstruction of
-// a0..a6 (same forward arithmetic: differences, candidates d_k (q_k - a3),
-// smoothness from differences, Z or JS weights, R = a3 + sum w r / sum w d),
-// then the chain back through weights, smoothness indicators, candidates and
-// differences.  Every multiply-add is an explicit fma.
-template <class R, int S>
-__device__ __forceinline__ void weno7_vjp(const R* a, R phi, R eps, R* ab) {
-  const R e0 = a[1] - a[0], e1 = a[2] - a[1], e2 = a[3] - a[2], e3 = a[4] - a[3], e4 = a[5] - a[4],
-          e5 = a[6] - a[5];
-  R eb[6], fb[5], gb[4];
-  R rb0, rb1, rb2, rb3;
-  if (S == kWenoLinear) {
-    rb0 = rb1 = rb2 = rb3 = phi;
+// The same for an admissible cell (no fix-up) whose e is known from the
+// recovery: sqrt(4E^2 - 3M^2) = E + e, one division, and only v_AX has an
+// adjoint, so few values stay live.
+template <class R, int AX>
+__device__ __forceinline__ void split_flux_vjp_known(const R u[5], double e, const double ap[5], const double am[5],
+                                                     double ub[5]) {
+  const double E = (double)u[0];
+  const double s = E + e, W = E + e * (1.0 / 3.0);
+  const double inv = rcp_nr(s * W);
+  const double is = W * inv, iW = s * inv;
+  const double v = (double)u[1 + AX] * iW, vd = (double)(R)v;
+  double vbd = 0.5 * (ap[4] + am[4]) * (double)u[4];
+  ub[4] = fma(0.5 * (ap[4] + am[4]), vd, 0.5 * (ap[4] - am[4]));
 #pragma unroll
-    for (int k = 0; k < 6; ++k) eb[k] = R(0);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) fb[k] = R(0);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) gb[k] = R(0);
-  } else {
-    const R r0 = fma(R(13.0 / 420.0), e2, fma(R(-10.0 / 420.0), e1, R(3.0 / 420.0) * e0));
-    const R r1 = fma(R(3.0 / 35.0), e3, fma(R(4.0 / 35.0), e2, R(-1.0 / 35.0) * e1));
-    const R r2 = fma(R(-3.0 / 70.0), e4, fma(R(18.0 / 70.0), e3, R(3.0 / 70.0) * e2));
-    const R r3 = fma(R(1.0 / 105.0), e5, fma(R(-4.0 / 105.0), e4, R(9.0 / 105.0) * e3));
-    const R f[5] = {e1 - e0, e2 - e1, e3 - e2, e4 - e3, e5 - e4};
-    const R g[4] = {f[1] - f[0], f[2] - f[1], f[3] - f[2], f[4] - f[3]};
-    const R e[4] = {e0, e1, e2, e3};
-    const R hk[4] = {R(2.5), R(1.5), R(0.5), R(-0.5)};
-    const R mk[4] = {R(11.0 / 6.0), R(1.0 / 3.0), R(-1.0 / 6.0), R(1.0 / 3.0)};
-    const R gk[4] = {R(2), R(1), R(0), R(-1)};
-    // X_k = 13/12 c_k and Y_k = 781/720 D3_k are kept: half the indicator's
-    // partials in c_k and D3_k
-    R b[4], sk[4], ck[4], X[4], Y[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      sk[k] = fma(mk[k], g[k], fma(hk[k], f[k], e[k]));
-      ck[k] = fma(gk[k], g[k], f[k]);
-      X[k] = R(13.0 / 12.0) * ck[k];
-      Y[k] = R(781.0 / 720.0) * g[k];
-      b[k] = fma(sk[k], sk[k], fma(X[k], ck[k], fma(Y[k], g[k], eps)));
-    }
-    R iv[4];
-    if (sizeof(R) == 8) {
-      const R p01 = b[0] * b[1], p23 = b[2] * b[3];
-      const R inv = (R)rcp_nr((double)(p01 * p23));
-      const R u23 = inv * p23, u01 = inv * p01;
-      iv[0] = u23 * b[1];
-      iv[1] = u23 * b[0];
-      iv[2] = u01 * b[3];
-      iv[3] = u01 * b[2];
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) iv[k] = rcp_approx<R>(b[k]);
-    }
-    R w[4], s[4];
-    R traw = R(0);
-    if (S == kWenoZ) {
-      traw = fma(R(3), b[1] - b[2], b[0] - b[3]);
-      const R tau = fabs(traw);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        s[k] = tau * iv[k];
-        w[k] = fma(s[k], s[k], R(1));
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) w[k] = iv[k] * iv[k];
-    }
-    const R dk[4] = {R(1.0 / 35.0), R(12.0 / 35.0), R(18.0 / 35.0), R(4.0 / 35.0)};
-    const R den = fma(w[3], dk[3], fma(w[2], dk[2], fma(w[1], dk[1], w[0] * dk[0])));
-    const R num = fma(w[3], r3, fma(w[2], r2, fma(w[1], r1, w[0] * r0)));
-    const R invd = sizeof(R) == 8 ? (R)rcp_nr((double)den) : rcp_approx<R>(den);
-    const R corr = num * invd;
-    const R pin = phi * invd;
-    rb0 = pin * w[0];
-    rb1 = pin * w[1];
-    rb2 = pin * w[2];
-    rb3 = pin * w[3];
-    const R rr[4] = {r0, r1, r2, r3};
-    // bb2[k] = 2 dR/db_k, formed directly (4 dR/dw_k below): the factor 2 of
-    // every partial of b_k = s_k^2 + X_k c_k + Y_k D3_k + eps then needs no
-    // multiply (powers of two scale exactly, so this is bit-identical to
-    // forming dR/db_k and doubling it)
-    const R pin4 = R(4) * pin;
-    R bb2[4];
-    R taub2 = R(0);  // 2 dR/dtau
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const R wb4 = pin4 * fma(-dk[k], corr, rr[k]);  // 4 dR/dw_k
-      if (S == kWenoZ) {
-        const R t2 = wb4 * (s[k] * iv[k]);  // 2 dR/dtau through w_k
-        bb2[k] = -t2 * s[k];
-        taub2 = taub2 + t2;
-      } else {
-        bb2[k] = -wb4 * (w[k] * iv[k]);
-      }
-    }
-    if (S == kWenoZ) {
-      const R t = traw < R(0) ? -taub2 : taub2;  // tau = |traw|
-      bb2[0] = bb2[0] + t;
-      bb2[1] = fma(R(3), t, bb2[1]);
-      bb2[2] = fma(R(-3), t, bb2[2]);
-      bb2[3] = bb2[3] - t;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const R sb = sk[k] * bb2[k];  // s_k partial
-      const R cb = X[k] * bb2[k];   // c_k partial
-      const R gd = Y[k] * bb2[k];   // D3_k partial (direct term)
-      eb[k] = sb;
-      fb[k] = fma(hk[k], sb, cb);
-      gb[k] = (k == 2) ? fma(mk[k], sb, gd) : fma(mk[k], sb, fma(gk[k], cb, gd));  // g_2 = 0
-    }
-    eb[4] = R(0);
-    eb[5] = R(0);
-    fb[4] = R(0);
+  for (int j = 1; j < 4; ++j) {
+    const double fb = 0.5 * (ap[j] + am[j]);
+    vbd = fma(fb, (double)u[j], vbd);
+    ub[j] = fma(fb, vd, 0.5 * (ap[j] - am[j]));
   }
-  // candidates r_k(e)
-  eb[0] = fma(R(3.0 / 420.0), rb0, eb[0]);
-  eb[1] = fma(R(-1.0 / 35.0), rb1, fma(R(-10.0 / 420.0), rb0, eb[1]));
-  eb[2] = fma(R(3.0 / 70.0), rb2, fma(R(4.0 / 35.0), rb1, fma(R(13.0 / 420.0), rb0, eb[2])));
-  eb[3] = fma(R(9.0 / 105.0), rb3, fma(R(18.0 / 70.0), rb2, fma(R(3.0 / 35.0), rb1, eb[3])));
-  eb[4] = fma(R(-4.0 / 105.0), rb3, fma(R(-3.0 / 70.0), rb2, eb[4]));
-  eb[5] = fma(R(1.0 / 105.0), rb3, eb[5]);
-  // second differences g_j = f_{j+1} - f_j, first f_j = e_{j+1} - e_j, e_j = a_{j+1} - a_j
+  const double Q = vbd * v * iW;
+  const double kap = (0.5 * (ap[1 + AX] + am[1 + AX]) - Q) * (1.0 / 3.0);
+  ub[0] = 0.5 * (ap[0] - am[0]) + (kap * (4.0 * E * is - 1.0) - Q);
+  ub[1 + AX] = ub[1 + AX] + fma(vbd, iW, 0.5 * (ap[0] + am[0]));
+  const double km = -3.0 * kap * is;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    fb[j + 1] = fb[j + 1] + gb[j];
-    fb[j] = fb[j] - gb[j];
-  }
-#pragma unroll
-  for (int j = 0; j < 5; ++j) {
-    eb[j + 1] = eb[j + 1] + fb[j];
-    eb[j] = eb[j] - fb[j];
-  }
-  ab[0] = -eb[0];
-#pragma unroll
-  for (int j = 1; j < 6; ++j) ab[j] = eb[j - 1] - eb[j];
-  ab[6] = eb[5];
-  ab[3] = ab[3] + phi;
+  for (int j = 1; j < 4; ++j) ub[j] = fma(km, (double)u[j], ub[j]);
 }
 
 // ---------------------------------------------------------------------------
-// Line adjoint along axis AX: one workgroup per line (blockDim >= n, <= 1024).
-// G (first: =, else +=) receives (dD_AX/dW)^T mu for the faces -1/2..n-3/2
-// of the line (periodic: face -1/2 is also the right face of cell n-1); the
-// outflow face n-1/2 is added by k_bound_adj.
+// Reverse mode of weno7_face: adds phi dR/d(e, f, g) of one face to the
+// adjoints ea2, ea3 of the first, fa1..fa3 of the (scaled) second and ga of
+// the third differences (the a_i term, phi itself, is the caller's).  Forward
+// arithmetic as there, weights by reciprocals: w_k = 1 + z_k^2, z_k = tau/b_k
+// (Jiang-Shu: 1/b_k^2), R = a_i + num / (12 sqrt(13/12) den), num = sum d_k w_k
+// r_k, den = sum d_k w_k.  ea3, fa3 and ga[3] are first touched by this face.
+template <class R, int S>
+__device__ __forceinline__ void weno7_face_vjp(R phi, R e2, R e3, R f1, R f2, R f3, const R* g, const R* G, R& ea2,
+                                               R& ea3, R& fa1, R& fa2, R& fa3, R* ga) {
+  const R sm = fma(R(0.5 / kCurv), f2, e2);
+  const R s0 = fma(R(1.0 / (3.0 * kCurv)), g[0], fma(R(0.5 / kCurv), f1, e2));
+  const R s1 = fma(R(-1.0 / (6.0 * kCurv)), g[1], sm);
+  const R s2 = fma(R(-1.0 / (6.0 * kCurv)), g[2], sm);
+  const R s3 = fma(R(1.0 / (3.0 * kCurv)), g[3], fma(R(-0.5 / kCurv), f3, e3));
+  const R c0 = f1 + g[0], c3 = f3 - g[3];
+  R rb0, rb1, rb2, rb3;                             // adjoints of the candidates r_k
+  R bb0 = R(0), bb1 = R(0), bb2 = R(0), bb3 = R(0);  // twice those of the indicators
+  if (S == kWenoLinear) {
+    const R pin = R(1.0 / (35.0 * 12.0 * kCurv)) * phi;
+    rb0 = pin;
+    rb1 = R(12) * pin;
+    rb2 = R(18) * pin;
+    rb3 = R(4) * pin;
+  } else {
+    const R r0 = fma(R(6.0 * kCurv), s0, c0), r1 = fma(R(6.0 * kCurv), s1, f2), r2 = fma(R(6.0 * kCurv), s2, f2),
+            r3 = fma(R(6.0 * kCurv), s3, c3);
+    const R b0 = fma(s0, s0, fma(c0, c0, G[0]));
+    const R b1 = fma(s1, s1, fma(f2, f2, G[1]));
+    const R b2 = fma(s2, s2, fma(f2, f2, G[2]));
+    const R b3 = fma(s3, s3, fma(c3, c3, G[3]));
+    R i0, i1, i2, i3;
+    if (sizeof(R) == 8) {
+      const R p01 = b0 * b1, p23 = b2 * b3;
+      const R inv = (R)rcp_nr((double)(p01 * p23));
+      const R u23 = inv * p23, u01 = inv * p01;
+      i0 = u23 * b1;
+      i1 = u23 * b0;
+      i2 = u01 * b3;
+      i3 = u01 * b2;
+    } else {
+      i0 = rcp_approx<R>(b0);
+      i1 = rcp_approx<R>(b1);
+      i2 = rcp_approx<R>(b2);
+      i3 = rcp_approx<R>(b3);
+    }
+    const R tau = fma(R(3), b1 - b2, b0 - b3);
+    const R z0 = tau * i0, z1 = tau * i1, z2 = tau * i2, z3 = tau * i3;
+    const R w0 = S == kWenoZ ? fma(z0, z0, R(1)) : i0 * i0;
+    const R w1 = R(12) * (S == kWenoZ ? fma(z1, z1, R(1)) : i1 * i1);
+    const R w2 = R(18) * (S == kWenoZ ? fma(z2, z2, R(1)) : i2 * i2);
+    const R w3 = R(4) * (S == kWenoZ ? fma(z3, z3, R(1)) : i3 * i3);
+    const R den = (w0 + w1) + (w2 + w3);
+    const R num = fma(w3, r3, fma(w2, r2, fma(w1, r1, w0 * r0)));
+    const R invd = sizeof(R) == 8 ? (R)rcp_nr((double)den) : rcp_approx<R>(den);
+    const R corr = num * invd;
+    const R pin = R(1.0 / (12.0 * kCurv)) * (phi * invd);
+    rb0 = pin * w0;
+    rb1 = pin * w1;
+    rb2 = pin * w2;
+    rb3 = pin * w3;
+    // 4 times the adjoints of w_k (without their d_k in w1..w3 above)
+    const R v0 = (R(4) * pin) * (r0 - corr), v1 = (R(48) * pin) * (r1 - corr), v2 = (R(72) * pin) * (r2 - corr),
+            v3 = (R(16) * pin) * (r3 - corr);
+    if (S == kWenoZ) {
+      const R t0 = v0 * (z0 * i0), t1 = v1 * (z1 * i1), t2 = v2 * (z2 * i2), t3 = v3 * (z3 * i3);
+      const R t = (t0 + t1) + (t2 + t3);  // twice the adjoint of tau
+      bb0 = fma(-t0, z0, t);
+      bb1 = fma(-t1, z1, R(3) * t);
+      bb2 = fma(-t2, z2, R(-3) * t);
+      bb3 = fma(-t3, z3, -t);
+    } else {
+      bb0 = -v0 * ((i0 * i0) * i0);
+      bb1 = -v1 * ((i1 * i1) * i1);
+      bb2 = -v2 * ((i2 * i2) * i2);
+      bb3 = -v3 * ((i3 * i3) * i3);
+    }
+  }
+  const R sb0 = fma(s0, bb0, R(6.0 * kCurv) * rb0), sb1 = fma(s1, bb1, R(6.0 * kCurv) * rb1),
+          sb2 = fma(s2, bb2, R(6.0 * kCurv) * rb2), sb3 = fma(s3, bb3, R(6.0 * kCurv) * rb3);
+  const R cb0 = fma(c0, bb0, rb0), cb3 = fma(c3, bb3, rb3);
+  const R cbm = fma(f2, bb1 + bb2, rb1 + rb2), sbm = sb1 + sb2;
+  constexpr double kG = 781.0 / 780.0;
+  ga[0] = fma(R(1.0 / (3.0 * kCurv)), sb0, fma(R(kG) * g[0], bb0, ga[0] + cb0));
+  ga[1] = fma(R(-1.0 / (6.0 * kCurv)), sb1, fma(R(kG) * g[1], bb1, ga[1]));
+  ga[2] = fma(R(-1.0 / (6.0 * kCurv)), sb2, fma(R(kG) * g[2], bb2, ga[2]));
+  ga[3] = fma(R(1.0 / (3.0 * kCurv)), sb3, fma(R(kG) * g[3], bb3, -cb3));
+  fa1 = fma(R(0.5 / kCurv), sb0, fa1 + cb0);
+  fa2 = fma(R(0.5 / kCurv), sbm, fa2 + cbm);
+  fa3 = fma(R(-0.5 / kCurv), sb3, cb3);
+  ea2 = ea2 + (sb0 + sbm);
+  ea3 = sb3;
+}
+
+// L neighbouring faces of one line in reverse: get(m), m = 0..L+5 in order
+// (value k + 6 before face k), phi(k) the adjoint of face k, put(j, adjoint of
+// value j by these faces), j = 0..L+5 in order.  A difference's adjoint is
+// complete once the last face that uses it is done, and passes on to the two
+// differences (values) it was formed from: seven operations a point in the
+// place of a face's seven partials.
+template <class R, int S, int L, class Get, class Phi, class Put>
+__device__ __forceinline__ void weno_line_vjp(Get get, Phi phi, R eps, Put put) {
+  R a[L + 6], e[L + 5], f[L + 4], g[L + 3], G[L + 3];
+  R aa[L + 6], ea[L + 5], fa[L + 4], ga[L + 3];
+#pragma unroll
+  for (int m = 0; m < L + 6; ++m) aa[m] = R(0);
+#pragma unroll
+  for (int m = 0; m < L + 5; ++m) ea[m] = R(0);
+#pragma unroll
+  for (int m = 0; m < L + 4; ++m) fa[m] = R(0);
+#pragma unroll
+  for (int m = 0; m < L + 3; ++m) ga[m] = R(0);
+  auto pass = [&](int j) {  // values and differences j are complete
+    if (j < L + 3) {
+      fa[j + 1] = fa[j + 1] + ga[j];
+      fa[j] = fa[j] - ga[j];
+    }
+    if (j < L + 4) {
+      const R p = R(kCurv) * fa[j];
+      ea[j + 1] = ea[j + 1] + p;
+      ea[j] = ea[j] - p;
+    }
+    if (j < L + 5) {
+      aa[j + 1] = aa[j + 1] + ea[j];
+      aa[j] = aa[j] - ea[j];
+    }
+    put(j, aa[j]);
+  };
+#pragma unroll
+  for (int k = 0; k < L; ++k) {
+#pragma unroll
+    for (int m = (k == 0 ? 0 : k + 6); m <= k + 6; ++m) {
+      a[m] = get(m);
+      if (m >= 1) e[m - 1] = a[m] - a[m - 1];
+      if (m >= 2) f[m - 2] = R(kCurv) * (e[m - 1] - e[m - 2]);
+      if (m >= 3) {
+        g[m - 3] = f[m - 2] - f[m - 3];
+        G[m - 3] = fma(R(781.0 / 780.0) * g[m - 3], g[m - 3], eps);
+      }
+    }
+    const R ph = phi(k);
+    weno7_face_vjp<R, S>(ph, e[k + 2], e[k + 3], f[k + 1], f[k + 2], f[k + 3], g + k, G + k, ea[k + 2], ea[k + 3],
+                         fa[k + 1], fa[k + 2], fa[k + 3], ga + k);
+    aa[k + 3] = aa[k + 3] + ph;
+    pass(k);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = L; j < L + 6; ++j) pass(j);
+}
+
+// ---------------------------------------------------------------------------
+// Line adjoint along axis AX: G (first: =, else +=) receives (dD_AX/dW)^T mu
+// of whole lines (faces -1/2..n-3/2; periodic: face -1/2 is also the right face
+// of cell n-1; outflow: also face n-1/2).  A workgroup owns NL neighbouring
+// lines, so that the loads of y and z lines fetch runs of consecutive x.
+//   (1) The cells' split fluxes go to LDS (area 2 field + split, [slot][line];
+//       F- in reverse slot order), and so do the faces' adjoints phi.
+//   (2) Each wave takes whole areas: it copies the ghost slots and marches; its
+//       lanes are the lines by 64 / NL runs of L faces, turn after turn along
+//       the line.  The adjoint of a run's value takes the value's place, L - 7
+//       faces late (the run before it reads value L + j at face L + j - 7), and
+//       the six values beyond the run are added to those of the run that starts
+//       there, for a turn's last run in the next turn.  The ghosts' adjoints
+//       are added to their cells'.  Lanes execute their LDS operations in
+//       order, and no other wave uses the area.
+//   (3) Each cell reverses the splits through its recovery (recomputed) and
+//       finishes G or, on the last axis, the reverse RK combine.
+//
+// Bound by VALU issue (FP64) and by its serial chains at five waves a SIMD
+// (FP32).  One lane per face, its seven partials of a split gathered through
+// LDS (two barriers a field, one or two lines a workgroup, face n-1/2 in a
+// launch of its own), took 194 operations a reconstruction, this 150.  us an
+// axis (x, y, z) before and after, those launches included: 60x52x66 FP64 41,
+// 39, 53 / 27, 23, 29; 128^3 FP32 119, 113, 117 / 121, 102, 99.
 __device__ __forceinline__ long long line_base(int AX, long long L, const Grid& g, long long& stride) {
   const int nx = g.n[0], ny = g.n[1];
   if (AX == 0) {
@@ -324,299 +356,250 @@ __device__ __forceinline__ long long line_base(int AX, long long L, const Grid& 
   return y * nx + x;
 }
 
-__device__ __forceinline__ long long n_lines(int AX, const Grid& g) {
-  return AX == 0 ? (long long)g.n[1] * g.n[2] : (AX == 1 ? (long long)g.n[0] * g.n[2] : (long long)g.n[0] * g.n[1]);
-}
-
-// Block order: consecutive lines (neighbours in memory for the y/z axes) go
-// to the same XCD (blocks are dealt round-robin over the 8 XCDs).
-__device__ __forceinline__ long long xcd_line(long long nlines) {
-  const long long per = (nlines + 7) / 8;
+// Block order: consecutive groups of lines (neighbours in memory for the y/z
+// axes) go to the same XCD (blocks are dealt round-robin over the 8 XCDs).
+__device__ __forceinline__ long long xcd_group(long long groups) {
+  const long long per = (groups + 7) / 8;
   return (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
 }
 
-template <class R, int S, int AX, int TBMAX, int NL>
-__global__ void __launch_bounds__(TBMAX) k_line_adj(AdjArgs<R> a) {
+template <class R, int S, int AX, int L, int NL>
+__global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8 ? 4 : 5) k_line_adj(AdjArgs<R> a) {
+  constexpr int kBlock = line_adj_block((int)sizeof(R));
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const long long nlines = n_lines(AX, a.g);
-  // NL neighbouring lines (consecutive x) per workgroup, lanes interleaved
-  // line-fastest, so that the strided loads and stores of y and z lines
-  // fetch NL neighbouring values per cache line; each line has its own LDS
-  // area (pitch chosen so that the lines' copies fall in different banks)
-  const long long ngroups = nlines / NL;
-  const long long grp = xcd_line(ngroups);
-  if (grp >= ngroups) return;  // whole workgroup
-  const int xi = threadIdx.x % NL;
-  const long long L = grp * NL + xi;
+  R* s = reinterpret_cast<R*>(smem_raw);
+  constexpr int nl = NL, rpt = 64 / NL;  // lines, runs of a wave's turn
+  constexpr int pitch = line_adj_pitch(AX, NL);
   const int n = a.g.n[AX];
   const int bc = a.g.bc[AX];
-  const int P = n + 8;
-  const int Q = n + 16;
   const long long nc = a.g.nc;
-  long long stride;
-  const long long base = line_base(AX, L, a.g, stride);
-  R* s = reinterpret_cast<R*>(smem_raw) + (long long)xi * line_adj_pitch(n, NL);
-  R* sFp = s;               // [5][P]
-  R* sFm = s + 5 * P;       // [5][P]
-  R* sX = s + 10 * P;       // [2][7][Q]; first used to stage mu [5][n]
-  const int tid = threadIdx.x / NL;  // point / face of the lane in its line
-  const int TB = blockDim.x / NL;    // lanes per line
+  const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
+                                   : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
+  const long long grp = xcd_group((nlines + nl - 1) / nl);
+  const long long line0 = grp * nl;
+  if (line0 >= nlines) return;  // whole workgroup
+  const int nf = n + (bc ? 0 : 1);
+  const int area = line_adj_slots(nf, L) * pitch;
+  const int fields = a.skip_n ? 4 : 5;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = threadIdx.x & 63;
   unsigned fix = 0;
 
-  // Points: lane tid < n recomputes the split fluxes of its own cell (slot
-  // tid + 4).  A ghost point (slots 0..3, n+4..n+7) is a copy of the cell it
-  // maps to, so its split fluxes are copied in LDS, and in the reverse its
-  // split-flux adjoints are added to that cell's before the one split-flux
-  // VJP (the same Jacobian, so this equals reversing the ghost on its own).
-  R uo[5];
-  double eo = 0.0;     // recovered e of the own cell
-  bool fixed = false;  // the recovery fixed the own cell up
-  if (tid < n) {
-    load5(a.W, nc, base + (long long)tid * stride, uo);
-    const unsigned f0 = fix;
-    const PrimV pv = c2p(uo, fix);
-    eo = pv.e;
-    fixed = fix != f0;
-    R Fp[5], Fm[5];
-    split_flux<R, AX>(uo, pv, Fp, Fm);
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      sFp[c * P + tid + 4] = Fp[c];
-      sFm[c * P + tid + 4] = Fm[c];
-    }
-  }
-  R my[5];  // mu of the lane's own cell (used by the fused combine)
-  if (tid < n) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      my[c] = (c == 4 && a.skip_n) ? R(0) : a.mu[c * nc + base + (long long)tid * stride];
-      sX[c * n + tid] = my[c];
-    }
-  }
-  __syncthreads();
-  // ghost slot of lane tid < 8: slot jg, copy of cell map_idx(jg - 4)
-  const int jg = tid < 4 ? tid : n + tid;
-  if (tid < 8) {
-    const int src = map_idx(jg - 4, n, bc) + 4;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      sFp[c * P + jg] = sFp[c * P + src];
-      sFm[c * P + jg] = sFm[c * P + src];
-    }
-  }
-  // face adjoints phi(x - 1/2) = (mu(x) - mu(x-1)) / dx
-  R phi[5];
-  if (tid < n) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R left = tid > 0 ? sX[c * n + tid - 1] : (bc ? sX[c * n + n - 1] : R(0));
-      phi[c] = (sX[c * n + tid] - left) * a.inv_d;
-    }
-  }
-  __syncthreads();
-  for (int z = tid; z < 14 * 16; z += TB) {  // pads: 8 below and 8 above each row
-    const int row = z >> 4, k = z & 15;
-    sX[row * Q + (k < 8 ? k : n + k)] = R(0);
-  }
-
-  // slot j is argument m of face j - m (F+) and of face j - 7 + m (F-)
-  auto gather = [&](int j, R& sp, R& sm) {
-    sp = R(0);
-    sm = R(0);
-#pragma unroll
-    for (int m = 0; m < 7; ++m) {
-      sp = sp + sX[m * Q + j - m + 8];
-      sm = sm + sX[(7 + m) * Q + j - 7 + m + 8];
-    }
-  };
-  R acc[2][5];  // [split][field] of the own cell
-#pragma unroll
-  for (int c = 0; c < 5; ++c) {
-    if (c == 4 && a.skip_n) {  // uniform over the workgroup
-      acc[0][c] = acc[1][c] = R(0);
-      continue;
-    }
-    if (tid < n) {
-      R args[7], ab[7];
-#pragma unroll
-      for (int m = 0; m < 7; ++m) args[m] = sFp[c * P + tid + m];
-      weno7_vjp<R, S>(args, phi[c], a.eps, ab);
-#pragma unroll
-      for (int m = 0; m < 7; ++m) sX[m * Q + tid + 8] = ab[m];
-#pragma unroll
-      for (int m = 0; m < 7; ++m) args[m] = sFm[c * P + tid + 7 - m];
-      weno7_vjp<R, S>(args, phi[c], a.eps, ab);
-#pragma unroll
-      for (int m = 0; m < 7; ++m) sX[(7 + m) * Q + tid + 8] = ab[m];
-    }
-    __syncthreads();
-    if (tid < n) gather(tid + 4, acc[0][c], acc[1][c]);
-    if (tid < 8) {
-      // the ghost's sums go to slots 0..7 of field c's rows, which no lane
-      // reads again (field c's reconstructions are done)
-      R gp, gm;
-      gather(jg, gp, gm);
-      sFp[c * P + tid] = gp;
-      sFm[c * P + tid] = gm;
-    }
-    __syncthreads();
-  }
-
-  if (tid < n) {
-    // ghosts in slot order onto the cells they copy
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const int j = g < 4 ? g : n + g;
-      if (map_idx(j - 4, n, bc) == tid) {
-#pragma unroll
-        for (int c = 0; c < 5; ++c) {
-          if (c == 4 && a.skip_n) continue;  // slots still hold field 4's split fluxes
-          acc[0][c] = acc[0][c] + sFp[c * P + g];
-          acc[1][c] = acc[1][c] + sFm[c * P + g];
-        }
-      }
-    }
-    // split-flux adjoint -> adjoint of W at the cell
-    const double E = (double)uo[0], Mx = (double)uo[1], My = (double)uo[2], Mz = (double)uo[3];
-    const PrimJ J = fixed ? c2p_jac(E, Mx, My, Mz) : c2p_jac_known(E, Mx, My, Mz, eo);
-    double ap[5], am[5], ub[5];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      ap[c] = (double)acc[0][c];
-      am[c] = (double)acc[1][c];
-    }
-    split_flux_vjp<R, AX>(uo, J, ap, am, ub);
-    const long long cell = base + (long long)tid * stride;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const long long q = c * nc + cell;
-      const R gv = a.first ? (R)ub[c] : a.G[q] + (R)ub[c];
-      if (a.stage == 0) {
-        a.G[q] = gv;
-      } else {
-        const R t = fma(a.dt, gv, my[c]);
-        if (a.stage == 3) {
-          a.lW[q] = R(2.0 / 3.0) * t;
-          a.acc[q] = R(1.0 / 3.0) * my[c];
-        } else if (a.stage == 2) {
-          a.lW[q] = R(0.25) * t;
-          a.acc[q] = fma(R(0.75), my[c], a.acc[q]);
-        } else {
-          a.lW[q] = a.acc[q] + t;
-        }
-      }
-    }
-  }
-  add_fixups(a.fixups, fix);
-}
-
-// Outflow face n-1/2 of every line along AX: phi = -mu(n-1)/dx.  Its
-// stencil points n-4..n+3 are the cells clamp(n-4+m) (the ghosts copy cell
-// n-1), so they fall into runs of equal cells; the first point of a run
-// stands for it.  A workgroup takes 32 lines: (1) one lane per run recovers
-// its cell and forms the split fluxes; (2) one lane per (line, field, split)
-// reverses that reconstruction; (3) the lane of each run adds the run's
-// reconstruction adjoints in point order, reverses the split through the
-// cell's Jacobian and adds the result to G (distinct cells, so no two lanes
-// touch the same element).
-constexpr int kBoundLines = 32;
-
-__device__ __forceinline__ int bound_cell(int n, int m) { return min(max(n - 4 + m, 0), n - 1); }
-// first point of m's run of equal cells
-__device__ __forceinline__ int bound_rep(int n, int m) {
-  const int k = bound_cell(n, m);
-  return k == 0 ? 0 : k - (n - 4);
-}
-
-template <class R, int S, int AX>
-__global__ void __launch_bounds__(kBoundLines * 10) k_bound_adj(AdjArgs<R> a) {
-  __shared__ R sF[kBoundLines][4][10];        // split fluxes of the runs' cells (F+ 0..4, F- 5..9)
-  __shared__ double sA[kBoundLines][8][10];   // reconstruction adjoints per point
-  const long long nlines = n_lines(AX, a.g);
-  const int n = a.g.n[AX];
-  const long long nc = a.g.nc;
-  const int tid = threadIdx.x;
-  unsigned fix = 0;
-  // (1) lane = (line, point m < 4); point m starts a run when its cell
-  // differs from point m-1's (points 4..7 are in point 3's run)
-  const int l1 = tid >> 2, m1 = tid & 3;
-  const long long L1 = (long long)blockIdx.x * kBoundLines + l1;
-  const bool act1 = tid < kBoundLines * 4 && L1 < nlines && (m1 == 0 || bound_cell(n, m1) != bound_cell(n, m1 - 1));
-  // the face adjoint of lane (line, field, split) of step (2) and the G of
-  // the run's cell, loaded first so that their latency overlaps step (1)
-  const int l2 = tid / 10, r2 = tid % 10, c2 = r2 >> 1, sp2 = r2 & 1;
-  const long long L2 = (long long)blockIdx.x * kBoundLines + l2;
-  R phi = R(0);
-  if (L2 < nlines && !(c2 == 4 && a.skip_n)) {
+  // Lane and step of the point phases: y and z: lines fastest; x: a wave per
+  // row, cells fastest.
+  const int l0 = AX == 0 ? w : (int)threadIdx.x & (nl - 1), lstep = AX == 0 ? kBlock / 64 : nl;
+  const int p0 = AX == 0 ? q : (int)threadIdx.x / nl, pstep = AX == 0 ? 64 : kBlock / nl;
+  R* const hold = s + 2 * fields * area;            // [area][6][line], the last run of a turn's values beyond it
+  R* const phi = hold + 2 * fields * 6 * nl;        // [field][face + pad][pitch], zeros beyond the faces
+  const int pad = (nf + L - 1) / L * L - nf, prows = line_adj_phi_rows(nf, L);
+  const int parea = prows * pitch;
+  // slot j holds padded position j - 4; F- slot j at nf + 6 - j (slot nf + 7
+  // belongs to no face)
+#pragma unroll 1
+  for (int l = l0; l < nl && line0 + l < nlines; l += lstep) {
     long long stride;
-    const long long base = line_base(AX, L2, a.g, stride);
-    phi = -a.mu[c2 * nc + base + (long long)(n - 1) * stride] * a.inv_d;
-  }
-  R u[5], gpre[5];
-  double eo = 0.0;
-  bool fixed = false;
-  long long cell1 = 0;
-  if (act1) {
-    long long stride;
-    cell1 = line_base(AX, L1, a.g, stride) + (long long)bound_cell(n, m1) * stride;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) gpre[c] = a.G[c * nc + cell1];
-    load5(a.W, nc, cell1, u);
-    const unsigned f0 = fix;
-    const PrimV pv = c2p(u, fix);
-    eo = pv.e;
-    fixed = fix != f0;
-    R Fp[5], Fm[5];
-    split_flux<R, AX>(u, pv, Fp, Fm);
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      sF[l1][m1][c] = Fp[c];
-      sF[l1][m1][5 + c] = Fm[c];
-    }
-  }
-  __syncthreads();
-  // (2) reconstruction adjoints, lane = (line, field, split)
-  {
-    const int l = l2, c = c2, sp = sp2;
-    if (L2 < nlines) {
-      R args[7], ab[7];
-      if (sp == 0) {
-#pragma unroll
-        for (int m = 0; m < 7; ++m) args[m] = sF[l][bound_rep(n, m)][c];
-        weno7_vjp<R, S>(args, phi, a.eps, ab);
-#pragma unroll
-        for (int m = 0; m < 7; ++m) sA[l][m][c] = (double)ab[m];
-        sA[l][7][c] = 0.0;
-      } else {
-#pragma unroll
-        for (int m = 0; m < 7; ++m) args[m] = sF[l][bound_rep(n, 7 - m)][5 + c];
-        weno7_vjp<R, S>(args, phi, a.eps, ab);
-#pragma unroll
-        for (int m = 0; m < 7; ++m) sA[l][7 - m][5 + c] = (double)ab[m];
-        sA[l][0][5 + c] = 0.0;
-      }
-    }
-  }
-  __syncthreads();
-  // (3) the run's adjoints in point order, the split-flux adjoint, G
-  if (act1) {
-    double ap[5], am[5], ub[5];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) ap[c] = am[c] = 0.0;
-    const int k = bound_cell(n, m1);
-    for (int m = m1; m < 8 && bound_cell(n, m) == k; ++m) {
+    const long long base = line_base(AX, line0 + l, a.g, stride);
+#pragma unroll 1
+    for (int x = p0; x < n; x += pstep) {
+      long long cell = base + x * stride;
+      __asm__ __volatile__("" : "+v"(cell));  // as in (3)
+      R u[5], Fp[5], Fm[5];
+      load5(a.W, nc, cell, u);
+      const PrimV pv = c2p(u, fix);
+      split_flux<R, AX>(u, pv, Fp, Fm);
+      R* sp = s + (x + 4) * pitch + l;
+      R* sm = s + area + (nf + 2 - x) * pitch + l;
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
-        ap[c] = ap[c] + sA[l1][m][c];
-        am[c] = am[c] + sA[l1][m][5 + c];
+        if (c < fields) {
+          sp[2 * c * area] = Fp[c];
+          sm[2 * c * area] = Fm[c];
+        }
       }
     }
-    const double E = (double)u[0], Mx = (double)u[1], My = (double)u[2], Mz = (double)u[3];
-    const PrimJ J = fixed ? c2p_jac(E, Mx, My, Mz) : c2p_jac_known(E, Mx, My, Mz, eo);
-    split_flux_vjp<R, AX>(u, J, ap, am, ub);
+    // the last run's values past the line: any finite ones (phi is 0 there)
+    for (int j = nf + 7 + p0; j < line_adj_slots(nf, L); j += pstep)
+      for (int ar = 0; ar < 2 * fields; ++ar) s[ar * area + j * pitch + l] = R(0);
+    // face f = 0.. is f - 1/2: phi = (mu(f) - mu(f - 1)) / dx, outflow: nothing
+    // beyond the ends
+#pragma unroll 1
+    for (int k = p0; k < prows; k += pstep) {
+      const int f = k - pad;
+      const bool face = f >= 0 && f < nf;
+      const int fl = f == 0 ? (bc ? n - 1 : -1) : f - 1;
 #pragma unroll
-    for (int c = 0; c < 5; ++c) a.G[c * nc + cell1] = gpre[c] + (R)ub[c];
+      for (int c = 0; c < 5; ++c) {
+        if (c < fields) {
+          const R* mu = a.mu + c * nc + base;
+          const R left = face && fl >= 0 ? mu[fl * stride] : R(0);
+          const R right = face && f < n ? mu[f * stride] : R(0);
+          phi[c * parea + k * pitch + l] = (right - left) * a.inv_d;
+        }
+      }
+    }
   }
+  __syncthreads();
+
+  {
+    const int runs = (nf + L - 1) / L;
+    for (int ar = w; ar < 2 * fields; ar += kBlock / 64) {
+      // the empty asm keeps the lane's addresses from being formed ahead of
+      // the loops and held in registers through the march
+      int qa = q;
+      __asm__ __volatile__("" : "+v"(qa));
+      const int l = qa & (nl - 1);
+      const bool in = line0 + l < nlines;
+      R* const hd = hold + ar * 6 * nl + l;
+      R* const line = s + ar * area + l;
+      auto at = [&](int slot) { return ((ar & 1) ? nf + 6 - slot : slot) * pitch; };
+      // ghost slots: copies of their cells
+      const int h = qa / nl;
+      const int gj = h < 4 ? h : n + h;
+      if (h < 8 && gj <= nf + 6) line[at(gj)] = line[at(map_idx(gj - 4, n, bc) + 4)];
+      __asm__ __volatile__("" ::: "memory");
+      for (int r0 = 0; r0 < runs; r0 += rpt) {
+        int qr = qa;
+        __asm__ __volatile__("" : "+v"(qr));
+        const int r = r0 + qr / nl;
+        const bool act = in && r < runs;
+        R* const t = s + ar * area + r * L * pitch + l;
+        R beyond[6];
+        if (act) {
+          // faces r L.. of the area's order: F- runs from face nf - 1 down
+          const int f0 = (ar & 1) ? nf - 1 - r * L : r * L;
+          const R* ph = phi + (ar >> 1) * parea + (f0 + pad) * pitch + l;
+          const int pstep1 = (ar & 1) ? -pitch : pitch;
+          R next = t[0];
+          R late[L + 6];
+          weno_line_vjp<R, S, L>(
+              [&](int m) {
+                const R v = next;
+                if (m + 1 < L + 6) next = t[(m + 1) * pitch];
+                __asm__ __volatile__("" ::: "memory");
+                return v;
+              },
+              [&](int k) {
+                return ph[k * pstep1];
+              },
+              a.eps,
+              [&](int j, R v) {
+                constexpr int kLate = L > 7 ? L - 7 : 0;
+                late[j] = v;
+                if (j >= L) beyond[j - L] = v;
+                if (j >= kLate && j - kLate < L) t[(j - kLate) * pitch] = late[j - kLate];
+                __asm__ __volatile__("" ::: "memory");
+              });
+        }
+        __builtin_amdgcn_wave_barrier();
+        __asm__ __volatile__("" ::: "memory");
+        if (act) {
+          const bool group0 = r0 > 0 && r == r0, end = r == runs - 1, last = r == r0 + rpt - 1 && !end;
+#pragma unroll
+          for (int m = 0; m < 6; ++m) {
+            if (group0) t[m * pitch] = t[m * pitch] + hd[m * nl];
+          }
+          __asm__ __volatile__("" ::: "memory");
+#pragma unroll
+          for (int m = 0; m < 6; ++m) {
+            R* d = t + (L + m) * pitch;
+            if (last) hd[m * nl] = beyond[m];
+            else *d = end ? beyond[m] : *d + beyond[m];  // past the last run no run starts
+          }
+        }
+        __builtin_amdgcn_wave_barrier();
+        __asm__ __volatile__("" ::: "memory");
+      }
+      // ghosts' adjoints onto the cells they copy, in slot order (slot nf + 6
+      // in the area's order belongs to no face); several onto one cell unless
+      // the axis is periodic with at least 8 cells
+      int qg = q;
+      __asm__ __volatile__("" : "+v"(qg));
+      R* const gl = s + ar * area + (qg & (nl - 1));
+      const int gh = qg / nl, gs = gh < 4 ? gh : n + gh;
+      if (gh == 0) gl[(nf + 6) * pitch] = R(0);
+      __asm__ __volatile__("" ::: "memory");
+      if (bc && n >= 8) {
+        if (gh < 8 && gs <= nf + 6) {
+          R* d = gl + at(map_idx(gs - 4, n, bc) + 4);
+          *d = *d + gl[at(gs)];
+        }
+      } else if (!bc && n >= 2) {
+        if (gh < 2) {
+          R* d = gl + at(gh == 0 ? 4 : n + 3);
+          const int j0 = gh == 0 ? 0 : n + 4;
+          *d = (((*d + gl[at(j0)]) + gl[at(j0 + 1)]) + gl[at(j0 + 2)]) + gl[at(j0 + 3)];
+        }
+      } else if (gh == 0) {
+        for (int k = 0; k < 8; ++k) {
+          const int j = k < 4 ? k : n + k;
+          if (j <= nf + 6) {
+            R* d = gl + at(map_idx(j - 4, n, bc) + 4);
+            *d = *d + gl[at(j)];
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+
+  // (3) cells without a fix-up, then those with one: the general Jacobian's
+  // registers stay out of the first loop
+  bool any = false;
+  auto cells = [&](auto slow) {
+    constexpr bool SLOW = decltype(slow)::value;
+#pragma unroll 1
+    for (int l = l0; l < nl && line0 + l < nlines; l += lstep) {
+      long long stride;
+      const long long base = line_base(AX, line0 + l, a.g, stride);
+#pragma unroll 1
+      for (int x = p0; x < n; x += pstep) {
+        long long cell = base + x * stride;
+        // opaque: the loop keeps one index, not a pointer per array and field
+        __asm__ __volatile__("" : "+v"(cell));
+        R u[5];
+        load5(a.W, nc, cell, u);
+        // split-flux adjoint -> adjoint of W at the cell
+        unsigned f1 = 0;
+        const PrimV pv = c2p(u, f1);
+        any = any || f1 != 0;
+        if (SLOW != (f1 != 0)) continue;
+        const R* sp = s + (x + 4) * pitch + l;
+        const R* sm = s + area + (nf + 2 - x) * pitch + l;
+        double dp[5], dm[5], ub[5];
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          dp[c] = c < fields ? (double)sp[2 * c * area] : 0.0;
+          dm[c] = c < fields ? (double)sm[2 * c * area] : 0.0;
+        }
+        if constexpr (SLOW)
+          split_flux_vjp<R, AX>(u, c2p_jac((double)u[0], (double)u[1], (double)u[2], (double)u[3]), dp, dm, ub);
+        else
+          split_flux_vjp_known<R, AX>(u, pv.e, dp, dm, ub);
+#pragma unroll
+        for (int c = 0; c < 5; ++c) {
+          __asm__ __volatile__("" ::: "memory");  // one field's loads at a time: fewer registers
+          const long long k = c * nc + cell;
+          const R gv = a.first ? (R)ub[c] : a.G[k] + (R)ub[c];
+          if (a.stage == 0) {
+            a.G[k] = gv;
+          } else {
+            const R my = (c == 4 && a.skip_n) ? R(0) : a.mu[k];
+            const R t = fma(a.dt, gv, my);
+            if (a.stage == 3) {
+              a.lW[k] = R(2.0 / 3.0) * t;
+              a.acc[k] = R(1.0 / 3.0) * my;
+            } else if (a.stage == 2) {
+              a.lW[k] = R(0.25) * t;
+              a.acc[k] = fma(R(0.75), my, a.acc[k]);
+            } else {
+              a.lW[k] = a.acc[k] + t;
+            }
+          }
+        }
+      }
+    }
+  };
+  cells(std::false_type{});
+  if (any) cells(std::true_type{});
   add_fixups(a.fixups, fix);
 }
 
@@ -909,46 +892,51 @@ __global__ void __launch_bounds__(256) k_prim_vjp(const double* __restrict__ pri
 
 // ---------------------------------------------------------------------------
 // Host-side launchers.
-template <class R, int S>
-void launch_bound_adj(int AX, const AdjArgs<R>& a, long long nl, hipStream_t st) {
-  const unsigned nbb = (unsigned)((nl + kBoundLines - 1) / kBoundLines);
-  const dim3 tb(kBoundLines * 10);
-  if (AX == 0) hipLaunchKernelGGL((k_bound_adj<R, S, 0>), dim3(nbb), tb, 0, st, a);
-  if (AX == 1) hipLaunchKernelGGL((k_bound_adj<R, S, 1>), dim3(nbb), tb, 0, st, a);
-  if (AX == 2) hipLaunchKernelGGL((k_bound_adj<R, S, 2>), dim3(nbb), tb, 0, st, a);
+// Lines per workgroup of a line adjoint: 8 (FP64) or 4 (FP32), else 4 or 1, at
+// most the request, fewer while their LDS exceeds 64 KiB (one always fits: the
+// adjoint's grids are bounded so).  Run length: the one of 6, 8, 9 and 13 faces
+// with the shortest march in turns of the runs that those lines leave a wave
+// (by type and face count alone, so that every number of lines adds in the same
+// order); the other weights, less used, take 8.
+template <class R, int S, int AX, int L, int NL>
+void launch_line_adj_n(const AdjArgs<R>& a, long long nlines, size_t lds, hipStream_t st) {
+  const long long ng = (nlines + NL - 1) / NL;
+  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, NL>), dim3((unsigned)(((ng + 7) / 8) * 8)), dim3(line_adj_block((int)sizeof(R))), lds, st,
+                     a);
 }
 
-// Lines per workgroup of a line adjoint along AX: 1 for x lines (contiguous);
-// for y and z lines the request or fewer, so that n_x is a multiple, the
-// workgroup has at most 1024 lanes and its LDS stays within 64 KiB.
-// Automatic: 2 in FP32 (at n = 128 five such workgroups fit a CU's LDS, the
-// occupancy of one line per workgroup, and the strided loads fetch half the
-// cache lines: 128^3 backward 170 -> 150 ms; 4 lines: 156 ms), 1 in FP64
-// (twice the LDS per line: two lines cost a workgroup per CU, 3 % slower).
-template <class R>
-int line_adj_lines(int AX, const AdjArgs<R>& a) {
-  if (AX == 0) return 1;
-  const int n = a.g.n[AX];
-  int nl = a.lines > 0 ? a.lines : (sizeof(R) == 4 ? 2 : 1);
-  while (nl > 1 && (a.g.n[0] % nl != 0 || n * nl > 1024 ||
-                    (size_t)line_adj_pitch(n, nl) * nl * sizeof(R) > 65536))
-    nl /= 2;
-  return nl;
-}
-
-template <class R, int S, int AX, int NL>
-void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
-  const int n = a.g.n[AX];
+template <class R, int S, int AX, int L>
+void launch_line_adj_l(const AdjArgs<R>& a, hipStream_t st) {
+  const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
+  const int most = a.lines > 0 ? a.lines : (sizeof(R) == 8 ? 8 : 4);
   const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                    : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
-  const long long ng = nlines / NL;
-  const int tb = ((n * NL + 63) / 64) * 64;
-  const size_t lds = (size_t)line_adj_pitch(n, NL) * NL * sizeof(R);
-  const unsigned nb = (unsigned)(((ng + 7) / 8) * 8);
-  if (tb <= 256)
-    hipLaunchKernelGGL((k_line_adj<R, S, AX, 256, NL>), dim3(nb), dim3(tb), lds, st, a);
-  else
-    hipLaunchKernelGGL((k_line_adj<R, S, AX, 1024, NL>), dim3(nb), dim3(tb), lds, st, a);
+  auto lds = [&](int nl) { return line_adj_lds_bytes(AX, nf, L, nl, a.skip_n ? 4 : 5, (int)sizeof(R)); };
+  if (most >= 8 && lds(8) <= 65536) launch_line_adj_n<R, S, AX, L, 8>(a, nlines, lds(8), st);
+  else if (most >= 4 && lds(4) <= 65536) launch_line_adj_n<R, S, AX, L, 4>(a, nlines, lds(4), st);
+  else launch_line_adj_n<R, S, AX, L, 1>(a, nlines, lds(1), st);
+}
+
+template <class R, int S, int AX>
+void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
+  const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
+  if constexpr (S == kWenoZ) {
+    int L = 8, best = 1 << 30;
+    for (int c : {8, 6, 9, 13}) {
+      const int turn = (sizeof(R) == 8 ? 8 : 16) * c;
+      const int steps = (nf + turn - 1) / turn * (c + 1);  // and about one more to finish a run
+      if (steps < best) {
+        best = steps;
+        L = c;
+      }
+    }
+    if (L == 6) launch_line_adj_l<R, S, AX, 6>(a, st);
+    else if (L == 9) launch_line_adj_l<R, S, AX, 9>(a, st);
+    else if (L == 13) launch_line_adj_l<R, S, AX, 13>(a, st);
+    else launch_line_adj_l<R, S, AX, 8>(a, st);
+  } else {
+    launch_line_adj_l<R, S, AX, 8>(a, st);
+  }
 }
 
 template <class R, int S>
@@ -956,25 +944,9 @@ void launch_adj_axis_t(int AX, const AdjArgs<R>& a0, hipStream_t st) {
   AdjArgs<R> a = a0;
   a.inv_d = R(1.0 / a.g.dx[AX]);
   a.eps = R(4) * a.eps;  // indicators of the doubled split fluxes; the partials dR/da do not change
-  const long long nl = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
-                               : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
-  // The outflow face n-1/2 adds to G: before the line kernel when that one
-  // finishes G (fused combine), after it when that one starts G (first).
-  const bool bound = a.g.bc[AX] == 0;
-  if (bound && a.stage != 0) launch_bound_adj<R, S>(AX, a, nl, st);
-  const int lines = line_adj_lines<R>(AX, a);
-  if (AX == 0) launch_line_adj<R, S, 0, 1>(a, st);
-  if (AX == 1) {
-    if (lines == 4) launch_line_adj<R, S, 1, 4>(a, st);
-    else if (lines == 2) launch_line_adj<R, S, 1, 2>(a, st);
-    else launch_line_adj<R, S, 1, 1>(a, st);
-  }
-  if (AX == 2) {
-    if (lines == 4) launch_line_adj<R, S, 2, 4>(a, st);
-    else if (lines == 2) launch_line_adj<R, S, 2, 2>(a, st);
-    else launch_line_adj<R, S, 2, 1>(a, st);
-  }
-  if (bound && a.stage == 0) launch_bound_adj<R, S>(AX, a, nl, st);
+  if (AX == 0) launch_line_adj<R, S, 0>(a, st);
+  if (AX == 1) launch_line_adj<R, S, 1>(a, st);
+  if (AX == 2) launch_line_adj<R, S, 2>(a, st);
 }
 
 template <class R>

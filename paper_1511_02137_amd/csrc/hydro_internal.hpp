@@ -194,21 +194,30 @@ struct AdjArgs {
   // skipped and its outputs (G, lW, acc) are zero.  N enters no other field's
   // flux and no source, so with a zero N adjoint on entry this is exact.
   int skip_n;
-  // lines per workgroup of the y and z line adjoints requested by the caller
-  // (0: automatic; 1, 2 or 4); the launcher takes fewer where they do not fit
+  // lines per workgroup requested by the caller (0: automatic; 1, 2 or 4): the
+  // launcher takes 8, 4 or 1, at most the request and what fits
   int lines;
 };
 
-// LDS of the line adjoint kernel, in elements of the field type: split fluxes
-// [2][5][n+8] and the face partials of both splits [2][7][n+16] (face x at
-// x+8, zero pads so the gather needs no bounds tests).
+// Bound on the adjoint's axis lengths (hydro_workspace_bytes): elements of the
+// field type that must fit 64 KiB.
 constexpr long long line_adj_lds_elems(int n) { return 10LL * (n + 8) + 14LL * (n + 16); }
-// Elements between the LDS areas of the nl lines of one line-adjoint
-// workgroup: padded so that neighbouring lines' copies of a slot are 32/nl
-// four-byte banks apart.
-constexpr long long line_adj_pitch(int n, int nl) {
-  return nl == 1 ? line_adj_lds_elems(n)
-                 : line_adj_lds_elems(n) + ((32 / nl - line_adj_lds_elems(n) % 32) % 32 + 32) % 32;
+// Line adjoint: LDS slots of a line of nf faces in runs of L (the last run's
+// values included), words between slots (x: one more, so that a wave's cells of
+// a row fall in different banks), bytes of the two areas of each field, of the
+// six values a line that pass from a turn to the next, and of phi.
+// Workgroups: with 128 VGPRs in FP64 two of eight waves share a CU (four lines
+// in four waves, with half the LDS and loads half as wide, were 1.2x slower at
+// 60x52x66); FP32 takes four waves, five workgroups a CU (eight waves of eight
+// lines: 112 against 107 us an axis at 128^3).
+__host__ __device__ constexpr int line_adj_block(int elem) { return elem == 8 ? 512 : 256; }
+__host__ __device__ constexpr int line_adj_slots(int nf, int L) { return (nf + L - 1) / L * L + 7; }
+__host__ __device__ constexpr int line_adj_pitch(int AX, int lines) { return AX == 0 && lines > 1 ? lines + 1 : lines; }
+// phi rows: the faces and zeros up to a run's length less one on each side
+__host__ __device__ constexpr int line_adj_phi_rows(int nf, int L) { return 2 * ((nf + L - 1) / L * L) - nf; }
+__host__ __device__ constexpr size_t line_adj_lds_bytes(int AX, int nf, int L, int lines, int fields, int elem) {
+  return (size_t)fields * ((2 * line_adj_slots(nf, L) + line_adj_phi_rows(nf, L)) * line_adj_pitch(AX, lines) +
+                           12 * lines) * elem;
 }
 
 // Arguments of the jet-source adjoint kernel.
