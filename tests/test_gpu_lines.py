@@ -83,6 +83,38 @@ def test_batch_of_mixed_tile_lengths_is_bitwise(precision):
         assert np.array_equal(b.U[e].cpu().numpy(), U), e
 
 
+# shorter than the ghosts, a turn's last run full and partly filled, two turns
+ADJ_SHAPES = [(1, 3, 7), (8, 9, 2), (63, 4, 5), (5, 64, 6), (6, 5, 72), (71, 3, 4), (4, 103, 3), (2, 7, 128)]
+
+
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", ADJ_SHAPES)
+def test_line_adjoint_at_run_edges(n, bc):
+    """<J^T W, V> against the oracle's forward mode <W, J V> for one step of a
+    rough state: both are exact derivatives of the discrete map, so they agree
+    to rounding times the step's conditioning, 1e-10 of the sum of |products|;
+    any number of lines per workgroup gives the same bits."""
+    w = W.small_event(1, n=n, with_jet=False)
+    pb = O.Problem(n=w.n, dx=w.dx, t0=w.t0, dt=w.dt, bc=(bc,) * 3)
+    U0 = rough_state(n, sum(n))
+    rng = np.random.default_rng(sum(n) + 1)
+    V, Wt = rng.uniform(-1.0, 1.0, U0.shape), rng.uniform(-1.0, 1.0, U0.shape)
+    _, JV = O.jvp(pb, U0, V, 1, [])
+    outs = []
+    for lines in (0, 1, 4):
+        h = H().from_workload(w, bc=(bc,) * 3, adjoint_k=1)
+        h.set_option(H().OPT_ADJ_LINES, lines)
+        lam = torch.from_numpy(Wt).cuda()
+        h.adjoint_step(torch.from_numpy(U0).cuda(), 0, None, 1, lam, None)
+        torch.cuda.synchronize()
+        outs.append(lam.cpu().numpy())
+        h.close()
+    rel = abs(np.sum(outs[0] * V) - np.sum(Wt * JV)) / np.sum(np.abs(Wt * JV))
+    print(n, bc, "dot product %.2e" % rel, flush=True)
+    assert rel <= 1e-10
+    assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
+
+
 def test_freezeout_range_of_p_t():
     """p_T from 1e-3 to where every exponential is subnormal or zero: rows
     within 1e-12 of their largest value (an exponent x carries x 2^-53, 6e-14
