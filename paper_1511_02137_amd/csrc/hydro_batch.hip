@@ -43,6 +43,7 @@ struct hydro_batch {
   int64_t step = 0;
   int cus = 256;
   long long blocks[3] = {0, 0, 0}; // workgroups per axis launch (0: one per item)
+  bool picked[3] = {false, false, false};  // blocks[] was set or tuned, not the default
   int xrows = 0;                   // x pass: 0 LDS tiles, 1 groups of whole rows (+ boundary faces)
   int tile_a[3] = {0, 0, 0};       // per axis: the tile length every event shares (31, 32), else 0
   int xtb = 256;                   // x-row workgroup size (limiter, MUSTA-FORCE)
@@ -98,6 +99,15 @@ BatchArgs<R> batch_args(const hydro_batch* b, int AX, int stage) {
   return a;
 }
 
+// Workgroups of an axis launch.  Unless they were set or tuned, plain WENO
+// faces take one item per workgroup: their persistent form has 68 VGPRs (FP32)
+// instead of 44, a workgroup per CU fewer.  16 FP32 events of 64 to 128 cells an
+// edge, us an axis (x, y, z): persistent, two workgroups per CU 462, 510, 550;
+// one item each 371, 374, 395.
+long long axis_blocks(const hydro_batch* b, int AX) {
+  return !b->picked[AX] && line_scheme(face_scheme(b->cfg[0])) ? 0 : b->blocks[AX];
+}
+
 // One stage of every event: x tiles (or x rows and the outflow x faces),
 // y tiles, jets, z tiles (+ RK combine).
 template <class R>
@@ -105,14 +115,14 @@ hipError_t stage_launches(hydro_batch* b, int stage, hipStream_t st) {
   const int scheme = face_scheme(b->cfg[0]);
   hipError_t e;
   if (b->xrows) {
-    e = launch_batch_axis<R>(3, batch_args<R>(b, 3, stage), scheme, b->blocks[0], st);
+    e = launch_batch_axis<R>(3, batch_args<R>(b, 3, stage), scheme, axis_blocks(b, 0), st);
     if (e == hipSuccess) e = launch_batch_axis<R>(4, batch_args<R>(b, 4, stage), scheme, 0, st);
   } else {
-    e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, b->blocks[0], st);
+    e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, axis_blocks(b, 0), st);
   }
-  if (e == hipSuccess) e = launch_batch_axis<R>(1, batch_args<R>(b, 1, stage), scheme, b->blocks[1], st);
+  if (e == hipSuccess) e = launch_batch_axis<R>(1, batch_args<R>(b, 1, stage), scheme, axis_blocks(b, 1), st);
   if (e == hipSuccess) e = launch_batch_jet<R>(batch_args<R>(b, 0, stage), st);
-  if (e == hipSuccess) e = launch_batch_axis<R>(2, batch_args<R>(b, 2, stage), scheme, b->blocks[2], st);
+  if (e == hipSuccess) e = launch_batch_axis<R>(2, batch_args<R>(b, 2, stage), scheme, axis_blocks(b, 2), st);
   return e;
 }
 
@@ -247,7 +257,10 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
   long long best[3];
   int xr = 0;
   if (cache_lookup(cache, key, best, &xr)) {
-    for (int a = 0; a < 3; ++a) b->blocks[a] = best[a];
+    for (int a = 0; a < 3; ++a) {
+      b->blocks[a] = best[a];
+      b->picked[a] = true;
+    }
     b->xrows = xr;
     if (from_cache) *from_cache = 1;
     drop_graph(b);
@@ -284,10 +297,12 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
       bx[AX == 3] = pick;
     } else {
       b->blocks[AX] = pick;
+      b->picked[AX] = true;
     }
   }
   b->xrows = tx[1] < tx[0] ? 1 : 0;
   b->blocks[0] = bx[b->xrows];
+  b->picked[0] = true;
   cache_store(cache, key, b->blocks, b->xrows);
   if (from_cache) *from_cache = 0;
   drop_graph(b);
@@ -513,6 +528,7 @@ int hydro_batch_set_option(hydro_batch* b, int option, long long value) {
     case HYDRO_BOPT_BLOCKS_Z:
       if (value < 0) return bfail(b, HYDRO_EINVAL, "workgroup count must be >= 0");
       b->blocks[option - HYDRO_BOPT_BLOCKS_X] = value;
+      b->picked[option - HYDRO_BOPT_BLOCKS_X] = true;
       drop_graph(b);
       return HYDRO_OK;
     case HYDRO_BOPT_GRAPH:
