@@ -511,7 +511,7 @@ __device__ __forceinline__ int ngp_index(double x, int n, double dx) {
 }
 
 __device__ __forceinline__ double temperature(double e, double g, double hc) {
-  return pow(30.0 * e * (hc * hc * hc) / (g * 3.14159265358979323846 * 3.14159265358979323846), 0.25);
+  return sqrt(sqrt(30.0 * e * (hc * hc * hc) / (g * 3.14159265358979323846 * 3.14159265358979323846)));
 }
 
 __device__ __forceinline__ double energy_loss(const JetDev& jt, double T, double ell, double hc) {

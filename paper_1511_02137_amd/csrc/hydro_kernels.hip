@@ -834,108 +834,169 @@ __global__ void __launch_bounds__(512) k_xtile(StageArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Jet source (Eq. 2 and 3).  One workgroup of 512 threads; jets in order.
+// Jet source (Eq. 2 and 3).  One workgroup of 512 threads.  The kernel is a
+// chain of memory latencies and of serial FP64 arithmetic (a microsecond each),
+// not work, so every lane finds the jet's cell itself and all that needs no
+// other result is under way at once.  NGP: lane j of the first wave takes jet
+// j; jets in one cell add in jet order, each lane of that cell forming the same
+// sum (ensemble with up to three jets an event: 6.4 us a launch, 12.5
+// one jet after the other).
+// Gaussian: jets in order, 343 lanes for the 7^3 footprint, its weights by 21
+// lanes, the sums by wave shuffles (5.1 us a launch; 9.9 with the weights by
+// one lane and two trees of nine barriers).
 template <class R>
 __device__ __forceinline__ void jet_body(const JetArgs& a) {
   const R* W = static_cast<const R*>(a.W);
   R* D = static_cast<R*>(a.D);
   const long long nc = a.g.nc;
   const double dV = a.g.dx[0] * a.g.dx[1] * a.g.dx[2];
-  __shared__ double red_w[512], red_t[512];
-  __shared__ double wax[3][7];
-  __shared__ int ctr_s[3];
-  __shared__ int inside_s;
+  const int t = threadIdx.x;
   unsigned fix = 0;
+  // deposits of a step, added to the ledger in jet order
+  auto deposit_of = [&](int j, double P) {
+    return a.dt * ((1.0 / 6.0) * a.s->P[0][j] + (1.0 / 6.0) * a.s->P[1][j] + (2.0 / 3.0) * P);
+  };
+  if (a.deposit == 0) {
+    if (t >= 64) return;
+    const bool mine = t < a.njet;
+    const JetDev jt = a.s->jets[mine ? t : 0];
+    const double E = a.s->E_jet[mine ? t : 0];
+    const bool chi = mine && E > 0.0;
+    const double ell = a.t - jt.t_start;
+    int c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) c[d] = ngp_index(jt.x0[d] + jt.dir[d] * ell, a.g.n[d], a.g.dx[d]);
+    const bool in = chi && ell >= 0.0 && c[0] >= 0 && c[1] >= 0 && c[2] >= 0;
+    long long cell = -1 - t;  // distinct
+    double P = 0.0;
+    R dv[4] = {R(0), R(0), R(0), R(0)}, sv[4] = {R(0), R(0), R(0), R(0)};
+    if (in) {
+      cell = ((long long)c[2] * a.g.n[1] + c[1]) * a.g.n[0] + c[0];
+      R u[5];
+      load5(W, nc, cell, u);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) dv[d] = D[d * nc + cell];
+      const PrimV pv = c2p(u, fix);
+      P = energy_loss(jt, temperature(pv.e, a.eos_dof, a.hbarc), ell, a.hbarc);
+      const double s0 = P / dV;
+      sv[0] = (R)s0;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) sv[1 + d] = (R)(jt.dir[d] * s0);
+    }
+    for (int j = 0; j < a.njet; ++j) {
+      const bool same = __shfl(cell, j, 64) == cell;
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const R v = __shfl(sv[d], j, 64);
+        if (same) dv[d] = dv[d] + v;
+      }
+    }
+    if (in) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) D[d * nc + cell] = dv[d];
+    }
+    if (a.stage == 3) {
+      const double dep = chi ? deposit_of(t, P) : 0.0;
+      double ledger = a.s->ledger;
+      for (int j = 0; j < a.njet; ++j) {
+        const double v = __shfl(dep, j, 64);
+        if (__shfl(chi ? 1 : 0, j, 64)) ledger = ledger + v;
+      }
+      if (t == 0) a.s->ledger = ledger;
+      if (chi) a.s->E_jet[t] = E - dep > 0.0 ? E - dep : 0.0;
+    }
+    if (mine && a.stage > 0) a.s->P[a.stage - 1][t] = P;
+    add_fixups(&a.s->fixups, fix);
+    return;
+  }
+  __shared__ double red[8][2];
+  __shared__ double raw[3][7];
+  const int wd = t / 7, wm = t % 7;
   for (int j = 0; j < a.njet; ++j) {
     const JetDev jt = a.s->jets[j];
-    const bool chi = a.s->E_jet[j] > 0.0;
+    const double E = a.s->E_jet[j];
+    const bool chi = E > 0.0;
     const double ell = a.t - jt.t_start;
+    double x[3];
+    int c[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      x[d] = jt.x0[d] + jt.dir[d] * ell;
+      c[d] = ngp_index(x[d], a.g.n[d], a.g.dx[d]);
+    }
+    const bool in = chi && ell >= 0.0 && c[0] >= 0 && c[1] >= 0 && c[2] >= 0;  // uniform
     double P = 0.0;
-    if (threadIdx.x == 0) {
-      int in = (chi && ell >= 0.0) ? 1 : 0;
-      for (int d = 0; d < 3; ++d) {
-        const double x = jt.x0[d] + jt.dir[d] * ell;
-        const int c = ngp_index(x, a.g.n[d], a.g.dx[d]);
-        ctr_s[d] = c;
-        if (c < 0) in = 0;
-        if (a.deposit == 1) {
-          double sum = 0.0;
-          for (int m = 0; m < 7; ++m) {
-            const double del = cell_centre(c - 3 + m, a.g.n[d], a.g.dx[d]) - x;
-            wax[d][m] = exp(-(del * del) / (2.0 * a.g.dx[d] * a.g.dx[d]));
-            sum = sum + wax[d][m];
-          }
-          for (int m = 0; m < 7; ++m) wax[d][m] = wax[d][m] / sum;
-        }
-      }
-      inside_s = in;
-    }
-    __syncthreads();
-    if (inside_s) {
-      if (a.deposit == 0) {
-        if (threadIdx.x == 0) {
-          const long long cell = ((long long)ctr_s[2] * a.g.n[1] + ctr_s[1]) * a.g.n[0] + ctr_s[0];
-          R u[5], dv[4];  // the cell's state and its D, read together
+    if (in) {
+      // 7^3 footprint, thread t < 343 owns cell (mi, mj, mk)
+      const int mi = t % 7, mj = (t / 7) % 7, mk = t / 49;
+      long long cell = -1;
+      R u[5], dv[4];
+      if (t < 343) {
+        const int i = c[0] - 3 + mi, jj = c[1] - 3 + mj, k = c[2] - 3 + mk;
+        if (i >= 0 && i < a.g.n[0] && jj >= 0 && jj < a.g.n[1] && k >= 0 && k < a.g.n[2]) {
+          cell = ((long long)k * a.g.n[1] + jj) * a.g.n[0] + i;
           load5(W, nc, cell, u);
+#pragma unroll
           for (int d = 0; d < 4; ++d) dv[d] = D[d * nc + cell];
-          const PrimV pv = c2p(u, fix);
-          const double T = temperature(pv.e, a.eos_dof, a.hbarc);
-          P = energy_loss(jt, T, ell, a.hbarc);
-          const double s0 = P / dV;
-          D[cell] = dv[0] + (R)s0;
-          for (int d = 0; d < 3; ++d) D[(1 + d) * nc + cell] = dv[1 + d] + (R)(jt.dir[d] * s0);
-        }
-      } else {
-        // 7^3 footprint, thread t < 343 owns cell (mi, mj, mk)
-        const int t = threadIdx.x;
-        double w = 0.0, wT = 0.0;
-        long long cell = -1;
-        R dv[4];  // the cell's D, read with its state
-        if (t < 343) {
-          const int mi = t % 7, mj = (t / 7) % 7, mk = t / 49;
-          const int i = ctr_s[0] - 3 + mi, jj = ctr_s[1] - 3 + mj, k = ctr_s[2] - 3 + mk;
-          if (i >= 0 && i < a.g.n[0] && jj >= 0 && jj < a.g.n[1] && k >= 0 && k < a.g.n[2]) {
-            cell = ((long long)k * a.g.n[1] + jj) * a.g.n[0] + i;
-            w = wax[0][mi] * wax[1][mj] * wax[2][mk];
-            R u[5];
-            load5(W, nc, cell, u);
-            for (int d = 0; d < 4; ++d) dv[d] = D[d * nc + cell];
-            const PrimV pv = c2p(u, fix);
-            wT = w * temperature(pv.e, a.eos_dof, a.hbarc);
-          }
-        }
-        red_w[t] = w;
-        red_t[t] = wT;
-        __syncthreads();
-        for (int h = 256; h > 0; h >>= 1) {
-          if (t < h) {
-            red_w[t] = red_w[t] + red_w[t + h];
-            red_t[t] = red_t[t] + red_t[t + h];
-          }
-          __syncthreads();
-        }
-        const double wsum = red_w[0];
-        const double T = red_t[0] / wsum;
-        const double Pj = energy_loss(jt, T, ell, a.hbarc);
-        P = Pj * wsum;
-        if (cell >= 0) {
-          const double s0 = Pj * w / dV;
-          D[cell] = dv[0] + (R)s0;
-          for (int d = 0; d < 3; ++d) D[(1 + d) * nc + cell] = dv[1 + d] + (R)(jt.dir[d] * s0);
         }
       }
+      if (t < 21) {  // the lane's axis by selects (an index would put the structs in scratch memory)
+        const double xd = wd == 0 ? x[0] : (wd == 1 ? x[1] : x[2]);
+        const double dx = wd == 0 ? a.g.dx[0] : (wd == 1 ? a.g.dx[1] : a.g.dx[2]);
+        const int cd = wd == 0 ? c[0] : (wd == 1 ? c[1] : c[2]);
+        const int nd = wd == 0 ? a.g.n[0] : (wd == 1 ? a.g.n[1] : a.g.n[2]);
+        const double del = cell_centre(cd - 3 + wm, nd, dx) - xd;
+        raw[wd][wm] = exp(-(del * del) / (2.0 * dx * dx));
+      }
+      __syncthreads();
+      double w = 0.0, wT = 0.0;
+      if (cell >= 0) {
+        double sum[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          sum[d] = 0.0;
+#pragma unroll
+          for (int m = 0; m < 7; ++m) sum[d] = sum[d] + raw[d][m];
+        }
+        w = (raw[0][mi] / sum[0]) * (raw[1][mj] / sum[1]) * (raw[2][mk] / sum[2]);
+        const PrimV pv = c2p(u, fix);
+        wT = w * temperature(pv.e, a.eos_dof, a.hbarc);
+      }
+      double ws = w, wts = wT;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        ws = ws + __shfl_xor(ws, off, 64);
+        wts = wts + __shfl_xor(wts, off, 64);
+      }
+      if ((t & 63) == 0) {
+        red[t >> 6][0] = ws;
+        red[t >> 6][1] = wts;
+      }
+      __syncthreads();
+      double wsum = red[0][0], T = red[0][1];
+#pragma unroll
+      for (int k = 1; k < 8; ++k) {
+        wsum = wsum + red[k][0];
+        T = T + red[k][1];
+      }
+      T = T / wsum;
+      const double Pj = energy_loss(jt, T, ell, a.hbarc);
+      P = Pj * wsum;
+      if (cell >= 0) {
+        const double s0 = Pj * w / dV;
+        D[cell] = dv[0] + (R)s0;
+        for (int d = 0; d < 3; ++d) D[(1 + d) * nc + cell] = dv[1 + d] + (R)(jt.dir[d] * s0);
+      }
     }
-    if (threadIdx.x == 0 && a.stage > 0) {
-      a.s->P[a.stage - 1][j] = P;
+    if (t == 0 && a.stage > 0) {
       if (a.stage == 3 && chi) {
-        const double dep =
-            a.dt * ((1.0 / 6.0) * a.s->P[0][j] + (1.0 / 6.0) * a.s->P[1][j] + (2.0 / 3.0) * a.s->P[2][j]);
+        const double dep = deposit_of(j, P);
         a.s->ledger = a.s->ledger + dep;
-        const double rest = a.s->E_jet[j] - dep;
-        a.s->E_jet[j] = rest > 0.0 ? rest : 0.0;
+        a.s->E_jet[j] = E - dep > 0.0 ? E - dep : 0.0;
       }
+      a.s->P[a.stage - 1][j] = P;
     }
-    __syncthreads();
+    __syncthreads();  // D and raw, red before the next jet
   }
   add_fixups(&a.s->fixups, fix);
 }
