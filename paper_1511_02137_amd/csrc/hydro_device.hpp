@@ -279,13 +279,86 @@ __device__ __forceinline__ R weno5_face(R ai, R e1, R e2, const R* f, const R* F
   return fma(R(1.0 / 12.0), quot(num, den), ai);
 }
 
+// Both face values of a cell from one window (MUSTA-FORCE): `right` at i + 1/2
+// as above, `left` at i - 1/2, p_k(-1/2) = a_i - s_k/2 + c_k/12 with the linear
+// weights mirrored.  Differences, indicators and nonlinear weights serve both.
+// s_1 and s_2 take the slope (e2 + e3)/2, so that a mirrored window gives the
+// mirrored values bit for bit.
+template <class R>
+__device__ __forceinline__ void weno7_sides(R ai, R e2, R e3, R f1, R f2, R f3, const R* g, const R* G, R& right,
+                                            R& left) {
+  const R sm = R(0.5) * (e2 + e3);
+  const R s0 = fma(R(1.0 / (3.0 * kCurv)), g[0], fma(R(0.5 / kCurv), f1, e2));
+  const R s1 = fma(R(-1.0 / (6.0 * kCurv)), g[1], sm);
+  const R s2 = fma(R(-1.0 / (6.0 * kCurv)), g[2], sm);
+  const R s3 = fma(R(1.0 / (3.0 * kCurv)), g[3], fma(R(-0.5 / kCurv), f3, e3));
+  const R c0 = f1 + g[0], c3 = f3 - g[3];
+  const R b0 = fma(s0, s0, fma(c0, c0, G[0]));
+  const R b1 = fma(s1, s1, fma(f2, f2, G[1]));
+  const R b2 = fma(s2, s2, fma(f2, f2, G[2]));
+  const R b3 = fma(s3, s3, fma(c3, c3, G[3]));
+  const R tau = fma(R(3), b1 - b2, b0 - b3);  // enters squared
+  const R kR = R(6.0 * kCurv), kL = R(-6.0 * kCurv);
+  const R r0 = fma(kR, s0, c0), r1 = fma(kR, s1, f2), r2 = fma(kR, s2, f2), r3 = fma(kR, s3, c3);
+  const R l0 = fma(kL, s0, c0), l1 = fma(kL, s1, f2), l2 = fma(kL, s2, f2), l3 = fma(kL, s3, c3);
+  R numr, denr, numl, denl;
+  if (sizeof(R) == 8) {
+    const R B0 = b0 * b0, B1 = b1 * b1, B2 = b2 * b2, B3 = b3 * b3;
+    const R P01 = B0 * B1, P23 = B2 * B3;
+    const R t2 = tau * tau;
+    const R a0 = fma(t2, B1, P01), a1 = fma(t2, B0, P01), a2 = fma(t2, B3, P23), a3 = fma(t2, B2, P23);
+    const R P = R(4) * P01, Q = R(4) * P23;
+    numr = fma(P23, fma(R(12), a1 * r1, a0 * r0), P * fma(R(4.5), a2 * r2, a3 * r3));
+    denr = fma(P23, fma(R(12), a1, a0), P * fma(R(4.5), a2, a3));
+    numl = fma(P01, fma(R(12), a2 * l2, a3 * l3), Q * fma(R(4.5), a1 * l1, a0 * l0));
+    denl = fma(P01, fma(R(12), a2, a3), Q * fma(R(4.5), a1, a0));
+  } else {
+    const R z0 = tau * rcp_approx<R>(b0), z1 = tau * rcp_approx<R>(b1), z2 = tau * rcp_approx<R>(b2),
+            z3 = tau * rcp_approx<R>(b3);
+    const R w0 = fma(z0, z0, R(1)), w1 = fma(z1, z1, R(1)), w2 = fma(z2, z2, R(1)), w3 = fma(z3, z3, R(1));
+    numr = fma(R(4), w3 * r3, fma(R(18), w2 * r2, fma(R(12), w1 * r1, w0 * r0)));
+    denr = fma(R(4), w3, fma(R(18), w2, fma(R(12), w1, w0)));
+    numl = fma(R(4), w0 * l0, fma(R(18), w1 * l1, fma(R(12), w2 * l2, w3 * l3)));
+    denl = fma(R(4), w0, fma(R(18), w1, fma(R(12), w2, w3)));
+  }
+  right = fma(R(1.0 / (12.0 * kCurv)), quot(numr, denr), ai);
+  left = fma(R(1.0 / (12.0 * kCurv)), quot(numl, denl), ai);
+}
+
+template <class R>
+__device__ __forceinline__ void weno5_sides(R ai, R e1, R e2, const R* f, const R* F, R& right, R& left) {
+  const R s0 = fma(R(0.5), f[0], e1), s1 = R(0.5) * (e1 + e2), s2 = fma(R(-0.5), f[2], e2);
+  const R r0 = fma(R(6), s0, f[0]), r1 = fma(R(6), s1, f[1]), r2 = fma(R(6), s2, f[2]);
+  const R l0 = fma(R(-6), s0, f[0]), l1 = fma(R(-6), s1, f[1]), l2 = fma(R(-6), s2, f[2]);
+  const R b0 = fma(s0, s0, F[0]), b1 = fma(s1, s1, F[1]), b2 = fma(s2, s2, F[2]);
+  const R tau = b0 - b2;  // enters squared
+  R w0, w1, w2;
+  if (sizeof(R) == 8) {  // over the common denominator, in a form that mirrors
+    const R B0 = b0 * b0, B1 = b1 * b1, B2 = b2 * b2;
+    const R t2 = tau * tau;
+    w0 = (B0 + t2) * (B1 * B2);
+    w1 = (B1 + t2) * (B0 * B2);
+    w2 = (B2 + t2) * (B0 * B1);
+  } else {
+    const R z0 = tau * rcp_approx<R>(b0), z1 = tau * rcp_approx<R>(b1), z2 = tau * rcp_approx<R>(b2);
+    w0 = fma(z0, z0, R(1));
+    w1 = fma(z1, z1, R(1));
+    w2 = fma(z2, z2, R(1));
+  }
+  right = fma(R(1.0 / 12.0), quot(fma(R(3), w2 * r2, fma(R(6), w1 * r1, w0 * r0)), fma(R(3), w2, fma(R(6), w1, w0))),
+              ai);
+  left = fma(R(1.0 / 12.0), quot(fma(R(3), w0 * l0, fma(R(6), w1 * l1, w2 * l2)), fma(R(3), w0, fma(R(6), w1, w2))),
+             ai);
+}
+
 // L neighbouring faces of one line: put(k, R(a_k..a_{k+6})), k = 0..L-1, from
 // the values get(0..L+5), taken in this order, value k + 6 before face k;
 // schemes kWeno5* use the middle five of each window.
 // Differences are formed as the faces reach them and every face by the same
 // operations whatever L is, so that all splits of a line give the same bits.
-// The scheduling barriers keep the live set at one face.
-template <class R, int S, int L, class Get, class Put>
+// The scheduling barriers keep the live set at one face.  SIDES: put(k, right,
+// left) with both face values of the windows' middle cells (WENO-Z).
+template <class R, int S, int L, bool SIDES = false, class Get, class Put>
 __device__ __forceinline__ void weno_line(Get get, R eps, Put put) {
   if constexpr (S >= kWeno5Z) {
     R a[L + 6], e[L + 4], f[L + 3], F[L + 3];  // a[0] and a[k + 6] are read, not used
@@ -300,7 +373,13 @@ __device__ __forceinline__ void weno_line(Get get, R eps, Put put) {
           F[m - 3] = fma(R(13.0 / 12.0) * f[m - 3], f[m - 3], eps);
         }
       }
-      put(k, weno5_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f + k + 1, F + k + 1));
+      if constexpr (SIDES) {
+        R r, l;
+        weno5_sides<R>(a[k + 3], e[k + 2], e[k + 3], f + k + 1, F + k + 1, r, l);
+        put(k, r, l);
+      } else {
+        put(k, weno5_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f + k + 1, F + k + 1));
+      }
       if (L > 1) __builtin_amdgcn_sched_barrier(0);
     }
   } else {
@@ -317,7 +396,13 @@ __device__ __forceinline__ void weno_line(Get get, R eps, Put put) {
           G[m - 3] = fma(R(781.0 / 780.0) * g[m - 3], g[m - 3], eps);
         }
       }
-      put(k, weno7_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f[k + 1], f[k + 2], f[k + 3], g + k, G + k));
+      if constexpr (SIDES) {
+        R r, l;
+        weno7_sides<R>(a[k + 3], e[k + 2], e[k + 3], f[k + 1], f[k + 2], f[k + 3], g + k, G + k, r, l);
+        put(k, r, l);
+      } else {
+        put(k, weno7_face<R, S>(a[k + 3], e[k + 2], e[k + 3], f[k + 1], f[k + 2], f[k + 3], g + k, G + k));
+      }
       if (L > 1) __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -384,15 +469,15 @@ __device__ __forceinline__ void musta_force(R uL[5], R uR[5], int k, R F[5], uns
 
 // One face with the MUSTA-FORCE flux: at(c, m) is component c of the
 // conserved value at window point m = 0..7 (points i-3..i+4 for face i+1/2);
-// uL from points 0..6, uR from the mirrored stencil 7..1 (WENO5: the middle
-// five of each).
+// uL the right value of the cell with window 0..6, uR the left value of the
+// next one (WENO5: the middle five of each).
 template <class R, int SC, int AX, class At>
 __device__ __forceinline__ void musta_face(At at, R eps, int k, R F[5], unsigned& fix) {
   R uL[5], uR[5];
 #pragma unroll
   for (int c = 0; c < 5; ++c) {
-    uL[c] = weno7<R, SC>(at(c, 0), at(c, 1), at(c, 2), at(c, 3), at(c, 4), at(c, 5), at(c, 6), eps);
-    uR[c] = weno7<R, SC>(at(c, 7), at(c, 6), at(c, 5), at(c, 4), at(c, 3), at(c, 2), at(c, 1), eps);
+    weno_line<R, SC, 1, true>([&](int m) { return at(c, m); }, eps, [&](int, R r, R) { uL[c] = r; });
+    weno_line<R, SC, 1, true>([&](int m) { return at(c, m + 1); }, eps, [&](int, R, R l) { uR[c] = l; });
   }
   musta_force<R, AX>(uL, uR, k, F, fix);
 }

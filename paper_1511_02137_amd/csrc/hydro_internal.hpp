@@ -90,9 +90,8 @@ __host__ __device__ constexpr int tile_len(int n) {
   return ((n + 30) / 31) * 31 * 100 < 112 * (((n + 31) / 32) * 32) ? 31 : 32;
 }
 
-// Schemes whose faces are taken along lines (line_body, xline_body): plain
-// WENO fluxes, without the limiter or MUSTA-FORCE.
-__host__ __device__ constexpr bool line_scheme(int scheme) { return (scheme & (kPP | kMusta)) == 0; }
+// Schemes whose faces are taken along lines (line_body): all without the limiter.
+__host__ __device__ constexpr bool line_scheme(int scheme) { return (scheme & kPP) == 0; }
 
 // Line tiles: 16 lines of A + 8 points for each (field, split).
 constexpr int kLineX = 16;

@@ -8,16 +8,16 @@
 //   combine: Shu-Osher SSP-RK3.
 //
 // Work split (all kernels of a stage run on one stream):
-//   k_line    x, y or z faces of plain WENO fluxes from LDS tiles of 16 lines:
-//             one lane per point recovers it, lanes then march over runs of
-//             faces.  x assigns its divergence to D, y adds, z adds its own,
+//   k_line    x, y or z faces of plain WENO and MUSTA-FORCE fluxes from LDS
+//             tiles of 16 lines: one lane per point recovers it, lanes then
+//             march over runs of faces.  x assigns its divergence to D, y adds, z adds its own,
 //             does the RK combine and writes the stage output.
-//   k_xface   x faces with the limiter or MUSTA-FORCE, one workgroup per group
+//   k_xface   x faces with the limiter, one workgroup per group
 //             of whole x-rows: each lane recovers its cell, stores the split
 //             x-fluxes of the row plus 4+4 ghost cells in LDS, takes its left
 //             face and writes the x-divergence;
 //   k_xbound  the right boundary face of those rows (outflow x only);
-//   k_tile    y and z faces with the limiter or MUSTA-FORCE from LDS tiles.
+//   k_tile    y and z faces with the limiter from LDS tiles.
 //   k_march   lanes along x (coalesced), each lane marches along y or z over
 //             a segment, keeping the split fluxes of the 8-point stencil in
 //             registers: one new cell and one face per step, no halo recompute.
@@ -34,7 +34,7 @@
 namespace hydro {
 
 // ---------------------------------------------------------------------------
-// x-faces (limiter, MUSTA-FORCE): a workgroup owns rpi = blockDim / nx whole
+// x-faces (limiter): a workgroup owns rpi = blockDim / nx whole
 // rows (row0, row0 + 1, ...; fewer at the end of the grid).  LDS per row: the
 // split fluxes of its nx cells and 8 ghost slots (slot j holds padded position
 // j - 4), then the face values.  One lane per cell: it recovers its cell,
@@ -151,10 +151,8 @@ __device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0
   if (act) {
     // face x - 1/2: F+ at x-4..x+2 (slots x..x+6), F- at x-3..x+3 (slots x+1..x+7)
 #pragma unroll
-    for (int c = 0; c < 5 && (S & kMusta) == 0; ++c)
+    for (int c = 0; c < 5; ++c)
       Fh[c] = face_flux<R, (S & 7)>(sFp + c * P + x, sFm + c * P + x, a.eps);
-    if constexpr ((S & kMusta) != 0)
-      musta_face<R, (S & 7), 0>([&](int c, int m) { return sFp[c * P + x + m]; }, a.eps, a.musta_k, Fh, fix);
     if constexpr ((S & kPP) != 0) {  // cells x - 1 and x: slots x + 3 and x + 4
       pp_limit<R>(
           Fh, [&](int c, int k) { return ((k & 1) ? sFm : sFp)[c * P + x + 3 + (k >> 1)]; }, a.pp_mu);
@@ -226,30 +224,14 @@ __device__ __forceinline__ void xbound_body(const StageArgs<R>& a, long long gro
     const int l = t / 10, r = t % 10, c = r >> 1;
     const long long row = group * kXBoundRows + l;
     if (row < rows) {
-      const int cm = ((S & kMusta) != 0) ? c : 5 + c;  // MUSTA: both states from the conserved values
       sR[l][r] = (r & 1) == 0
                      ? weno7<R, (S & 7)>(sF[l][0][c], sF[l][1][c], sF[l][2][c], sF[l][3][c], sF[l][4][c], sF[l][5][c],
                                    sF[l][6][c], a.eps)
-                     : weno7<R, (S & 7)>(sF[l][7][cm], sF[l][6][cm], sF[l][5][cm], sF[l][4][cm],
-                                   sF[l][3][cm], sF[l][2][cm], sF[l][1][cm], a.eps);
+                     : weno7<R, (S & 7)>(sF[l][7][5 + c], sF[l][6][5 + c], sF[l][5][5 + c], sF[l][4][5 + c],
+                                   sF[l][3][5 + c], sF[l][2][5 + c], sF[l][1][5 + c], a.eps);
     }
   }
   __syncthreads();
-  if constexpr ((S & kMusta) != 0) {  // one lane per row: the MUSTA-FORCE flux of (uL, uR)
-    if (t < kXBoundRows && group * kXBoundRows + t < rows) {
-      const int l = t;
-      R uL[5], uR[5], F[5];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        uL[c] = sR[l][2 * c];
-        uR[c] = sR[l][2 * c + 1];
-      }
-      musta_force<R, 0>(uL, uR, a.musta_k, F, fix);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sF[l][0][c] = F[c];  // point 0 is no longer read
-    }
-    __syncthreads();
-  }
   if constexpr ((S & kPP) != 0) {  // one lane per row: cell nx-1 (point 3) and its copy (point 4)
     if (t < kXBoundRows && group * kXBoundRows + t < rows) {
       const int l = t;
@@ -266,7 +248,7 @@ __device__ __forceinline__ void xbound_body(const StageArgs<R>& a, long long gro
     const int l = t / 5, c = t % 5;
     const long long row = group * kXBoundRows + l;
     if (row < rows) {
-      const R r = ((S & (kPP | kMusta)) != 0) ? sF[l][0][c] : sR[l][2 * c] + sR[l][2 * c + 1];
+      const R r = ((S & kPP) != 0) ? sF[l][0][c] : sR[l][2 * c] + sR[l][2 * c + 1];
       R* d = a.D + c * nc + row * nx + nx - 1;
       *d = (*d - r) * a.inv_d;
     }
@@ -370,7 +352,7 @@ __global__ void __launch_bounds__(256) k_march(StageArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// y- or z-faces from an LDS tile (AX = 1 or 2; limiter, MUSTA-FORCE).  A workgroup of 512 lanes
+// y- or z-faces from an LDS tile (AX = 1 or 2; limiter).  A workgroup of 512 lanes
 // owns 16 cells along x (coalesced 128-byte rows) by 31 cells along AX at one
 // value of the remaining axis, so that its 32 face rows are exactly one face
 // per lane.  It stores the split AX-fluxes of its 16 x 39 points (4 ghost rows on each side) in LDS,
@@ -470,13 +452,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
   R Fh[5], Fh2[5];
   const bool has1 = xin && ta < nf;
   const bool has2 = (kTileA + 1) * kTileX > 512 && xin && threadIdx.x < kTileX && kTileA < nf;
-  if constexpr ((S & kMusta) != 0) {  // face row f: points in slots f..f+7
-    auto at = [&](int f) {
-      return [=](int c, int m) { return sFp[(c * kTileP + f + m) * kTileXP + tx]; };
-    };
-    if (has1) musta_face<R, (S & 7), AX>(at(ta), a.eps, a.musta_k, Fh, fix);
-    if (has2) musta_face<R, (S & 7), AX>(at(kTileA), a.eps, a.musta_k, Fh2, fix);
-  } else if (has1) {
+  if (has1) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const R* fp = sFp + (c * kTileP + ta) * kTileXP + tx;
@@ -487,7 +463,7 @@ __device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by,
                           fm[2 * kTileXP], fm[kTileXP], a.eps);
     }
   }
-  if ((S & kMusta) == 0 && has2) {
+  if (has2) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const R* fp = sFp + (c * kTileP + kTileA) * kTileXP + tx;
@@ -547,8 +523,8 @@ __global__ void __launch_bounds__(512) k_tile(StageArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// Faces taken along lines (plain WENO fluxes; the limiter and MUSTA-FORCE use
-// the bodies above).  A lane marches over neighbouring faces of one split of
+// Faces taken along lines (plain WENO fluxes, and below MUSTA-FORCE; the limiter
+// uses the bodies above).  A lane marches over neighbouring faces of one split of
 // one field of its line, so that the differences and their indicator terms of
 // a point serve every face of the run (weno_line).  A workgroup has eight
 // waves, which the hardware deals evenly over the four SIMDs; the ten (field,
@@ -598,6 +574,7 @@ constexpr int kLineRun = 8;
 
 template <class R, int S, int AX, bool LAST, int A>
 __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
+  constexpr bool kM = (S & kMusta) != 0;
   constexpr int kP = A + 8;  // points of a line
   constexpr int kRow = AX == 0 ? kLineX + 1 : kLineX;
   constexpr int kArea = kP * kRow;  // one (field, split): area 2 field + split
@@ -630,7 +607,7 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       sp[2 * c * kArea] = Fp[c];
-      sm[2 * c * kArea] = Fm[c];
+      if (!kM) sm[2 * c * kArea] = Fm[c];
     }
   };
   // waves 6 and 7 also take ghost slots 0..3 and len + 4..len + 7; their loads
@@ -661,30 +638,93 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
   }
   if (ghost) point(gl, gslot, ug);
   __syncthreads();
-  // face row f: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, its result in
-  // row f; F- at slots f+7..f+1, stored from row A - f on, its result there
   const int xl = t & (kLineX - 1), grp = (t >> 4) & 3;
-  {
-    R* area = s + w * kArea + grp * kLineRun * kRow + xl;
+  if constexpr (kM) {
+    // MUSTA-FORCE: points in area 2 field; window q (slots q..q+6, cell slot
+    // q + 3) gives uL of face row q (right value) and uR of face row q - 1
+    // (left value).  Waves 2c and 2c + 1 march over rows 0..15 and 16..31 of
+    // field c = 0..3, every lane takes one window of N, and lanes of the first
+    // waves the windows from 32 on; the results wait in registers until all
+    // points are read, then uL goes to area 2 field and uR to the next.
+    // One window per cell and field instead of two per face, and then one lane
+    // per face with its 3 k recoveries, which bound the kernel: ~112 registers,
+    // so 4 waves a SIMD (6 would spill).  At 128^3 in double precision, k = 2:
+    // 106 to 114 us a launch, a step 1170 -> 895 us.
+    const R* v4 = s + 2 * (w >> 1) * kArea + ((w & 1) * 16 + grp * 4) * kRow + xl;
+    R ur[4], ul[4], nr, nl, xr = R(0), xm = R(0);
+    weno_line<R, (S & 7), 4, true>([&](int m) { return v4[m * kRow]; }, a.eps, [&](int k, R r, R l) {
+      ur[k] = r;
+      ul[k] = l;
+    });
+    const int q4 = (w & 1) * 16 + grp * 4, qn = t >> 4;
+    const R* vn = s + 8 * kArea + qn * kRow + xl;
+    weno_line<R, (S & 7), 1, true>([&](int m) { return vn[m * kRow]; }, a.eps, [&](int, R r, R l) {
+      nr = r;
+      nl = l;
+    });
+    // windows 32 .. A + 1
+    const int xc = (t >> 4) % 5, xq = 32 + (t >> 4) / 5;
+    const bool extra = xq <= A + 1;
+    const R* vx = s + 2 * xc * kArea + xq * kRow + xl;
+    if (extra) {
+      weno_line<R, (S & 7), 1, true>([&](int m) { return vx[m * kRow]; }, a.eps, [&](int, R r, R l) {
+        xr = r;
+        xm = l;
+      });
+    }
+    __syncthreads();
+    auto store = [&](int c, int q, R r, R l) {
+      R* d = s + 2 * c * kArea + q * kRow + xl;
+      if (q <= A) d[0] = r;
+      if (q > 0) d[kArea - kRow] = l;
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k) store(w >> 1, q4 + k, ur[k], ul[k]);
+    store(4, qn, nr, nl);
+    if (extra) store(xc, xq, xr, xm);
+    __syncthreads();
+    // one lane per face: row t / 16, and row 32 by the first 16 lanes
+    auto flux = [&](int row) {
+      R* d = s + row * kRow + xl;
+      R uL[5], uR[5], F[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        uL[c] = d[2 * c * kArea];
+        uR[c] = d[(2 * c + 1) * kArea];
+      }
+      musta_force<R, AX>(uL, uR, a.musta_k, F, fix);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) d[2 * c * kArea] = F[c];
+    };
+    const bool line_in = bx * kLineX + xl < no;
+    if (line_in && qn <= len) flux(qn);
+    if (A == 32 && t < kLineX && line_in && len == 32) flux(32);
+    __syncthreads();
+  } else {
+    // face row f: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, its result in
+    // row f; F- at slots f+7..f+1, stored from row A - f on, its result there
+    {
+      R* area = s + w * kArea + grp * kLineRun * kRow + xl;
 #pragma unroll 1
-    for (int u = 0; u < 32; u += 4 * kLineRun, area += 4 * kLineRun * kRow)
-      line_faces<R, S, kLineRun>(area, [](int m) { return m * kRow; }, a.eps);
+      for (int u = 0; u < 32; u += 4 * kLineRun, area += 4 * kLineRun * kRow)
+        line_faces<R, S, kLineRun>(area, [](int m) { return m * kRow; }, a.eps);
+    }
+    // N: split w & 1, rows 2q and 2q + 1, q = 4 (w >> 1) + grp
+    R* const nrow = s + (8 + (w & 1)) * kArea + ((w >> 1) * 8 + grp * 2) * kRow + xl;
+    R nf[2];
+    weno_line<R, S, 2>([&](int m) { return nrow[m * kRow]; }, a.eps, [&](int k, R v) { nf[k] = v; });
+    R ex = R(0);
+    const bool extra = A == 32 && t < 160;  // row 32 of area t / 16
+    R* const xrow = s + (t >> 4) * kArea + 32 * kRow + xl;
+    if (extra) {
+      weno_line<R, S, 1>([&](int m) { return xrow[m * kRow]; }, a.eps, [&](int, R v) { ex = v; });
+    }
+    __syncthreads();  // the points of N and of row 32 are no longer read
+    nrow[0] = nf[0];
+    nrow[kRow] = nf[1];
+    if (extra) *xrow = ex;
+    __syncthreads();
   }
-  // N: split w & 1, rows 2q and 2q + 1, q = 4 (w >> 1) + grp
-  R* const nrow = s + (8 + (w & 1)) * kArea + ((w >> 1) * 8 + grp * 2) * kRow + xl;
-  R nf[2];
-  weno_line<R, S, 2>([&](int m) { return nrow[m * kRow]; }, a.eps, [&](int k, R v) { nf[k] = v; });
-  R ex = R(0);
-  const bool extra = A == 32 && t < 160;  // row 32 of area t / 16
-  R* const xrow = s + (t >> 4) * kArea + 32 * kRow + xl;
-  if (extra) {
-    weno_line<R, S, 1>([&](int m) { return xrow[m * kRow]; }, a.eps, [&](int, R v) { ex = v; });
-  }
-  __syncthreads();  // the points of N and of row 32 are no longer read
-  nrow[0] = nf[0];
-  nrow[kRow] = nf[1];
-  if (extra) *xrow = ex;
-  __syncthreads();
   if (own) {
     // LAST, stages 2 and 3: the five U^n values are read before any output
     // is stored (out may be U^n itself, so the compiler would otherwise keep
@@ -698,8 +738,8 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
     const R* sm = s + kArea + (A - 1 - ta) * kRow + tx;  // F- of the right face; the left face's follows
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-      const R fl = sp[2 * c * kArea] + sm[2 * c * kArea + kRow];
-      const R fr = sp[2 * c * kArea + kRow] + sm[2 * c * kArea];
+      const R fl = kM ? sp[2 * c * kArea] : sp[2 * c * kArea] + sm[2 * c * kArea + kRow];
+      const R fr = kM ? sp[2 * c * kArea + kRow] : sp[2 * c * kArea + kRow] + sm[2 * c * kArea];
       const R div = (fl - fr) * a.inv_d;
       if (AX == 0) {
         a.D[c * nc + cell] = div;
@@ -714,7 +754,7 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 }
 
 template <class R, int S, int AX, bool LAST, int A>
-__global__ void __launch_bounds__(kLineBlock, 6) k_line(StageArgs<R> a) {
+__global__ void __launch_bounds__(kLineBlock, (S & kMusta) ? 4 : 6) k_line(StageArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   // blockIdx.x: 16 lines; tile along AX and transverse index in either order
   unsigned b0 = blockIdx.x, b1 = blockIdx.y;
@@ -779,13 +819,7 @@ __device__ __forceinline__ void xtile_body(const StageArgs<R>& a, int bx, int by
   const bool has1 = yin && f < nf;
   const bool has2 = (kXTileX + 1) * kXTileY > 512 && yin && threadIdx.x < kXTileY && kXTileX < nf;
   R Fh[5], Fh2[5];
-  if constexpr ((S & kMusta) != 0) {  // face row f: points in slots f..f+7
-    auto at = [&](int fr) {
-      return [=](int c, int m) { return sFp[(c * kXTileP + fr + m) * kXTileY + r]; };
-    };
-    if (has1) musta_face<R, (S & 7), 0>(at(f), a.eps, a.musta_k, Fh, fix);
-    if (has2) musta_face<R, (S & 7), 0>(at(kXTileX), a.eps, a.musta_k, Fh2, fix);
-  } else if (has1) {
+  if (has1) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const R* fp = sFp + (c * kXTileP + f) * kXTileY + r;
@@ -796,7 +830,7 @@ __device__ __forceinline__ void xtile_body(const StageArgs<R>& a, int bx, int by
                           fm[2 * kXTileY], fm[kXTileY], a.eps);
     }
   }
-  if ((S & kMusta) == 0 && has2) {
+  if (has2) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       const R* fp = sFp + (c * kXTileP + kXTileX) * kXTileY + r;
@@ -1540,7 +1574,7 @@ void launch_bline(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStr
   if (AX == 2) launch_bline_ax<R, S, 2>(persist, grid, b, st);
 }
 
-// The limiter and MUSTA-FORCE.
+// The limiter.
 template <class R, int S>
 void launch_bface(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
   const size_t lds = (size_t)2 * 5 * (32 + 8) * 16 * sizeof(R);  // the largest tile (A = 32)
@@ -1560,7 +1594,7 @@ void launch_bface(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStr
     return;
   }
   // the uniform-tile-length kernels for WENO7-Z with the limiter (the other
-  // limited schemes and MUSTA-FORCE keep the general one)
+  // limited schemes keep the general one)
   if constexpr (S == (kWenoZ | kPP)) {
     if (b.tile_a == 31 || b.tile_a == 32) {
       launch_btile_u<R, S>(AX, b.tile_a, persist, grid, b, st);
@@ -1590,8 +1624,8 @@ hipError_t launch_batch_axis(int AX, const BatchArgs<R>& b, int scheme, long lon
     case kWeno5Z | kPP: launch_bface<R, (kWeno5Z | kPP)>(AX, persist, grid, b, st); break;
     case kWeno5JS | kPP: launch_bface<R, (kWeno5JS | kPP)>(AX, persist, grid, b, st); break;
     case kWeno5Linear | kPP: launch_bface<R, (kWeno5Linear | kPP)>(AX, persist, grid, b, st); break;
-    case kWenoZ | kMusta: launch_bface<R, (kWenoZ | kMusta)>(AX, persist, grid, b, st); break;
-    case kWeno5Z | kMusta: launch_bface<R, (kWeno5Z | kMusta)>(AX, persist, grid, b, st); break;
+    case kWenoZ | kMusta: launch_bline<R, (kWenoZ | kMusta)>(AX, persist, grid, b, st); break;
+    case kWeno5Z | kMusta: launch_bline<R, (kWeno5Z | kMusta)>(AX, persist, grid, b, st); break;
     default: launch_bline<R, kWenoZ>(AX, persist, grid, b, st); break;
   }
   return hipGetLastError();

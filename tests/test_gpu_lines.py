@@ -65,6 +65,37 @@ def test_rhs_at_tile_edges(n, bc):
         h.close()
 
 
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", SHAPES)
+def test_musta_rhs_at_tile_edges(n, bc):
+    # MUSTA-FORCE: the flux is a Lipschitz function of the two face values where
+    # both are admissible, k = 2 stages of three recoveries each: four times the
+    # bar above.  Fluctuations of 0.03 keep every face value admissible (a
+    # stencil's weights add up to 64/12 in magnitude).  The marching kernels
+    # take one face a time by the same operations: equal bits.
+    w = W.small_event(1, n=n, with_jet=False)
+    rng = np.random.default_rng(sum(n) + 1)
+    shape = (n[2], n[1], n[0])
+    U = np.stack([rng.uniform(2.0, 2.06, shape), *rng.uniform(-0.06, 0.06, (3,) + shape),
+                  rng.uniform(0.5, 0.515, shape)])
+    for precision, weno, u in (("f64", "z", 2.0 ** -53), ("f64", "z5", 2.0 ** -53), ("f32", "z", 2.0 ** -24),
+                               ("f32", "z5", 2.0 ** -24)):
+        V = U.astype(np.float32).astype(np.float64) if precision == "f32" else U
+        pb = O.Problem(n=w.n, bc=(bc,) * 3, weno=weno, flux="musta", musta_k=2)
+        Lo, _, _ = O.rhs(pb, V, 1.0, [])
+        h = H().from_workload(w, precision=precision, weno=weno, bc=(bc,) * 3, flux="musta", musta_k=2)
+        x = torch.from_numpy(V).to("cuda", h.dtype)
+        L = h.rhs(x, 1.0).clone()
+        h.set_option(H().OPT_YZ_KERNEL, 1)
+        M = h.rhs(x, 1.0)
+        assert torch.equal(L, M), (n, bc, precision, weno)
+        bar = 512 * u * np.abs(V).max() * 30.0
+        err = np.abs(L.double().cpu().numpy() - Lo).max()
+        print("musta", n, bc, precision, weno, "max |dL| %.2e bar %.2e" % (err, bar), flush=True)
+        assert err <= bar
+        h.close()
+
+
 @pytest.mark.parametrize("precision", ["f64", "f32"])
 def test_batch_of_mixed_tile_lengths_is_bitwise(precision):
     # tile lengths 31 and 32 in one batch (no common one), persistent and not
