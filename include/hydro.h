@@ -355,14 +355,15 @@ int hydro_init_vjp(hydro_ctx* ctx, const double* prim0, const void* lambda, doub
 typedef enum {
   HYDRO_OPT_YZ_KERNEL = 0,  /* y/z faces: 0 = LDS tiles (default), 1 = register marches */
   HYDRO_OPT_MARCH_SEG = 1,  /* cells per march segment (default 32) */
-  HYDRO_OPT_X_KERNEL = 2,   /* x faces: 0 = one row per workgroup (default), 1 = 32 x 16 LDS tiles */
+  HYDRO_OPT_X_KERNEL = 2,   /* 0 (default) or 1; kept for callers that set it: x faces have one kernel
+                               (LDS tiles), the same results either way */
   HYDRO_OPT_ADJ_SKIP_N = 3, /* 0 (default) or 1, see above */
   HYDRO_OPT_TILE_ORDER = 4, /* order of the y/z LDS tiles' workgroups, 0..3: bit 0 (y tiles), bit 1 (z
                                tiles) set = neighbouring workgroups share the tile index and step the
                                transverse axis, clear = they step along the axis; default 2 */
   HYDRO_OPT_ADJ_LINES = 5   /* lines per workgroup of the y and z line adjoints: 0 = automatic
-                               (default: 2 in FP32, 1 in FP64), 1, 2 or 4; fewer where n_x is not a
-                               multiple or the workgroup would exceed 1024 lanes or 64 KiB of LDS.
+                               (default), 1, 2 or 4: the most lines a workgroup may take; it takes
+                               8 (FP64), 4 or 1, as many as that and 64 KiB of LDS allow.
                                Neighbouring x lines share the workgroup, so their strided loads
                                share cache lines; every line is computed by the same arithmetic
                                (same results) */
@@ -448,18 +449,18 @@ typedef enum {
   HYDRO_BOPT_BLOCKS_Y = 1,
   HYDRO_BOPT_BLOCKS_Z = 2,
   HYDRO_BOPT_GRAPH = 3,     /* 1 (default): replay a captured graph per step; 0: direct launches */
-  HYDRO_BOPT_X_ROWS = 4     /* x faces: 0 (default) = 31/32 x 16 LDS tiles; 1 = groups of whole rows
-                               plus a launch for the outflow x faces */
+  HYDRO_BOPT_X_ROWS = 4     /* 0 (default) or 1; kept for callers that set it: x faces have one
+                               kernel (LDS tiles), the same results either way */
 } hydro_batch_option;
 
 int hydro_batch_set_option(hydro_batch* b, int option, long long value);
 int hydro_batch_get_option(hydro_batch* b, int option, long long* value);
 
-/* Pick the x-face form (tiles or whole rows) and the workgroup count of each
- * axis launch: the candidates 0 (one per work item) and c * (number of CUs),
+/* Pick the workgroup count of each axis launch: the candidates 0 (one per work item) and c * (number of CUs),
  * c in {1, 2, 3, 4, 6, 8}, are timed on this batch (median of 5 launches of
  * the right-hand-side form, no state change) and the fastest kept.
- * cache_path (may be NULL) is a text file of "key bx by bz xrows" lines, the
+ * cache_path (may be NULL) is a text file of "key bx by bz xrows" lines (xrows
+ * 0, older files also 1: HYDRO_BOPT_X_ROWS), the
  * key a hash of the GPU, precision, scheme and the sorted event shapes: a hit
  * skips the timing (*from_cache = 1), a miss appends the picks.
  * Synchronous. */

@@ -55,7 +55,7 @@ struct hydro_ctx {
   int64_t step = 0;
   int seg = 32;      // march segment length
   int yz_tile = 1;   // 1: y/z faces from LDS tiles, 0: register-window marches
-  int x_tile = 0;    // 1: x faces from 32 x 16 LDS tiles, 0: one row per workgroup
+  int x_tile = 0;    // HYDRO_OPT_X_KERNEL as set (x faces have one kernel)
   int adj_skip_n = 0;  // 1: the adjoint sweep takes lambda_N as zero and skips N
   int adj_lines = 0;   // lines per workgroup of the y/z line adjoints (0: automatic)
   int tile_order = 2;  // HYDRO_OPT_TILE_ORDER: z tiles step the transverse axis (measured 6 % faster)
@@ -221,15 +221,11 @@ hipError_t stage_impl(hydro_ctx* ctx, const R* W, const R* Un, R* out, int stage
   hipError_t e;
   {
     ProfScope p(ctx, HYDRO_K_XFACE, st);
-    e = launch_face_kernel<R>(ctx->x_tile ? 6 : 0, a, scheme, ctx->seg, st);
-  }
-  if (e == hipSuccess && c.bc[0] == HYDRO_BC_OUTFLOW && !ctx->x_tile && !line_scheme(scheme)) {
-    ProfScope p(ctx, HYDRO_K_XBOUND, st);
-    e = launch_face_kernel<R>(1, a, scheme, ctx->seg, st);
+    e = launch_face_kernel<R>(0, a, scheme, ctx->seg, st);
   }
   if (e == hipSuccess) {
     ProfScope p(ctx, HYDRO_K_YMARCH, st);
-    e = launch_face_kernel<R>(ctx->yz_tile ? 4 : 2, a, scheme, ctx->seg, st);
+    e = launch_face_kernel<R>(ctx->yz_tile ? 1 : 3, a, scheme, ctx->seg, st);
   }
   if (e == hipSuccess && ctx->njet > 0) {
     JetArgs j;
@@ -249,7 +245,7 @@ hipError_t stage_impl(hydro_ctx* ctx, const R* W, const R* Un, R* out, int stage
   }
   if (e == hipSuccess) {
     ProfScope p(ctx, HYDRO_K_ZMARCH, st);
-    e = launch_face_kernel<R>(ctx->yz_tile ? 5 : 3, a, scheme, ctx->seg, st);
+    e = launch_face_kernel<R>(ctx->yz_tile ? 2 : 4, a, scheme, ctx->seg, st);
   }
   return e;
 }

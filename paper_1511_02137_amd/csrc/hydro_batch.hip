@@ -2,9 +2,8 @@
 // independent events (uneven grids, their own jets) advanced together.
 //
 // Per stage there is one launch per axis whose workgroups walk the work items
-// of every event (x: groups of whole rows, y/z: LDS tiles; a persistent grid
-// of a few workgroups per CU, or one workgroup per item), one launch for the
-// outflow x faces and one for the jets of every event, and per step one FP64
+// of every event (LDS tiles; one workgroup per item, or a persistent grid of a
+// few workgroups per CU), one launch for the jets of every event, and per step one FP64
 // reduction launch and a device step counter (stage times are computed on the
 // device from it).  The launches of one step are captured once into a HIP
 // graph and the graph is replayed for every step.  The grid size of each axis
@@ -35,7 +34,7 @@ struct hydro_batch {
   std::vector<std::vector<hydro_jet>> jets;
   std::vector<BatchEvent> ev;      // host copy of the device table
   BatchEvent* d_ev = nullptr;      // device table [n]
-  long long* d_off = nullptr;      // device item offsets [5][n + 1] (x tiles, y, z, x rows, x boundary)
+  long long* d_off = nullptr;      // device item offsets [3][n + 1] (x, y, z tiles)
   std::vector<long long> off;      // host copy
   DevScalars* d_dev = nullptr;     // per-event device scalars [n]
   double* d_part = nullptr;        // reduction partials [n][kSumBlocks][5]
@@ -44,10 +43,8 @@ struct hydro_batch {
   int cus = 256;
   long long blocks[3] = {0, 0, 0}; // workgroups per axis launch (0: one per item)
   bool picked[3] = {false, false, false};  // blocks[] was set or tuned, not the default
-  int xrows = 0;                   // x pass: 0 LDS tiles, 1 groups of whole rows (+ boundary faces)
+  int xrows = 0;                   // HYDRO_BOPT_X_ROWS as set (the x pass has one kernel)
   int tile_a[3] = {0, 0, 0};       // per axis: the tile length every event shares (31, 32), else 0
-  int xtb = 256;                   // x-row workgroup size (limiter, MUSTA-FORCE)
-  long long xlds = 0;              // dynamic LDS of the x-row launch
   int use_graph = 1;
   hipStream_t cap = nullptr;       // capture stream (never runs work)
   hipGraphExec_t exec = nullptr;
@@ -93,33 +90,23 @@ BatchArgs<R> batch_args(const hydro_batch* b, int AX, int stage) {
   a.n_events = b->n;
   a.stage = stage;
   a.eps = (R)b->cfg[0].weno_eps;
-  a.xtb = b->xtb;
-  a.xlds = b->xlds;
-  a.tile_a = AX <= 2 ? b->tile_a[AX] : 0;
+  a.tile_a = b->tile_a[AX];
   return a;
 }
 
-// Workgroups of an axis launch.  Unless they were set or tuned, plain WENO
-// faces take one item per workgroup: their persistent form has 68 VGPRs (FP32)
-// instead of 44, a workgroup per CU fewer.  16 FP32 events of 64 to 128 cells an
+// Workgroups of an axis launch.  Unless they were set or tuned, one item
+// each: the persistent form has 68 VGPRs (FP32) instead of 44, a workgroup per CU fewer.  16 FP32 events of 64 to 128 cells an
 // edge, us an axis (x, y, z): persistent, two workgroups per CU 462, 510, 550;
 // one item each 371, 374, 395.
 long long axis_blocks(const hydro_batch* b, int AX) {
-  return !b->picked[AX] && line_scheme(face_scheme(b->cfg[0])) ? 0 : b->blocks[AX];
+  return b->picked[AX] ? b->blocks[AX] : 0;
 }
 
-// One stage of every event: x tiles (or x rows and the outflow x faces),
-// y tiles, jets, z tiles (+ RK combine).
+// One stage of every event: x tiles, y tiles, jets, z tiles (+ RK combine).
 template <class R>
 hipError_t stage_launches(hydro_batch* b, int stage, hipStream_t st) {
   const int scheme = face_scheme(b->cfg[0]);
-  hipError_t e;
-  if (b->xrows) {
-    e = launch_batch_axis<R>(3, batch_args<R>(b, 3, stage), scheme, axis_blocks(b, 0), st);
-    if (e == hipSuccess) e = launch_batch_axis<R>(4, batch_args<R>(b, 4, stage), scheme, 0, st);
-  } else {
-    e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, axis_blocks(b, 0), st);
-  }
+  hipError_t e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, axis_blocks(b, 0), st);
   if (e == hipSuccess) e = launch_batch_axis<R>(1, batch_args<R>(b, 1, stage), scheme, axis_blocks(b, 1), st);
   if (e == hipSuccess) e = launch_batch_jet<R>(batch_args<R>(b, 0, stage), st);
   if (e == hipSuccess) e = launch_batch_axis<R>(2, batch_args<R>(b, 2, stage), scheme, axis_blocks(b, 2), st);
@@ -267,18 +254,7 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
     return HYDRO_OK;
   }
   const long long cand[] = {0, 1, 2, 3, 4, 6, 8};
-  // x: LDS tiles (item list 0) or groups of whole rows (3) plus the outflow
-  // faces (4, one workgroup per item, timed once); y and z: tiles (1, 2)
-  const int lists[4] = {0, 3, 1, 2};
-  float xbound = 0.f;
-  {
-    hipError_t e = time_axis<R>(b, 4, 0, 5, st, &xbound);
-    if (e != hipSuccess) return bhip(b, e, "autotune launch");
-  }
-  float tx[2] = {1e30f, 1e30f};
-  long long bx[2] = {0, 0};
-  for (int li = 0; li < 4; ++li) {
-    const int AX = lists[li];
+  for (int AX = 0; AX < 3; ++AX) {
     float tbest = 1e30f;
     long long pick = 0;
     for (long long c : cand) {
@@ -286,23 +262,15 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
       float ms = 0.f;
       hipError_t e = time_axis<R>(b, AX, blocks, 5, st, &ms);
       if (e != hipSuccess) return bhip(b, e, "autotune launch");
-      if (AX == 3) ms += xbound;
       if (ms < tbest) {
         tbest = ms;
         pick = blocks;
       }
     }
-    if (AX == 0 || AX == 3) {
-      tx[AX == 3] = tbest;
-      bx[AX == 3] = pick;
-    } else {
-      b->blocks[AX] = pick;
-      b->picked[AX] = true;
-    }
+    b->blocks[AX] = pick;
+    b->picked[AX] = true;
   }
-  b->xrows = tx[1] < tx[0] ? 1 : 0;
-  b->blocks[0] = bx[b->xrows];
-  b->picked[0] = true;
+  b->xrows = 0;
   cache_store(cache, key, b->blocks, b->xrows);
   if (from_cache) *from_cache = 0;
   drop_graph(b);
@@ -360,7 +328,7 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
     return code;
   };
   hipError_t e = lib_malloc(&b->d_ev, sizeof(BatchEvent) * n_events);
-  if (e == hipSuccess) e = lib_malloc(&b->d_off, sizeof(long long) * 5 * (n_events + 1));
+  if (e == hipSuccess) e = lib_malloc(&b->d_off, sizeof(long long) * 3 * (n_events + 1));
   if (e == hipSuccess) e = lib_malloc(&b->d_dev, sizeof(DevScalars) * n_events);
   if (e == hipSuccess) e = lib_malloc(&b->d_part, sizeof(double) * (size_t)n_events * kSumBlocks * 5);
   if (e == hipSuccess) e = lib_malloc(&b->d_step, sizeof(long long));
@@ -370,21 +338,12 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
 
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   b->ev.resize(n_events);
-  b->off.assign((size_t)5 * (n_events + 1), 0);
-  {
-    std::vector<int> nxs(n_events);
-    for (int i = 0; i < n_events; ++i) nxs[i] = cfgs[i].n[0];
-    const int elem = (int)elem_size(&cfgs[0]);
-    b->xtb = xrow_block(nxs.data(), n_events, elem);
-    for (int AX = 0; AX < 3; ++AX) {
-      int A = tile_len(cfgs[0].n[AX]);
-      for (int i = 1; i < n_events; ++i)
-        if (tile_len(cfgs[i].n[AX]) != A) A = 0;
-      b->tile_a[AX] = A;
-    }
-    b->xlds = 0;
-    for (int i = 0; i < n_events; ++i)
-      b->xlds = std::max<long long>(b->xlds, (long long)xrow_lds_bytes(nxs[i], xrow_rows(nxs[i], b->xtb, elem), elem));
+  b->off.assign((size_t)3 * (n_events + 1), 0);
+  for (int AX = 0; AX < 3; ++AX) {
+    int A = tile_len(cfgs[0].n[AX]);
+    for (int i = 1; i < n_events; ++i)
+      if (tile_len(cfgs[i].n[AX]) != A) A = 0;
+    b->tile_a[AX] = A;
   }
   for (int i = 0; i < n_events; ++i) {
     const hydro_config& c = cfgs[i];
@@ -409,9 +368,8 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
     v.hbarc = c.hbarc;
     v.njet = 0;
     v.deposit = c.deposit;
-    for (int a = 0; a < 5; ++a)
-      b->off[(size_t)a * (n_events + 1) + i + 1] =
-          b->off[(size_t)a * (n_events + 1) + i] + batch_items(a, v.g, face_scheme(c), b->xtb, (int)elem_size(&c));
+    for (int a = 0; a < 3; ++a)
+      b->off[(size_t)a * (n_events + 1) + i + 1] = b->off[(size_t)a * (n_events + 1) + i] + batch_items(a, v.g);
   }
   std::vector<DevScalars> zero(n_events);
   std::memset(zero.data(), 0, sizeof(DevScalars) * n_events);

@@ -152,7 +152,7 @@ template <class R>
 hipError_t launch_batch_jet(const BatchArgs<R>& b, hipStream_t st);
 template <class R>
 hipError_t launch_batch_sums(const BatchArgs<R>& b, long long* step, hipStream_t st);
-long long batch_items(int AX, const Grid& g, int scheme, int xtb, int elem);
+long long batch_items(int AX, const Grid& g);
 template <class R>
 hipError_t launch_freezeout(const FreezeArgs<R>& a, double* spectra, double* harm, int n_harm, hipStream_t st);
 

@@ -8,16 +8,10 @@
 //   combine: Shu-Osher SSP-RK3.
 //
 // Work split (all kernels of a stage run on one stream):
-//   k_line    x, y or z faces of plain WENO and MUSTA-FORCE fluxes from LDS
-//             tiles of 16 lines: one lane per point recovers it, lanes then
-//             march over runs of faces.  x assigns its divergence to D, y adds, z adds its own,
-//             does the RK combine and writes the stage output.
-//   k_xface   x faces with the limiter, one workgroup per group
-//             of whole x-rows: each lane recovers its cell, stores the split
-//             x-fluxes of the row plus 4+4 ghost cells in LDS, takes its left
-//             face and writes the x-divergence;
-//   k_xbound  the right boundary face of those rows (outflow x only);
-//   k_tile    y and z faces with the limiter from LDS tiles.
+//   k_line    x, y or z faces from LDS tiles of 16 lines: one lane per point
+//             recovers it, lanes then march over runs of faces.  x assigns its
+//             divergence to D, y adds, z adds its own, does the RK combine and
+//             writes the stage output.
 //   k_march   lanes along x (coalesced), each lane marches along y or z over
 //             a segment, keeping the split fluxes of the 8-point stencil in
 //             registers: one new cell and one face per step, no halo recompute.
@@ -33,14 +27,6 @@
 
 namespace hydro {
 
-// ---------------------------------------------------------------------------
-// x-faces (limiter): a workgroup owns rpi = blockDim / nx whole
-// rows (row0, row0 + 1, ...; fewer at the end of the grid).  LDS per row: the
-// split fluxes of its nx cells and 8 ghost slots (slot j holds padded position
-// j - 4), then the face values.  One lane per cell: it recovers its cell,
-// stores the split fluxes (also into every ghost slot that copies the cell),
-// reconstructs the cell's left face and forms the divergence; the outflow
-// right face of the last cell is added by k_xbound.
 // What the face kernels keep per point: twice the Lax-Friedrichs split fluxes
 // (F+, F-; face_scale sets what that changes), or with MUSTA-FORCE the
 // conserved values themselves (in the F+ slots; no recovery needed).
@@ -94,171 +80,6 @@ __device__ __forceinline__ R rk_out_v(int stage, R p, R dz, R dt, R un) {
   if (stage == 1) return v;
   if (stage == 2) return R(0.75) * un + R(0.25) * v;
   return R(1.0 / 3.0) * un + R(2.0 / 3.0) * v;
-}
-
-template <class R, int S>
-__device__ __forceinline__ void xrows_body(const StageArgs<R>& a, long long row0, int rpi, R* s) {
-  const int nx = a.g.n[0];
-  const int P = nx + 8;
-  const long long rows = (long long)a.g.n[1] * a.g.n[2];
-  const long long nc = a.g.nc;
-  const int r = threadIdx.x / nx;
-  const int x = threadIdx.x - r * nx;
-  const long long row = row0 + r;
-  const bool act = r < rpi && row < rows;
-  const long long rowbase = row * nx;
-  R* sFp = s + (size_t)r * 10 * P;
-  R* sFm = sFp + 5 * P;
-  unsigned fix = 0;
-  if (act) {
-    R u[5];
-    load5(a.W, nc, rowbase + x, u);
-    R Fp[5], Fm[5];
-    point_values<R, S, 0>(u, Fp, Fm, fix);
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      sFp[c * P + x + 4] = Fp[c];
-      sFm[c * P + x + 4] = Fm[c];
-    }
-    // ghost slots 0..3 and nx+4..nx+7, each filled by the lane whose cell it
-    // copies: outflow, the edge lanes; periodic, the lanes four from the far
-    // end (rows of at least 8 cells; shorter rows take the general map)
-    auto put = [&](int j) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sFp[c * P + j] = Fp[c];
-        sFm[c * P + j] = Fm[c];
-      }
-    };
-    if (nx >= 8) {
-      if (a.g.bc[0]) {
-        if (x >= nx - 4) put(x - nx + 4);
-        if (x < 4) put(nx + 4 + x);
-      } else if (x == 0 || x == nx - 1) {
-        const int j0 = x == 0 ? 0 : nx + 4;
-        for (int k = 0; k < 4; ++k) put(j0 + k);
-      }
-    } else {
-      for (int g = 0; g < 8; ++g) {
-        const int j = g < 4 ? g : nx + g;
-        if (map_idx(j - 4, nx, a.g.bc[0]) == x) put(j);
-      }
-    }
-  }
-  __syncthreads();
-
-  R Fh[5];
-  if (act) {
-    // face x - 1/2: F+ at x-4..x+2 (slots x..x+6), F- at x-3..x+3 (slots x+1..x+7)
-#pragma unroll
-    for (int c = 0; c < 5; ++c)
-      Fh[c] = face_flux<R, (S & 7)>(sFp + c * P + x, sFm + c * P + x, a.eps);
-    if constexpr ((S & kPP) != 0) {  // cells x - 1 and x: slots x + 3 and x + 4
-      pp_limit<R>(
-          Fh, [&](int c, int k) { return ((k & 1) ? sFm : sFp)[c * P + x + 3 + (k >> 1)]; }, a.pp_mu);
-    }
-  }
-  __syncthreads();
-  R* sF = s + (size_t)r * 5 * nx;  // [5][nx] per row
-  if (act) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sF[c * nx + x] = Fh[c];
-  }
-  __syncthreads();
-  if (act) {
-    const bool last = (x + 1 == nx);
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R l = sF[c * nx + x];
-      R* d = a.D + c * nc + rowbase + x;
-      if (!last) {
-        *d = (l - sF[c * nx + x + 1]) * a.inv_d;
-      } else if (a.g.bc[0]) {
-        *d = (l - sF[c * nx]) * a.inv_d;  // periodic: the right face is face -1/2
-      } else {
-        *d = l;  // finished by k_xbound
-      }
-    }
-  }
-  add_fixups(a.fixups, fix);
-}
-
-template <class R, int S, int TB>
-__global__ void __launch_bounds__(TB) k_xface(StageArgs<R> a, int rpi) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  xrows_body<R, S>(a, (long long)blockIdx.x * rpi, rpi, reinterpret_cast<R*>(smem_raw));
-}
-
-// Right boundary face of every row (outflow x): points nx-4..nx+3 (the last
-// four copies of cell nx-1).  A workgroup takes 32 rows: one lane per (row,
-// point) forms the split fluxes, one lane per (row, field, split) does one
-// reconstruction, one lane per (row, field) adds R+ + R- to finish D.
-constexpr int kXBoundRows = 32;
-
-template <class R, int S>
-__device__ __forceinline__ void xbound_body(const StageArgs<R>& a, long long group) {
-  __shared__ R sF[kXBoundRows][8][10];
-  __shared__ R sR[kXBoundRows][10];
-  const int nx = a.g.n[0];
-  const long long rows = (long long)a.g.n[1] * a.g.n[2];
-  const long long nc = a.g.nc;
-  const int t = threadIdx.x;
-  unsigned fix = 0;
-  if (t < kXBoundRows * 8) {
-    const int l = t >> 3, m = t & 7;
-    const long long row = group * kXBoundRows + l;
-    if (row < rows) {
-      R u[5];
-      load5(a.W, nc, row * nx + map_idx(nx - 4 + m, nx, 0), u);
-      R Fp[5], Fm[5];
-      point_values<R, S, 0>(u, Fp, Fm, fix);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sF[l][m][c] = Fp[c];
-        sF[l][m][5 + c] = Fm[c];
-      }
-    }
-  }
-  __syncthreads();
-  {
-    const int l = t / 10, r = t % 10, c = r >> 1;
-    const long long row = group * kXBoundRows + l;
-    if (row < rows) {
-      sR[l][r] = (r & 1) == 0
-                     ? weno7<R, (S & 7)>(sF[l][0][c], sF[l][1][c], sF[l][2][c], sF[l][3][c], sF[l][4][c], sF[l][5][c],
-                                   sF[l][6][c], a.eps)
-                     : weno7<R, (S & 7)>(sF[l][7][5 + c], sF[l][6][5 + c], sF[l][5][5 + c], sF[l][4][5 + c],
-                                   sF[l][3][5 + c], sF[l][2][5 + c], sF[l][1][5 + c], a.eps);
-    }
-  }
-  __syncthreads();
-  if constexpr ((S & kPP) != 0) {  // one lane per row: cell nx-1 (point 3) and its copy (point 4)
-    if (t < kXBoundRows && group * kXBoundRows + t < rows) {
-      const int l = t;
-      R H[5];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) H[c] = sR[l][2 * c] + sR[l][2 * c + 1];
-      pp_limit<R>(H, [&](int c, int k) { return sF[l][3 + (k >> 1)][(k & 1) * 5 + c]; }, a.pp_mu);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) sF[l][0][c] = H[c];  // point 0 is no longer read
-    }
-    __syncthreads();
-  }
-  if (t < kXBoundRows * 5) {
-    const int l = t / 5, c = t % 5;
-    const long long row = group * kXBoundRows + l;
-    if (row < rows) {
-      const R r = ((S & kPP) != 0) ? sF[l][0][c] : sR[l][2 * c] + sR[l][2 * c + 1];
-      R* d = a.D + c * nc + row * nx + nx - 1;
-      *d = (*d - r) * a.inv_d;
-    }
-  }
-  add_fixups(a.fixups, fix);
-}
-
-template <class R, int S>
-__global__ void __launch_bounds__(kXBoundRows * 10) k_xbound(StageArgs<R> a) {
-  xbound_body<R, S>(a, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -352,179 +173,8 @@ __global__ void __launch_bounds__(256) k_march(StageArgs<R> a) {
 }
 
 // ---------------------------------------------------------------------------
-// y- or z-faces from an LDS tile (AX = 1 or 2; limiter).  A workgroup of 512 lanes
-// owns 16 cells along x (coalesced 128-byte rows) by 31 cells along AX at one
-// value of the remaining axis, so that its 32 face rows are exactly one face
-// per lane.  It stores the split AX-fluxes of its 16 x 39 points (4 ghost rows on each side) in LDS,
-// reconstructs the face rows and forms the divergence; each lane's D is
-// loaded before the reconstructions to hide its latency.
-// LAST (z): adds D, does the RK combine (rk_pre, rk_out) and writes the
-// stage output.
-constexpr int kTileX = 16;
-constexpr int kTileXP = kTileX;      // x pitch of the LDS arrays (128-byte rows)
-
-// Tile length along the axis: 31 cells (32 face rows, one face per lane)
-// or 32 cells (33 face rows, the last one by 16 lanes); the launchers pick
-// the one that wastes less for the axis length (tile_len).
-// The limiter on an LDS tile laid out [c][slot][pitch]: face row f lies
-// between the points in slots f + 3 and f + 4, column col.
-template <class R, int kP, int kPitch>
-__device__ __forceinline__ void tile_limit(R H[5], const R* sFp, const R* sFm, int f, int col, double mu) {
-  pp_limit<R>(
-      H, [&](int c, int k) { return ((k & 1) ? sFm : sFp)[(c * kP + f + 3 + (k >> 1)) * kPitch + col]; }, mu);
-}
-
-template <class R, int S, int AX, bool LAST, int kTileA>
-__device__ __forceinline__ void tile_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
-  constexpr int kTileP = kTileA + 8;  // points along AX
-  R* sFp = s;                              // [5][kTileP][kTileXP]
-  R* sFm = s + 5 * kTileP * kTileXP;       // [5][kTileP][kTileXP]
-  const int nx = a.g.n[0], ny = a.g.n[1];
-  const int n = a.g.n[AX];
-  const int bc = a.g.bc[AX];
-  const long long nc = a.g.nc;
-  const int tx = threadIdx.x & (kTileX - 1);
-  const int ta = threadIdx.x >> 4;  // 0..31: own cell a0 + ta (ta < kTileA), face row ta
-  const int x = bx * kTileX + tx;
-  const int a0 = by * kTileA;
-  const int o = bz;
-  const long long stride = (AX == 1) ? (long long)nx : (long long)nx * ny;
-  const long long base = (AX == 1) ? (long long)o * nx * ny + x : (long long)o * nx + x;
-  const bool xin = x < nx;
-  unsigned fix = 0;
-
-  const int ac = a0 + ta;
-  const bool own_ok = xin && ta < kTileA && ac < n;
-  const long long cell = base + (long long)ac * stride;
-  // dpre: the own cell's D, loaded early so that its latency overlaps the
-  // ghost rows and the reconstructions; LAST: loaded with the cell's W and
-  // folded into the combine's p = w + dt D at once (rk_pre), so W need not
-  // stay in registers
-  R dpre[5];
-  // pass 1: own cell (slot ta + 4)
-  {
-    const int p = a0 + ta;
-    if (xin && ta < kTileA) {
-      R own[5];
-      load5(a.W, nc, base + (long long)map_idx(p, n, bc) * stride, own);
-      if (LAST && own_ok) {
-#pragma unroll
-        for (int c = 0; c < 5; ++c) dpre[c] = a.D[c * nc + cell];
-      }
-      R Fp[5], Fm[5];
-      point_values<R, S, AX>(own, Fp, Fm, fix);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sFp[(c * kTileP + ta + 4) * kTileXP + tx] = Fp[c];
-        sFm[(c * kTileP + ta + 4) * kTileXP + tx] = Fm[c];
-      }
-      if (LAST && own_ok) {
-#pragma unroll
-        for (int c = 0; c < 5; ++c) dpre[c] = rk_pre(a.stage, own[c], dpre[c], a.dt);
-      }
-    }
-  }
-  if (!LAST && own_ok) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) dpre[c] = a.D[c * nc + cell];
-  }
-  // pass 2: 4 ghost rows on each side (128 lanes)
-  if (threadIdx.x < 8 * kTileX) {
-    const int h = ta;  // 0..7
-    const int j = (h < 4) ? h : h + kTileA;
-    const int p = a0 - 4 + j;
-    if (xin) {
-      R u[5];
-      load5(a.W, nc, base + (long long)map_idx(p, n, bc) * stride, u);
-      R Fp[5], Fm[5];
-      point_values<R, S, AX>(u, Fp, Fm, fix);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sFp[(c * kTileP + j) * kTileXP + tx] = Fp[c];
-        sFm[(c * kTileP + j) * kTileXP + tx] = Fm[c];
-      }
-    }
-  }
-  __syncthreads();
-
-  // face rows f = 0..kTileA: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, F- at f+1..f+7
-  const int nf = min(kTileA, n - a0) + 1;  // face rows this tile needs
-  R Fh[5], Fh2[5];
-  const bool has1 = xin && ta < nf;
-  const bool has2 = (kTileA + 1) * kTileX > 512 && xin && threadIdx.x < kTileX && kTileA < nf;
-  if (has1) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R* fp = sFp + (c * kTileP + ta) * kTileXP + tx;
-      const R* fm = sFm + (c * kTileP + ta) * kTileXP + tx;
-      Fh[c] = weno7<R, (S & 7)>(fp[0], fp[kTileXP], fp[2 * kTileXP], fp[3 * kTileXP], fp[4 * kTileXP], fp[5 * kTileXP],
-                          fp[6 * kTileXP], a.eps) +
-              weno7<R, (S & 7)>(fm[7 * kTileXP], fm[6 * kTileXP], fm[5 * kTileXP], fm[4 * kTileXP], fm[3 * kTileXP],
-                          fm[2 * kTileXP], fm[kTileXP], a.eps);
-    }
-  }
-  if (has2) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R* fp = sFp + (c * kTileP + kTileA) * kTileXP + tx;
-      const R* fm = sFm + (c * kTileP + kTileA) * kTileXP + tx;
-      Fh2[c] = weno7<R, (S & 7)>(fp[0], fp[kTileXP], fp[2 * kTileXP], fp[3 * kTileXP], fp[4 * kTileXP], fp[5 * kTileXP],
-                           fp[6 * kTileXP], a.eps) +
-               weno7<R, (S & 7)>(fm[7 * kTileXP], fm[6 * kTileXP], fm[5 * kTileXP], fm[4 * kTileXP], fm[3 * kTileXP],
-                           fm[2 * kTileXP], fm[kTileXP], a.eps);
-    }
-  }
-  if constexpr ((S & kPP) != 0) {  // face row f: cells at slots f + 3 and f + 4
-    if (has1) tile_limit<R, kTileP, kTileXP>(Fh, sFp, sFm, ta, tx, a.pp_mu);
-    if (has2) tile_limit<R, kTileP, kTileXP>(Fh2, sFp, sFm, kTileA, tx, a.pp_mu);
-  }
-  __syncthreads();
-  R* sF = s;  // [5][kTileA + 1][kTileXP]
-  if (has1) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sF[(c * (kTileA + 1) + ta) * kTileXP + tx] = Fh[c];
-  }
-  if (has2) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sF[(c * (kTileA + 1) + kTileA) * kTileXP + tx] = Fh2[c];
-  }
-  __syncthreads();
-
-  if (own_ok) {
-    // LAST, stages 2 and 3: the five U^n values are read before any output
-    // is stored (out may be U^n itself, so the compiler would otherwise keep
-    // each read behind the previous field's store: five round trips)
-    R unv[5];
-    if (LAST && a.stage >= 2) {
-#pragma unroll
-      for (int c = 0; c < 5; ++c) unv[c] = a.Un[c * nc + cell];
-    }
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const int i0 = (c * (kTileA + 1) + ta) * kTileXP + tx;
-      const R div = (sF[i0] - sF[i0 + kTileXP]) * a.inv_d;
-      if (!LAST) {
-        a.D[c * nc + cell] = dpre[c] + div;
-      } else {
-        a.out[c * nc + cell] = rk_out_v(a.stage, dpre[c], div, a.dt, unv[c]);
-      }
-    }
-  }
-  add_fixups(a.fixups, fix);
-}
-
-
-template <class R, int S, int AX, bool LAST, int A>
-__global__ void __launch_bounds__(512) k_tile(StageArgs<R> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int by = a.order ? blockIdx.z : blockIdx.y;  // tile along AX
-  const int bz = a.order ? blockIdx.y : blockIdx.z;  // transverse index
-  tile_body<R, S, AX, LAST, A>(a, blockIdx.x, by, bz, reinterpret_cast<R*>(smem_raw));
-}
-
-// ---------------------------------------------------------------------------
-// Faces taken along lines (plain WENO fluxes, and below MUSTA-FORCE; the limiter
-// uses the bodies above).  A lane marches over neighbouring faces of one split of
+// Faces taken along lines (plain WENO fluxes; MUSTA-FORCE and the limiter have
+// their own sharing out, in line_body).  A lane marches over neighbouring faces of one split of
 // one field of its line, so that the differences and their indicator terms of
 // a point serve every face of the run (weno_line).  A workgroup has eight
 // waves, which the hardware deals evenly over the four SIMDs; the ten (field,
@@ -574,7 +224,7 @@ constexpr int kLineRun = 8;
 
 template <class R, int S, int AX, bool LAST, int A>
 __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
-  constexpr bool kM = (S & kMusta) != 0;
+  constexpr bool kM = (S & kMusta) != 0, kL = (S & kPP) != 0;
   constexpr int kP = A + 8;  // points of a line
   constexpr int kRow = AX == 0 ? kLineX + 1 : kLineX;
   constexpr int kArea = kP * kRow;  // one (field, split): area 2 field + split
@@ -700,6 +350,56 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
     if (line_in && qn <= len) flux(qn);
     if (A == 32 && t < kLineX && line_in && len == 32) flux(32);
     __syncthreads();
+  } else if constexpr (kL) {
+    // Limiter: it reads the split fluxes of the two cells next to a face, so
+    // the points stay and the face fluxes get rows of their own.  Waves 2c and
+    // 2c + 1 march over rows 0..15 and 16..31 of field c = 0..3, F+ and then F-
+    // (its run starts at the last face); every lane takes one face of N, and
+    // the first lanes row 32.  The rows of their own bring the tile to 72 KB in
+    // FP64, two workgroups a CU, which its registers (82) allow as well: 4 waves
+    // a SIMD still issue at the peak rate.  Against tiles of whole faces per
+    // lane, us a step without jets: FP64 128^3 989 -> 815, 31^3 99 -> 85; FP32
+    // 128^3 623 -> 515; batches of 16 x 64^3 2542 -> 1732 (FP64), 1644 -> 1017.
+    const int c4 = w >> 1, q4 = (w & 1) * 16 + grp * 4, qn = t >> 4;
+    auto rowp = [&](int c, int q) { return s + 2 * c * kArea + q * kRow + xl; };
+    auto rowm = [&](int c, int q) { return s + (2 * c + 1) * kArea + (A - q) * kRow + xl; };
+    auto flux = [&](int c, int q) { return s + 10 * kArea + (c * (A + 1) + q) * kRow + xl; };
+    R fr[4];
+    const R* vp = rowp(c4, q4);
+    weno_line<R, (S & 7), 4>([&](int m) { return vp[m * kRow]; }, a.eps, [&](int k, R v) { fr[k] = v; });
+    const R* vm = rowm(c4, q4 + 3);
+    weno_line<R, (S & 7), 4>([&](int m) { return vm[m * kRow]; }, a.eps, [&](int k, R v) { fr[3 - k] = fr[3 - k] + v; });
+    R* d = flux(c4, q4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d[k * kRow] = fr[k];
+    auto one = [&](int c, int q) {
+      R f = R(0);
+      const R* p = rowp(c, q);
+      weno_line<R, (S & 7), 1>([&](int m) { return p[m * kRow]; }, a.eps, [&](int, R v) { f = v; });
+      const R* m0 = rowm(c, q);
+      weno_line<R, (S & 7), 1>([&](int m) { return m0[m * kRow]; }, a.eps, [&](int, R v) { f = f + v; });
+      *flux(c, q) = f;
+    };
+    one(4, qn);
+    if (A == 32 && t < 80) one(t >> 4, 32);
+    __syncthreads();
+    // one lane per face, as above
+    auto limit = [&](int q) {
+      R H[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) H[c] = *flux(c, q);
+      const R* p = rowp(0, q + 3);
+      const R* m = rowm(0, q - 4);
+      pp_limit<R>(
+          H, [&](int c, int k) { return (k & 1) ? m[2 * c * kArea - (k >> 1) * kRow] : p[2 * c * kArea + (k >> 1) * kRow]; },
+          a.pp_mu);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) *flux(c, q) = H[c];
+    };
+    const bool line_in = bx * kLineX + xl < no;
+    if (line_in && qn <= len) limit(qn);
+    if (A == 32 && t < kLineX && line_in && len == 32) limit(32);
+    __syncthreads();
   } else {
     // face row f: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, its result in
     // row f; F- at slots f+7..f+1, stored from row A - f on, its result there
@@ -734,12 +434,13 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
       for (int c = 0; c < 5; ++c) unv[c] = a.Un[c * nc + cell];
     }
-    const R* sp = s + ta * kRow + tx;
+    const R* sp = s + (kL ? 10 * kArea : 0) + ta * kRow + tx;
     const R* sm = s + kArea + (A - 1 - ta) * kRow + tx;  // F- of the right face; the left face's follows
+    constexpr int kStep = kL ? (A + 1) * kRow : 2 * kArea;
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-      const R fl = kM ? sp[2 * c * kArea] : sp[2 * c * kArea] + sm[2 * c * kArea + kRow];
-      const R fr = kM ? sp[2 * c * kArea + kRow] : sp[2 * c * kArea + kRow] + sm[2 * c * kArea];
+      const R fl = kM || kL ? sp[c * kStep] : sp[c * kStep] + sm[c * kStep + kRow];
+      const R fr = kM || kL ? sp[c * kStep + kRow] : sp[c * kStep + kRow] + sm[c * kStep];
       const R div = (fl - fr) * a.inv_d;
       if (AX == 0) {
         a.D[c * nc + cell] = div;
@@ -754,7 +455,7 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 }
 
 template <class R, int S, int AX, bool LAST, int A>
-__global__ void __launch_bounds__(kLineBlock, (S & kMusta) ? 4 : 6) k_line(StageArgs<R> a) {
+__global__ void __launch_bounds__(kLineBlock, (S & (kMusta | kPP)) ? 4 : 6) k_line(StageArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   // blockIdx.x: 16 lines; tile along AX and transverse index in either order
   unsigned b0 = blockIdx.x, b1 = blockIdx.y;
@@ -769,111 +470,6 @@ __global__ void __launch_bounds__(kLineBlock, (S & kMusta) ? 4 : 6) k_line(Stage
   const int by = a.order ? blockIdx.z : b1;
   const int bz = a.order ? b1 : blockIdx.z;
   line_body<R, S, AX, LAST, A>(a, b0, by, bz, reinterpret_cast<R*>(smem_raw));
-}
-
-// ---------------------------------------------------------------------------
-// x-faces from an LDS tile: a workgroup of 512 lanes owns 31 or 32 cells
-// along x (tile_len) by 16 rows along y at one z.  The (A + 8) x 16 points
-// (4 ghosts on each side) are loaded x-fastest (coalesced) and their split
-// x-fluxes stored [c][x][y], so a face lane (y fastest) reads them without
-// bank conflicts; the A + 1 face rows are reconstructed (one face per lane;
-// for A = 32 one extra row by 16 lanes) and the divergence is formed with
-// lanes x-fastest again and assigned to D (x is the first axis).  Same
-// per-face arithmetic as k_xface + k_xbound.
-constexpr int kXTileY = 16;
-constexpr int kXFacePitch = kXTileY + 1;
-
-template <class R, int S, int kXTileX>
-__device__ __forceinline__ void xtile_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
-  constexpr int kXTileP = kXTileX + 8;
-  R* sFp = s;                                // [5][kXTileP][kXTileY]
-  R* sFm = s + 5 * kXTileP * kXTileY;        // [5][kXTileP][kXTileY]
-  const int nx = a.g.n[0], ny = a.g.n[1];
-  const int bc = a.g.bc[0];
-  const long long nc = a.g.nc;
-  const int x0 = bx * kXTileX, y0 = by * kXTileY;
-  const long long zbase = (long long)bz * nx * ny;
-  unsigned fix = 0;
-  for (int t = threadIdx.x; t < kXTileP * kXTileY; t += 512) {
-    const int j = t % kXTileP, r = t / kXTileP;
-    const int y = y0 + r;
-    if (y < ny) {
-      R u[5];
-      load5(a.W, nc, zbase + (long long)y * nx + map_idx(x0 - 4 + j, nx, bc), u);
-      R Fp[5], Fm[5];
-      point_values<R, S, 0>(u, Fp, Fm, fix);
-#pragma unroll
-      for (int c = 0; c < 5; ++c) {
-        sFp[(c * kXTileP + j) * kXTileY + r] = Fp[c];
-        sFm[(c * kXTileP + j) * kXTileY + r] = Fm[c];
-      }
-    }
-  }
-  __syncthreads();
-
-  // faces f = 0..32: face (x0 - 1 + f) + 1/2; F+ at slots f..f+6, F- at f+1..f+7
-  const int r = threadIdx.x & (kXTileY - 1);
-  const int f = threadIdx.x >> 4;  // 0..31: face row f
-  const int nf = min(kXTileX, nx - x0) + 1;
-  const bool yin = y0 + r < ny;
-  const bool has1 = yin && f < nf;
-  const bool has2 = (kXTileX + 1) * kXTileY > 512 && yin && threadIdx.x < kXTileY && kXTileX < nf;
-  R Fh[5], Fh2[5];
-  if (has1) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R* fp = sFp + (c * kXTileP + f) * kXTileY + r;
-      const R* fm = sFm + (c * kXTileP + f) * kXTileY + r;
-      Fh[c] = weno7<R, (S & 7)>(fp[0], fp[kXTileY], fp[2 * kXTileY], fp[3 * kXTileY], fp[4 * kXTileY], fp[5 * kXTileY],
-                          fp[6 * kXTileY], a.eps) +
-              weno7<R, (S & 7)>(fm[7 * kXTileY], fm[6 * kXTileY], fm[5 * kXTileY], fm[4 * kXTileY], fm[3 * kXTileY],
-                          fm[2 * kXTileY], fm[kXTileY], a.eps);
-    }
-  }
-  if (has2) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R* fp = sFp + (c * kXTileP + kXTileX) * kXTileY + r;
-      const R* fm = sFm + (c * kXTileP + kXTileX) * kXTileY + r;
-      Fh2[c] = weno7<R, (S & 7)>(fp[0], fp[kXTileY], fp[2 * kXTileY], fp[3 * kXTileY], fp[4 * kXTileY], fp[5 * kXTileY],
-                           fp[6 * kXTileY], a.eps) +
-               weno7<R, (S & 7)>(fm[7 * kXTileY], fm[6 * kXTileY], fm[5 * kXTileY], fm[4 * kXTileY], fm[3 * kXTileY],
-                           fm[2 * kXTileY], fm[kXTileY], a.eps);
-    }
-  }
-  if constexpr ((S & kPP) != 0) {  // face row f: cells at slots f + 3 and f + 4
-    if (has1) tile_limit<R, kXTileP, kXTileY>(Fh, sFp, sFm, f, r, a.pp_mu);
-    if (has2) tile_limit<R, kXTileP, kXTileY>(Fh2, sFp, sFm, kXTileX, r, a.pp_mu);
-  }
-  __syncthreads();
-  R* sF = s;  // [5][kXTileX + 1][kXFacePitch]
-  if (has1) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sF[(c * (kXTileX + 1) + f) * kXFacePitch + r] = Fh[c];
-  }
-  if (has2) {
-#pragma unroll
-    for (int c = 0; c < 5; ++c) sF[(c * (kXTileX + 1) + kXTileX) * kXFacePitch + r] = Fh2[c];
-  }
-  __syncthreads();
-
-  const int xa = threadIdx.x & 31, ra = threadIdx.x >> 5;
-  if (xa < kXTileX && x0 + xa < nx && y0 + ra < ny) {
-    const long long cell = zbase + (long long)(y0 + ra) * nx + x0 + xa;
-#pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      const R l = sF[(c * (kXTileX + 1) + xa) * kXFacePitch + ra];
-      const R rr = sF[(c * (kXTileX + 1) + xa + 1) * kXFacePitch + ra];
-      a.D[c * nc + cell] = (l - rr) * a.inv_d;
-    }
-  }
-  add_fixups(a.fixups, fix);
-}
-
-template <class R, int S, int A>
-__global__ void __launch_bounds__(512) k_xtile(StageArgs<R> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  xtile_body<R, S, A>(a, blockIdx.x, blockIdx.y, blockIdx.z, reinterpret_cast<R*>(smem_raw));
 }
 
 // ---------------------------------------------------------------------------
@@ -1187,69 +783,9 @@ __device__ __forceinline__ double batch_stage_time(const BatchEvent& ev, long lo
   return tn + c * ev.dt;
 }
 
-// x, y or z tiles of every event (xtile_body, tile_body).
-template <class R, int S, int AX>
-__global__ void __launch_bounds__(512) k_btile(BatchArgs<R> b) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  R* s = reinterpret_cast<R*>(smem_raw);
-  for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
-    const int e = batch_event_of(b.off, b.n_events, it);
-    const BatchEvent& ev = b.ev[e];
-    const long long local = it - b.off[e];
-    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
-    const int A = tile_len(ev.g.n[AX]);
-    if (AX == 0) {
-      const int gx = (ev.g.n[0] + A - 1) / A, gy = (ev.g.n[1] + kXTileY - 1) / kXTileY;
-      const int bx = (int)(local % gx), by = (int)((local / gx) % gy), bz = (int)(local / ((long long)gx * gy));
-      if (A == 31) xtile_body<R, S, 31>(a, bx, by, bz, s);
-      else xtile_body<R, S, 32>(a, bx, by, bz, s);
-    } else {
-      const int gx = (ev.g.n[0] + kTileX - 1) / kTileX, ga = (ev.g.n[AX] + A - 1) / A;
-      const int bx = (int)(local % gx), by = (int)((local / gx) % ga), bz = (int)(local / ((long long)gx * ga));
-      if (A == 31) tile_body<R, S, AX, AX == 2, 31>(a, bx, by, bz, s);
-      else tile_body<R, S, AX, AX == 2, 32>(a, bx, by, bz, s);
-    }
-    __syncthreads();  // the next item overwrites the LDS tile
-  }
-}
-
-// The same when every event has the tile length A along the axis (the
-// launcher checks): one tile body instead of two.  PERSIST: workgroups walk
-// items blockIdx.x, blockIdx.x + gridDim.x, ...; otherwise one item per
-// workgroup (the loop's live state costs ~20 VGPRs, a workgroup per CU).
-template <class R, int S, int AX, int A>
-__device__ __forceinline__ void btile_item(const BatchArgs<R>& b, long long it, R* s) {
-  const int e = batch_event_of(b.off, b.n_events, it);
-  const BatchEvent& ev = b.ev[e];
-  const long long local = it - b.off[e];
-  const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
-  if (AX == 0) {
-    const int gx = (ev.g.n[0] + A - 1) / A, gy = (ev.g.n[1] + kXTileY - 1) / kXTileY;
-    const int bx = (int)(local % gx), by = (int)((local / gx) % gy), bz = (int)(local / ((long long)gx * gy));
-    xtile_body<R, S, A>(a, bx, by, bz, s);
-  } else {
-    const int gx = (ev.g.n[0] + kTileX - 1) / kTileX, ga = (ev.g.n[AX] + A - 1) / A;
-    const int bx = (int)(local % gx), by = (int)((local / gx) % ga), bz = (int)(local / ((long long)gx * ga));
-    tile_body<R, S, AX, AX == 2, A>(a, bx, by, bz, s);
-  }
-}
-
-template <class R, int S, int AX, int A, bool PERSIST>
-__global__ void __launch_bounds__(512) k_btile_u(BatchArgs<R> b) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  R* s = reinterpret_cast<R*>(smem_raw);
-  if constexpr (PERSIST) {
-    for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
-      btile_item<R, S, AX, A>(b, it, s);
-      __syncthreads();  // the next item overwrites the LDS tile
-    }
-  } else {
-    if ((long long)blockIdx.x < b.items) btile_item<R, S, AX, A>(b, blockIdx.x, s);  // uniform
-  }
-}
-
-// Plain WENO faces: line tiles of every event (line_body; tile length 31 or
-// 32 by event).  PERSIST as above.
+// Line tiles of every event (line_body; tile length 31 or 32 by event).  PERSIST:
+// workgroups walk items blockIdx.x, blockIdx.x + gridDim.x, ...; otherwise one
+// item per workgroup (the loop's live state costs ~20 VGPRs, a workgroup per CU).
 template <class R, int S, int AX, int A>
 __device__ __forceinline__ void bline_item(const BatchArgs<R>& b, const BatchEvent& ev, long long local, R* s) {
   const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
@@ -1289,35 +825,6 @@ __global__ void __launch_bounds__(kLineBlock) k_bline(BatchArgs<R> b) {
   }
 }
 
-// x rows of every event: items are groups of TB / nx rows (xrows_body).
-template <class R, int S, int TB>
-__global__ void __launch_bounds__(TB) k_bxrows(BatchArgs<R> b) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  R* s = reinterpret_cast<R*>(smem_raw);
-  for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
-    const int e = batch_event_of(b.off, b.n_events, it);
-    const BatchEvent& ev = b.ev[e];
-    const int rpi = xrow_rows(ev.g.n[0], TB, (int)sizeof(R));
-    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, 0);
-    xrows_body<R, S>(a, (it - b.off[e]) * rpi, rpi, s);
-    __syncthreads();  // the next item overwrites the LDS rows
-  }
-}
-
-// Outflow right x-face of every event with outflow x: items are groups of
-// kXBoundRows rows (xbound_body).
-template <class R, int S>
-__global__ void __launch_bounds__(kXBoundRows * 10) k_bxbound(BatchArgs<R> b) {
-  for (long long it = blockIdx.x; it < b.items; it += gridDim.x) {
-    const int e = batch_event_of(b.off, b.n_events, it);
-    const BatchEvent& ev = b.ev[e];
-    const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, 0);
-    xbound_body<R, S>(a, it - b.off[e]);
-    __syncthreads();
-  }
-}
-
-// Jets of every event: one workgroup per event.
 template <class R>
 __global__ void __launch_bounds__(512) k_bjet(BatchArgs<R> b) {
   const BatchEvent& ev = b.ev[blockIdx.x];
@@ -1375,37 +882,9 @@ void launch_line_t(const StageArgs<R>& base, hipStream_t st) {
   // 1 % slower; FP64 z 709 -> 726)
   const bool xcd = sizeof(R) == 4 && AX == 2 && grid.x > 1 && (unsigned long long)grid.x * grid.x * grid.y < 0xffffffffULL;
   a.seg = xcd ? (int)((0x100000000ULL + grid.x - 1) / grid.x) : 0;
-  const size_t lds = line_lds_bytes(AX, A, (int)sizeof(R));
+  const size_t lds = line_lds_bytes(AX, A, S, (int)sizeof(R));
   if (A == 31) hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 31>), grid, dim3(kLineBlock), lds, st, a);
   else hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 32>), grid, dim3(kLineBlock), lds, st, a);
-}
-
-template <class R, int S>
-void launch_xface_t(const StageArgs<R>& base, hipStream_t st) {
-  StageArgs<R> a = base;
-  const int nx = a.g.n[0];
-  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
-  const int n1 = nx;
-  const int TB = xrow_block(&n1, 1, (int)sizeof(R));
-  const int rpi = xrow_rows(nx, TB, (int)sizeof(R));
-  const size_t lds = xrow_lds_bytes(nx, rpi, (int)sizeof(R));
-  const long long rows = (long long)a.g.n[1] * a.g.n[2];
-  const unsigned nb = (unsigned)((rows + rpi - 1) / rpi);
-  switch (TB) {
-    case 256: hipLaunchKernelGGL((k_xface<R, S, 256>), dim3(nb), dim3(256), lds, st, a, rpi); break;
-    case 384: hipLaunchKernelGGL((k_xface<R, S, 384>), dim3(nb), dim3(384), lds, st, a, rpi); break;
-    case 512: hipLaunchKernelGGL((k_xface<R, S, 512>), dim3(nb), dim3(512), lds, st, a, rpi); break;
-    default: hipLaunchKernelGGL((k_xface<R, S, 1024>), dim3(nb), dim3(1024), lds, st, a, rpi); break;
-  }
-}
-
-template <class R, int S>
-void launch_xbound_t(const StageArgs<R>& base, hipStream_t st) {
-  StageArgs<R> a = base;
-  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
-  const long long rows = (long long)a.g.n[1] * a.g.n[2];
-  const unsigned nb = (unsigned)((rows + kXBoundRows - 1) / kXBoundRows);
-  hipLaunchKernelGGL((k_xbound<R, S>), dim3(nb), dim3(kXBoundRows * 10), 0, st, a);
 }
 
 template <class R, int S, int AX>
@@ -1420,57 +899,16 @@ void launch_march_t(const StageArgs<R>& base, int seg, hipStream_t st) {
   hipLaunchKernelGGL((k_march<R, S, AX, AX == 2>), grid, dim3(64, 4), 0, st, a);
 }
 
-template <class R, int S, int AX>
-void launch_tile_t(const StageArgs<R>& base, hipStream_t st) {
-  StageArgs<R> a = base;
-  const int nx = a.g.n[0];
-  face_scale<R, S>(a, 1.0 / a.g.dx[AX]);
-  const int n = a.g.n[AX];
-  const int no = (AX == 1) ? a.g.n[2] : a.g.n[1];
-  const int A = tile_len(n);
-  const size_t lds = (size_t)2 * 5 * (A + 8) * kTileXP * sizeof(R);
-  a.order = (base.order >> (AX - 1)) & 1;
-  dim3 grid((nx + kTileX - 1) / kTileX, (n + A - 1) / A, no);
-  if (a.order) grid = dim3(grid.x, no, grid.y);
-  if (A == 31) hipLaunchKernelGGL((k_tile<R, S, AX, AX == 2, 31>), grid, dim3(512), lds, st, a);
-  else hipLaunchKernelGGL((k_tile<R, S, AX, AX == 2, 32>), grid, dim3(512), lds, st, a);
-}
-
-template <class R, int S>
-void launch_xtile_t(const StageArgs<R>& base, hipStream_t st) {
-  StageArgs<R> a = base;
-  face_scale<R, S>(a, 1.0 / a.g.dx[0]);
-  const int A = tile_len(a.g.n[0]);
-  const size_t lds = (size_t)2 * 5 * (A + 8) * kXTileY * sizeof(R);
-  dim3 grid((a.g.n[0] + A - 1) / A, (a.g.n[1] + kXTileY - 1) / kXTileY, a.g.n[2]);
-  if (A == 31) hipLaunchKernelGGL((k_xtile<R, S, 31>), grid, dim3(512), lds, st, a);
-  else hipLaunchKernelGGL((k_xtile<R, S, 32>), grid, dim3(512), lds, st, a);
-}
-
-// kernel: 0 x-faces, 1 x boundary faces, 2 y-march, 3 z-march (+ combine),
-// 4 y-tile, 5 z-tile (+ combine), 6 x-tile (all x faces, boundary included)
+// kernel: 0 x faces, 1 y, 2 z (+ combine), 3 y-march, 4 z-march (+ combine)
 template <class R>
 hipError_t launch_face_kernel(int kernel, const StageArgs<R>& a, int scheme, int seg, hipStream_t st) {
 #define HYDRO_DISPATCH(S)                                  \
   switch (kernel) {                                        \
-    case 2: launch_march_t<R, S, 1>(a, seg, st); break;    \
-    case 3: launch_march_t<R, S, 2>(a, seg, st); break;    \
-    default:                                               \
-      if constexpr (line_scheme(S)) {                      \
-        switch (kernel) {                                  \
-          case 4: launch_line_t<R, S, 1>(a, st); break;    \
-          case 5: launch_line_t<R, S, 2>(a, st); break;    \
-          default: launch_line_t<R, S, 0>(a, st); break;   \
-        }                                                  \
-      } else {                                             \
-        switch (kernel) {                                  \
-          case 0: launch_xface_t<R, S>(a, st); break;      \
-          case 1: launch_xbound_t<R, S>(a, st); break;     \
-          case 4: launch_tile_t<R, S, 1>(a, st); break;    \
-          case 5: launch_tile_t<R, S, 2>(a, st); break;    \
-          default: launch_xtile_t<R, S>(a, st); break;     \
-        }                                                  \
-      }                                                    \
+    case 0: launch_line_t<R, S, 0>(a, st); break;          \
+    case 1: launch_line_t<R, S, 1>(a, st); break;          \
+    case 2: launch_line_t<R, S, 2>(a, st); break;          \
+    case 3: launch_march_t<R, S, 1>(a, seg, st); break;    \
+    default: launch_march_t<R, S, 2>(a, seg, st); break;   \
   }
   switch (scheme) {
     case kWenoJS: HYDRO_DISPATCH(kWenoJS) break;
@@ -1520,42 +958,16 @@ hipError_t launch_primitives(const R* U, R* prim, long long nc, double g, double
   return hipGetLastError();
 }
 
-// Work items of one event for the batched launches: 0 x tiles, 1 and 2 y/z
-// tiles, 3 x-row groups, 4 groups of kXBoundRows rows for the outflow x face
-// (none for periodic x).  An x pass is either 0 or 3 + 4; plain WENO faces
-// take x tiles always (3: the same tiles, 4: none).
-long long batch_items(int AX, const Grid& g, int scheme, int xtb, int elem) {
-  const long long rows = (long long)g.n[1] * g.n[2];
-  const bool lines = line_scheme(scheme);
-  if (lines && AX == 3) AX = 0;
-  if (AX == 3) {
-    const int rpi = xrow_rows(g.n[0], xtb, elem);
-    return (rows + rpi - 1) / rpi;
-  }
-  if (AX == 4) return g.bc[0] || lines ? 0 : (rows + kXBoundRows - 1) / kXBoundRows;
+// Work items of one event for the batched launches: the tiles of an axis.
+long long batch_items(int AX, const Grid& g) {
   const int A = tile_len(g.n[AX]), no = AX == 2 ? g.n[1] : g.n[2];
-  return (long long)((g.n[AX] + A - 1) / A) * ((g.n[AX == 0 ? 1 : 0] + 15) / 16) * no;
+  return (long long)((g.n[AX] + A - 1) / A) * ((g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX) * no;
 }
 
-// blocks: workgroups of the launch (0: one per item).
-template <class R, int S>
-void launch_btile_u(int AX, int A, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
-  const size_t lds = (size_t)2 * 5 * (A + 8) * 16 * sizeof(R);
-  const dim3 tb(512);
-#define HYDRO_BTU(AXV, AV)                                                                 \
-  if (AX == AXV && A == AV) {                                                              \
-    if (persist) hipLaunchKernelGGL((k_btile_u<R, S, AXV, AV, true>), grid, tb, lds, st, b);  \
-    else hipLaunchKernelGGL((k_btile_u<R, S, AXV, AV, false>), grid, tb, lds, st, b);          \
-  }
-  HYDRO_BTU(0, 31) HYDRO_BTU(1, 31) HYDRO_BTU(2, 31) HYDRO_BTU(0, 32) HYDRO_BTU(1, 32) HYDRO_BTU(2, 32)
-#undef HYDRO_BTU
-}
-
-// Plain WENO faces.
 template <class R, int S, int AX>
 void launch_bline_ax(bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
   const dim3 tb(kLineBlock);
-  const size_t lds = line_lds_bytes(AX, b.tile_a == 31 ? 31 : 32, (int)sizeof(R));
+  const size_t lds = line_lds_bytes(AX, b.tile_a == 31 ? 31 : 32, S, (int)sizeof(R));
   if (b.tile_a == 31) {
     if (persist) hipLaunchKernelGGL((k_bline<R, S, AX, 31, true>), grid, tb, lds, st, b);
     else hipLaunchKernelGGL((k_bline<R, S, AX, 31, false>), grid, tb, lds, st, b);
@@ -1569,43 +981,12 @@ void launch_bline_ax(bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t
 
 template <class R, int S>
 void launch_bline(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
-  if (AX == 0 || AX == 3) launch_bline_ax<R, S, 0>(persist, grid, b, st);
+  if (AX == 0) launch_bline_ax<R, S, 0>(persist, grid, b, st);
   if (AX == 1) launch_bline_ax<R, S, 1>(persist, grid, b, st);
   if (AX == 2) launch_bline_ax<R, S, 2>(persist, grid, b, st);
 }
 
-// The limiter.
-template <class R, int S>
-void launch_bface(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStream_t st) {
-  const size_t lds = (size_t)2 * 5 * (32 + 8) * 16 * sizeof(R);  // the largest tile (A = 32)
-  const dim3 tb(512);
-  const size_t xl = (size_t)b.xlds;
-  if (AX == 3) {
-    switch (b.xtb) {
-      case 256: hipLaunchKernelGGL((k_bxrows<R, S, 256>), grid, dim3(256), xl, st, b); break;
-      case 384: hipLaunchKernelGGL((k_bxrows<R, S, 384>), grid, dim3(384), xl, st, b); break;
-      case 512: hipLaunchKernelGGL((k_bxrows<R, S, 512>), grid, dim3(512), xl, st, b); break;
-      default: hipLaunchKernelGGL((k_bxrows<R, S, 1024>), grid, dim3(1024), xl, st, b); break;
-    }
-    return;
-  }
-  if (AX == 4) {
-    hipLaunchKernelGGL((k_bxbound<R, S>), grid, dim3(kXBoundRows * 10), 0, st, b);
-    return;
-  }
-  // the uniform-tile-length kernels for WENO7-Z with the limiter (the other
-  // limited schemes keep the general one)
-  if constexpr (S == (kWenoZ | kPP)) {
-    if (b.tile_a == 31 || b.tile_a == 32) {
-      launch_btile_u<R, S>(AX, b.tile_a, persist, grid, b, st);
-      return;
-    }
-  }
-  if (AX == 0) hipLaunchKernelGGL((k_btile<R, S, 0>), grid, tb, lds, st, b);
-  else if (AX == 1) hipLaunchKernelGGL((k_btile<R, S, 1>), grid, tb, lds, st, b);
-  else hipLaunchKernelGGL((k_btile<R, S, 2>), grid, tb, lds, st, b);
-}
-
+// blocks: workgroups of the launch (0: one per item).
 template <class R>
 hipError_t launch_batch_axis(int AX, const BatchArgs<R>& b, int scheme, long long blocks, hipStream_t st) {
   const long long nb = (blocks <= 0 || blocks > b.items) ? b.items : blocks;
@@ -1618,12 +999,12 @@ hipError_t launch_batch_axis(int AX, const BatchArgs<R>& b, int scheme, long lon
     case kWeno5Z: launch_bline<R, kWeno5Z>(AX, persist, grid, b, st); break;
     case kWeno5JS: launch_bline<R, kWeno5JS>(AX, persist, grid, b, st); break;
     case kWeno5Linear: launch_bline<R, kWeno5Linear>(AX, persist, grid, b, st); break;
-    case kWenoZ | kPP: launch_bface<R, (kWenoZ | kPP)>(AX, persist, grid, b, st); break;
-    case kWenoJS | kPP: launch_bface<R, (kWenoJS | kPP)>(AX, persist, grid, b, st); break;
-    case kWenoLinear | kPP: launch_bface<R, (kWenoLinear | kPP)>(AX, persist, grid, b, st); break;
-    case kWeno5Z | kPP: launch_bface<R, (kWeno5Z | kPP)>(AX, persist, grid, b, st); break;
-    case kWeno5JS | kPP: launch_bface<R, (kWeno5JS | kPP)>(AX, persist, grid, b, st); break;
-    case kWeno5Linear | kPP: launch_bface<R, (kWeno5Linear | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoZ | kPP: launch_bline<R, (kWenoZ | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoJS | kPP: launch_bline<R, (kWenoJS | kPP)>(AX, persist, grid, b, st); break;
+    case kWenoLinear | kPP: launch_bline<R, (kWenoLinear | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5Z | kPP: launch_bline<R, (kWeno5Z | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5JS | kPP: launch_bline<R, (kWeno5JS | kPP)>(AX, persist, grid, b, st); break;
+    case kWeno5Linear | kPP: launch_bline<R, (kWeno5Linear | kPP)>(AX, persist, grid, b, st); break;
     case kWenoZ | kMusta: launch_bline<R, (kWenoZ | kMusta)>(AX, persist, grid, b, st); break;
     case kWeno5Z | kMusta: launch_bline<R, (kWeno5Z | kMusta)>(AX, persist, grid, b, st); break;
     default: launch_bline<R, kWenoZ>(AX, persist, grid, b, st); break;

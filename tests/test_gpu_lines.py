@@ -96,6 +96,27 @@ def test_musta_rhs_at_tile_edges(n, bc):
         h.close()
 
 
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", SHAPES)
+def test_limited_rhs_at_tile_edges_is_bitwise(n, bc):
+    # energies over six decades: the limiter acts at many faces.  The marching
+    # kernels take one face a time by the same operations: equal bits.
+    w = W.small_event(1, n=n, with_jet=False)
+    rng = np.random.default_rng(sum(n) + 2)
+    U = rough_state(n, sum(n)) * 10.0 ** rng.uniform(-6.0, 0.0, (n[2], n[1], n[0]))
+    for precision, weno in (("f64", "z"), ("f64", "z5"), ("f64", "js"), ("f32", "z")):
+        out = []
+        for limiter, march in (("pp", 0), ("pp", 1), ("none", 0)):
+            h = H().from_workload(w, precision=precision, weno=weno, bc=(bc,) * 3, limiter=limiter)
+            h.set_option(H().OPT_YZ_KERNEL, march)
+            out.append(h.rhs(torch.from_numpy(U).to("cuda", h.dtype), 1.0).clone())
+            h.close()
+        print("limiter", n, bc, precision, weno, "differs from unlimited:", not torch.equal(out[0], out[2]), flush=True)
+        assert torch.equal(out[0], out[1]), (n, bc, precision, weno)
+        if n != (1, 1, 1):
+            assert not torch.equal(out[0], out[2])
+
+
 @pytest.mark.parametrize("precision", ["f64", "f32"])
 def test_batch_of_mixed_tile_lengths_is_bitwise(precision):
     # tile lengths 31 and 32 in one batch (no common one), persistent and not
