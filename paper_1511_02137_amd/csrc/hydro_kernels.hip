@@ -425,17 +425,26 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
     if (extra) *xrow = ex;
     __syncthreads();
   }
-  if (own) {
+  // the own cell once more, in FP64 from a lane index that the compiler cannot
+  // match with the first one: kept across the faces, the cell's offset takes two
+  // registers too many for three workgroups a CU and is spilled (0.15 GB of
+  // scratch a launch at 256^3; three steps 18.08 -> 17.69 ms)
+  int t2 = threadIdx.x;
+  if (sizeof(R) == 8) __asm__ __volatile__("" : "+v"(t2));
+  const int tx2 = AX == 0 ? t2 >> 5 : t2 & (kLineX - 1);
+  const int ta2 = AX == 0 ? t2 & 31 : t2 >> 4;
+  if (bx * kLineX + tx2 < no && ta2 < len) {
+    const long long cell2 = base + tx2 * lstep + (long long)(a0 + ta2) * stride;
     // LAST, stages 2 and 3: the five U^n values are read before any output
     // is stored (out may be U^n itself, so the compiler would otherwise keep
     // each read behind the previous field's store: five round trips)
     R unv[5];
     if (LAST && a.stage >= 2) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) unv[c] = a.Un[c * nc + cell];
+      for (int c = 0; c < 5; ++c) unv[c] = a.Un[c * nc + cell2];
     }
-    const R* sp = s + (kL ? 10 * kArea : 0) + ta * kRow + tx;
-    const R* sm = s + kArea + (A - 1 - ta) * kRow + tx;  // F- of the right face; the left face's follows
+    const R* sp = s + (kL ? 10 * kArea : 0) + ta2 * kRow + tx2;
+    const R* sm = s + kArea + (A - 1 - ta2) * kRow + tx2;  // F- of the right face; the left face's follows
     constexpr int kStep = kL ? (A + 1) * kRow : 2 * kArea;
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
@@ -443,11 +452,11 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
       const R fr = kM || kL ? sp[c * kStep + kRow] : sp[c * kStep + kRow] + sm[c * kStep];
       const R div = (fl - fr) * a.inv_d;
       if (AX == 0) {
-        a.D[c * nc + cell] = div;
+        a.D[c * nc + cell2] = div;
       } else if (!LAST) {
-        a.D[c * nc + cell] = dpre[c] + div;
+        a.D[c * nc + cell2] = dpre[c] + div;
       } else {
-        a.out[c * nc + cell] = rk_out_v(a.stage, dpre[c], div, a.dt, unv[c]);
+        a.out[c * nc + cell2] = rk_out_v(a.stage, dpre[c], div, a.dt, unv[c]);
       }
     }
   }
