@@ -363,7 +363,7 @@ typedef enum {
                                transverse axis, clear = they step along the axis; default 2 */
   HYDRO_OPT_ADJ_LINES = 5   /* lines per workgroup of the y and z line adjoints: 0 = automatic
                                (default), 1, 2 or 4: the most lines a workgroup may take; it takes
-                               8 (FP64), 4 or 1, as many as that and 64 KiB of LDS allow.
+                               8 (FP64), 4 or 1, as many as that and its LDS allow.
                                Neighbouring x lines share the workgroup, so their strided loads
                                share cache lines; every line is computed by the same arithmetic
                                (same results) */

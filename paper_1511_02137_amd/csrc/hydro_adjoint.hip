@@ -892,12 +892,17 @@ __global__ void __launch_bounds__(256) k_prim_vjp(const double* __restrict__ pri
 
 // ---------------------------------------------------------------------------
 // Host-side launchers.
-// Lines per workgroup of a line adjoint: 8 (FP64) or 4 (FP32), else 4 or 1, at
-// most the request, fewer while their LDS exceeds 64 KiB (one always fits: the
-// adjoint's grids are bounded so).  Run length: the one of 6, 8, 9 and 13 faces
+// Lines per workgroup of a line adjoint: 8 (FP64) while two such workgroups fit
+// a CU's LDS, as many as their registers allow; else 4 while one fits; else 1,
+// or as few as the caller asks for.  A single line leaves most lanes of a
+// workgroup idle: x at 128^3 in FP64, where 4 lines take 67 KB, 745 us with one
+// line (backward of two steps 7.0 ms) against 190 with four (4.2 ms).  Run length: the one of 6, 8, 9 and 13 faces
 // with the shortest march in turns of the runs that those lines leave a wave
 // (by type and face count alone, so that every number of lines adds in the same
-// order); the other weights, less used, take 8.
+// order): 8 runs of 8 lines or 16 of 4 (100^3 in FP64: 2.6 -> 2.1 ms against
+// always 8); the other weights, less used, take 8.
+constexpr size_t kTwoPerCU = 80 * 1024, kOnePerCU = 160 * 1024;
+
 template <class R, int S, int AX, int L, int NL>
 void launch_line_adj_n(const AdjArgs<R>& a, long long nlines, size_t lds, hipStream_t st) {
   const long long ng = (nlines + NL - 1) / NL;
@@ -912,8 +917,8 @@ void launch_line_adj_l(const AdjArgs<R>& a, hipStream_t st) {
   const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                    : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
   auto lds = [&](int nl) { return line_adj_lds_bytes(AX, nf, L, nl, a.skip_n ? 4 : 5, (int)sizeof(R)); };
-  if (most >= 8 && lds(8) <= 65536) launch_line_adj_n<R, S, AX, L, 8>(a, nlines, lds(8), st);
-  else if (most >= 4 && lds(4) <= 65536) launch_line_adj_n<R, S, AX, L, 4>(a, nlines, lds(4), st);
+  if (most >= 8 && lds(8) <= kTwoPerCU) launch_line_adj_n<R, S, AX, L, 8>(a, nlines, lds(8), st);
+  else if (most >= 4 && lds(4) <= kOnePerCU) launch_line_adj_n<R, S, AX, L, 4>(a, nlines, lds(4), st);
   else launch_line_adj_n<R, S, AX, L, 1>(a, nlines, lds(1), st);
 }
 
@@ -923,7 +928,8 @@ void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
   if constexpr (S == kWenoZ) {
     int L = 8, best = 1 << 30;
     for (int c : {8, 6, 9, 13}) {
-      const int turn = (sizeof(R) == 8 ? 8 : 16) * c;
+      const bool eight = sizeof(R) == 8 && line_adj_lds_bytes(1, nf, c, 8, 4, 8) <= kTwoPerCU;
+      const int turn = (eight ? 8 : 16) * c;
       const int steps = (nf + turn - 1) / turn * (c + 1);  // and about one more to finish a run
       if (steps < best) {
         best = steps;

@@ -167,6 +167,13 @@ def test_line_adjoint_at_run_edges(n, bc):
     assert np.array_equal(outs[0], outs[1]) and np.array_equal(outs[0], outs[2])
 
 
+# lengths around which a workgroup takes 8, 4 or 1 lines, and their run lengths
+@pytest.mark.parametrize("n", [(77, 3, 2), (90, 2, 3), (100, 3, 2), (128, 3, 3), (200, 2, 2), (310, 2, 3), (3, 83, 2),
+                               (2, 100, 3), (3, 2, 128), (2, 310, 3)])
+def test_line_adjoint_at_workgroup_edges(n):
+    test_line_adjoint_at_run_edges(n, "outflow")
+
+
 def test_freezeout_range_of_p_t():
     """p_T from 1e-3 to where every exponential is subnormal or zero: rows
     within 1e-12 of their largest value (an exponent x carries x 2^-53, 6e-14
