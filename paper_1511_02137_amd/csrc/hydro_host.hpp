@@ -50,7 +50,7 @@ inline bool config_ok(const hydro_config* c, std::string* why) {
     if (c->bc[d] != HYDRO_BC_OUTFLOW && c->bc[d] != HYDRO_BC_PERIODIC) return fail("bad bc");
   }
   if (c->n[0] > 1024) return fail("n[0] must be <= 1024");
-  // the x-face kernel keeps the split fluxes of one row (+8 ghosts) in LDS
+  // a limit of the interface: the split fluxes of one row (+8 ghosts) in 64 KiB
   if ((size_t)10 * (c->n[0] + 8) * elem_size(c) > 65536) return fail("n[0] too large for the x-row LDS tile");
   if ((long long)c->n[1] * c->n[2] > 2147483647LL) return fail("too many rows");
   if (c->n[1] > 65535 || c->n[2] > 65535) return fail("n[1], n[2] must be <= 65535");

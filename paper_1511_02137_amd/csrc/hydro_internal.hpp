@@ -83,9 +83,9 @@ struct JetArgs {
   double eos_dof, hbarc;
 };
 
-// Cells per LDS tile along the reconstructed axis: 31 (32 face rows, one per
-// lane of a 512-lane workgroup) unless 32-cell tiles (33 face rows, the last
-// row by 16 lanes, measured ~12 % slower per tile) cover n with less waste.
+// Cells per LDS tile along the reconstructed axis: 31 (32 face rows, four runs of
+// eight) unless 32-cell tiles (33 face rows, the last one by lanes beside the
+// runs, measured ~12 % slower per tile) cover n with less waste.
 __host__ __device__ constexpr int tile_len(int n) {
   return ((n + 30) / 31) * 31 * 100 < 112 * (((n + 31) / 32) * 32) ? 31 : 32;
 }
