@@ -445,7 +445,7 @@ int hydro_batch_rhs(hydro_batch* b, void* stream);
 
 /* Launch-shape options of a batch (results do not depend on them). */
 typedef enum {
-  HYDRO_BOPT_BLOCKS_X = 0,  /* workgroups of the x launch: 0 = one per tile, else a persistent grid */
+  HYDRO_BOPT_BLOCKS_X = 0,  /* workgroups of the x launch: 0 (default) = one per tile, else a persistent grid */
   HYDRO_BOPT_BLOCKS_Y = 1,
   HYDRO_BOPT_BLOCKS_Z = 2,
   HYDRO_BOPT_GRAPH = 3,     /* 1 (default): replay a captured graph per step; 0: direct launches */

@@ -42,7 +42,6 @@ struct hydro_batch {
   int64_t step = 0;
   int cus = 256;
   long long blocks[3] = {0, 0, 0}; // workgroups per axis launch (0: one per item)
-  bool picked[3] = {false, false, false};  // blocks[] was set or tuned, not the default
   int xrows = 0;                   // HYDRO_BOPT_X_ROWS as set (the x pass has one kernel)
   int tile_a[3] = {0, 0, 0};       // per axis: the tile length every event shares (31, 32), else 0
   int use_graph = 1;
@@ -94,22 +93,14 @@ BatchArgs<R> batch_args(const hydro_batch* b, int AX, int stage) {
   return a;
 }
 
-// Workgroups of an axis launch.  Unless they were set or tuned, one item
-// each: the persistent form has 68 VGPRs (FP32) instead of 44, a workgroup per CU fewer.  16 FP32 events of 64 to 128 cells an
-// edge, us an axis (x, y, z): persistent, two workgroups per CU 462, 510, 550;
-// one item each 371, 374, 395.
-long long axis_blocks(const hydro_batch* b, int AX) {
-  return b->picked[AX] ? b->blocks[AX] : 0;
-}
-
 // One stage of every event: x tiles, y tiles, jets, z tiles (+ RK combine).
 template <class R>
 hipError_t stage_launches(hydro_batch* b, int stage, hipStream_t st) {
   const int scheme = face_scheme(b->cfg[0]);
-  hipError_t e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, axis_blocks(b, 0), st);
-  if (e == hipSuccess) e = launch_batch_axis<R>(1, batch_args<R>(b, 1, stage), scheme, axis_blocks(b, 1), st);
+  hipError_t e = launch_batch_axis<R>(0, batch_args<R>(b, 0, stage), scheme, b->blocks[0], st);
+  if (e == hipSuccess) e = launch_batch_axis<R>(1, batch_args<R>(b, 1, stage), scheme, b->blocks[1], st);
   if (e == hipSuccess) e = launch_batch_jet<R>(batch_args<R>(b, 0, stage), st);
-  if (e == hipSuccess) e = launch_batch_axis<R>(2, batch_args<R>(b, 2, stage), scheme, axis_blocks(b, 2), st);
+  if (e == hipSuccess) e = launch_batch_axis<R>(2, batch_args<R>(b, 2, stage), scheme, b->blocks[2], st);
   return e;
 }
 
@@ -220,7 +211,7 @@ hipError_t time_axis(hydro_batch* b, int AX, long long blocks, int reps, hipStre
   const int prev = (AX == 1) ? 0 : (AX == 2 ? 1 : 2);
   const BatchArgs<R> ap = batch_args<R>(b, prev, 0);
   for (int r = 0; r <= reps && e == hipSuccess; ++r) {
-    e = launch_batch_axis<R>(prev, ap, scheme, prev == 0 ? 0 : b->blocks[prev], st);
+    e = launch_batch_axis<R>(prev, ap, scheme, b->blocks[prev], st);
     if (e == hipSuccess) e = hipEventRecord(e0, st);
     if (e == hipSuccess) e = launch_batch_axis<R>(AX, a, scheme, blocks, st);
     if (e == hipSuccess) e = hipEventRecord(e1, st);
@@ -244,10 +235,7 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
   long long best[3];
   int xr = 0;
   if (cache_lookup(cache, key, best, &xr)) {
-    for (int a = 0; a < 3; ++a) {
-      b->blocks[a] = best[a];
-      b->picked[a] = true;
-    }
+    for (int a = 0; a < 3; ++a) b->blocks[a] = best[a];
     b->xrows = xr;
     if (from_cache) *from_cache = 1;
     drop_graph(b);
@@ -268,7 +256,6 @@ int autotune_impl(hydro_batch* b, const char* cache, hipStream_t st, int* from_c
       }
     }
     b->blocks[AX] = pick;
-    b->picked[AX] = true;
   }
   b->xrows = 0;
   cache_store(cache, key, b->blocks, b->xrows);
@@ -404,8 +391,10 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
     }
     if (e != hipSuccess) return cleanup(HYDRO_EDEVICE, std::string("prim->cons: ") + hipGetErrorString(e));
   }
-  // default launch shape: two workgroups per CU on every axis
-  for (int a = 0; a < 3; ++a) b->blocks[a] = 2LL * b->cus;
+  // blocks[] stays 0, one workgroup per tile: the persistent form has 68 VGPRs
+  // (FP32) instead of 44, a workgroup per CU fewer.  16 FP32 events of 64 to 128
+  // cells an edge, us an axis (x, y, z): persistent, two workgroups per CU 462,
+  // 510, 550; one tile each 371, 374, 395.
   *out = b;
   return HYDRO_OK;
 }
@@ -486,7 +475,6 @@ int hydro_batch_set_option(hydro_batch* b, int option, long long value) {
     case HYDRO_BOPT_BLOCKS_Z:
       if (value < 0) return bfail(b, HYDRO_EINVAL, "workgroup count must be >= 0");
       b->blocks[option - HYDRO_BOPT_BLOCKS_X] = value;
-      b->picked[option - HYDRO_BOPT_BLOCKS_X] = true;
       drop_graph(b);
       return HYDRO_OK;
     case HYDRO_BOPT_GRAPH:
