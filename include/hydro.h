@@ -459,10 +459,11 @@ int hydro_batch_get_option(hydro_batch* b, int option, long long* value);
 /* Pick the workgroup count of each axis launch: the candidates 0 (one per work item) and c * (number of CUs),
  * c in {1, 2, 3, 4, 6, 8}, are timed on this batch (median of 5 launches of
  * the right-hand-side form, no state change) and the fastest kept.
- * cache_path (may be NULL) is a text file of "key bx by bz xrows" lines (xrows
- * 0, older files also 1: HYDRO_BOPT_X_ROWS), the
- * key a hash of the GPU, precision, scheme and the sorted event shapes: a hit
- * skips the timing (*from_cache = 1), a miss appends the picks.
+ * cache_path (may be NULL) is a text file of "key bx by bz xrows" lines (xrows:
+ * HYDRO_BOPT_X_ROWS, stored as 0), the key a hash of the GPU, the form of the
+ * kernels, precision, scheme and the sorted event shapes: a hit skips the timing
+ * (*from_cache = 1), a miss appends the picks.  Lines timed with another form of
+ * the kernels miss.
  * Synchronous. */
 int hydro_batch_autotune(hydro_batch* b, const char* cache_path, void* stream, int* from_cache);
 

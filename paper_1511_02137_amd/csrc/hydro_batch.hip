@@ -138,6 +138,10 @@ hipError_t capture(hydro_batch* b) {
   return e;
 }
 
+// Form of the batched face kernels that cached launch shapes were timed with:
+// raised whenever their tiles or work items change, so that older lines miss.
+constexpr int kTuneForm = 2;  // line tiles on every axis (before: x rows, whole-face tiles)
+
 // 64-bit FNV-1a of the batch's tuning key.
 std::string tune_key(const hydro_batch* b) {
   std::vector<std::string> shapes;
@@ -152,7 +156,7 @@ std::string tune_key(const hydro_batch* b) {
   int dev = 0;
   (void)hipGetDevice(&dev);
   if (hipGetDeviceProperties(&p, dev) == hipSuccess) k << p.gcnArchName << ":" << p.multiProcessorCount;
-  k << ":p" << b->cfg[0].precision << ":w" << b->cfg[0].weno << ":l" << b->cfg[0].limiter << ":f" << b->cfg[0].flux
+  k << ":k" << kTuneForm << ":p" << b->cfg[0].precision << ":w" << b->cfg[0].weno << ":l" << b->cfg[0].limiter << ":f" << b->cfg[0].flux
     << ":" << b->cfg[0].musta_k;
   for (const auto& s : shapes) k << ":" << s;
   unsigned long long h = 1469598103934665603ULL;

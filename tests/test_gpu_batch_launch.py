@@ -29,3 +29,33 @@ def test_default_launch_shape_is_reported(precision):
     for a in (H().BOPT_BLOCKS_X, H().BOPT_BLOCKS_Y, H().BOPT_BLOCKS_Z):
         assert b.get_option(a) == 0, (a, b.get_option(a))
     b.close()
+
+
+def test_shapes_timed_with_other_kernels_are_not_taken(tmp_path):
+    """A cache line written before the x faces took line tiles (its key names no
+    form of the kernels, bx counts groups of whole rows) is a miss: the batch is
+    timed and its line appended, which the next batch takes."""
+    p = torch.cuda.get_device_properties(0)
+    n = (20, 18, 16)
+    key = "%s:%d:p1:w0:l0:f0:0:%s" % (p.gcnArchName, p.multi_processor_count, "x".join(map(str, n)))
+
+    def line(key):
+        h = 1469598103934665603
+        for c in key.encode():
+            h = ((h ^ c) * 1099511628211) % 2 ** 64
+        return "%016x 512 768 1024 1\n" % h
+
+    cache = tmp_path / "tune.txt"
+    # musta_k is part of the key whatever the flux is
+    b = H().batch_from_workloads([W.small_event(1, n=n)], precision="f32")
+    old = key.replace(":f0:0:", ":f0:%d:" % b.cfgs[0].musta_k)
+    cache.write_text(line(old))
+    assert b.autotune(str(cache)) is False
+    lines = cache.read_text().splitlines()
+    assert len(lines) == 2 and lines[1].split()[0] != lines[0].split()[0]
+    picks = [b.get_option(a) for a in (0, 1, 2)]
+    b.close()
+    b = H().batch_from_workloads([W.small_event(1, n=n)], precision="f32")
+    assert b.autotune(str(cache)) is True
+    assert [b.get_option(a) for a in (0, 1, 2)] == picks
+    b.close()
