@@ -97,6 +97,16 @@ __host__ __device__ constexpr size_t line_lds_bytes(int AX, int A, int scheme, i
   return (size_t)(10 * (A + 8) + ((scheme & kPP) ? 5 * (A + 1) : 0)) * (AX == 0 ? kLineX + 1 : kLineX) * elem;
 }
 
+// Lanes of a line-tile workgroup, and workgroups of a batched axis launch: one
+// per item (blocks 0), or `blocks` that walk the items.  A launch holds fewer
+// than 2^32 lanes, 8388607 workgroups; thin events (an item of one cell) have
+// more items than that long before memory ends, and a grid of that many walks.
+constexpr int kLineBlock = 512;
+__host__ __device__ constexpr long long batch_grid(long long items, long long blocks) {
+  const long long nb = (blocks <= 0 || blocks > items) ? items : blocks, most = 0xffffffffLL / kLineBlock;
+  return nb < most ? nb : most;
+}
+
 // One event of a batch (device table, see hydro_batch.hip).
 struct BatchEvent {
   Grid g;

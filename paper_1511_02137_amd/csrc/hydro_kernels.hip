@@ -189,8 +189,6 @@ __global__ void __launch_bounds__(256) k_march(StageArgs<R> a) {
 // the place of its first value: the lanes of a wave execute their LDS
 // operations in order, and result j of a run follows the read of value j + 8,
 // the last that the run before it (8 faces back) needs from that place.
-constexpr int kLineBlock = 512;
-
 template <class R, int S, int L, class Idx>
 __device__ __forceinline__ void line_faces(R* area, Idx idx, R eps) {
   R next = area[idx(0)], last = R(0);
@@ -998,7 +996,7 @@ void launch_bline(int AX, bool persist, dim3 grid, const BatchArgs<R>& b, hipStr
 // blocks: workgroups of the launch (0: one per item).
 template <class R>
 hipError_t launch_batch_axis(int AX, const BatchArgs<R>& b, int scheme, long long blocks, hipStream_t st) {
-  const long long nb = (blocks <= 0 || blocks > b.items) ? b.items : blocks;
+  const long long nb = batch_grid(b.items, blocks);
   if (nb <= 0) return hipSuccess;
   const dim3 grid((unsigned)nb);
   const bool persist = nb < b.items;

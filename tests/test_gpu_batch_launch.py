@@ -59,3 +59,25 @@ def test_shapes_timed_with_other_kernels_are_not_taken(tmp_path):
     assert b.autotune(str(cache)) is True
     assert [b.get_option(a) for a in (0, 1, 2)] == picks
     b.close()
+
+
+@pytest.mark.parametrize("graph", [1, 0])
+def test_more_tiles_than_one_launch_holds(graph):
+    """129 events of 1 x 1 x 65535 cells: 129 x 65535 x tiles, above the 2^32 / 512
+    workgroups of one launch; the first and last events step bit for bit as alone."""
+    n, k = (1, 1, 65535), 129
+    assert n[2] * k > 2 ** 32 // 512
+    w = W.Workload(name="thin", n=n, dx=(0.1,) * 3, t0=1.0, dt=0.02, steps=1,
+                   prim0=W.ellipsoid_prim(n, (0.1,) * 3, (1.0, 1.0, 500.0), 30.0), jets=[])
+    h = H().from_workload(w, precision="f32")
+    h.step(1)
+    torch.cuda.synchronize()
+    one = h.U.clone()
+    h.close()
+    prim = torch.from_numpy(w.prim0).cuda()
+    b = H().Batch([H().make_config(n, dt=w.dt, precision="f32")] * k, [prim] * k)
+    b.set_option(H().BOPT_GRAPH, graph)
+    b.run(1)
+    torch.cuda.synchronize()
+    assert torch.equal(b.U[0], one) and torch.equal(b.U[k - 1], one)
+    b.close()
