@@ -140,7 +140,7 @@ hipError_t capture(hydro_batch* b) {
 
 // Form of the batched face kernels that cached launch shapes were timed with:
 // raised whenever their tiles or work items change, so that older lines miss.
-constexpr int kTuneForm = 2;  // line tiles on every axis (before: x rows, whole-face tiles)
+constexpr int kTuneForm = 3;  // line tiles, x in groups of rows (2: of rows of one plane; before: whole-face tiles)
 
 // 64-bit FNV-1a of the batch's tuning key.
 std::string tune_key(const hydro_batch* b) {
@@ -355,6 +355,7 @@ int hydro_batch_create(const hydro_config* cfgs, int n_events, const double* con
     v.dV = c.dx[0] * c.dx[1] * c.dx[2];
     v.pp_mu = pp_mu(c);
     v.musta_k = c.musta_k;
+    v.xside = line_groups(0, v.g).x;
     v.eos_dof = c.eos_dof;
     v.hbarc = c.hbarc;
     v.njet = 0;

@@ -93,6 +93,22 @@ __host__ __device__ constexpr int tile_len(int n) {
 // Line tiles: 16 lines of A + 8 points for each (field, split), and with the
 // limiter A + 1 face fluxes for each field.
 constexpr int kLineX = 16;
+// Face rows that a tile marches over, a lane each in a workgroup of 16 of them.
+__host__ __device__ constexpr int line_rows(int A) { return A == 32 ? 32 : A + 1; }
+// Groups of 16 lines of a grid: x in groups of rows, whatever their y and z, up
+// to 16 groups side by side (a tile of the same rows follows soon after, while
+// their cache lines last) as evenly dealt as they go; y and z along x at each
+// value of the remaining axis.
+struct LineGroups {
+  int x, z;
+};
+inline LineGroups line_groups(int AX, const Grid& g) {
+  if (AX != 0) return {(g.n[0] + kLineX - 1) / kLineX, g.n[AX == 1 ? 2 : 1]};
+  const long long groups = ((long long)g.n[1] * g.n[2] + kLineX - 1) / kLineX;
+  const long long side = groups <= 16LL * 65535 ? 16 : (groups + 65534) / 65535;
+  const long long z = (groups + side - 1) / side;
+  return {(int)((groups + z - 1) / z), (int)z};
+}
 __host__ __device__ constexpr size_t line_lds_bytes(int AX, int A, int scheme, int elem) {
   return (size_t)(10 * (A + 8) + ((scheme & kPP) ? 5 * (A + 1) : 0)) * (AX == 0 ? kLineX + 1 : kLineX) * elem;
 }
@@ -122,6 +138,7 @@ struct BatchEvent {
   double eos_dof, hbarc;
   double pp_mu;       // 2 dt sum_d 1/dx_d (positivity limiter)
   int musta_k;        // MUSTA-FORCE stages
+  int xside;          // line_groups(0, g).x
   int njet;
   int deposit;
 };

@@ -187,8 +187,9 @@ __global__ void __launch_bounds__(256) k_march(StageArgs<R> a) {
 //
 // A run reads its values one ahead and stores each result, one face late, in
 // the place of its first value: the lanes of a wave execute their LDS
-// operations in order, and result j of a run follows the read of value j + 8,
-// the last that the run before it (8 faces back) needs from that place.
+// operations in order, and result j of a run follows the read of value j + 8
+// (its last value, if that comes first), after which no run before it needs
+// anything more from that place.
 template <class R, int S, int L, class Idx>
 __device__ __forceinline__ void line_faces(R* area, Idx idx, R eps) {
   R next = area[idx(0)], last = R(0);
@@ -208,27 +209,27 @@ __device__ __forceinline__ void line_faces(R* area, Idx idx, R eps) {
   area[idx(L - 1)] = last;
 }
 
-// Line tiles: a workgroup owns A = 31 or 32 cells along AX by 16 lines (y and
-// z: 16 cells along x; x: 16 rows along y) at one value of the remaining axis.
-// One lane per own cell, and 128 lanes for the 4 ghost slots on each side,
-// recover the points and store their split AX-fluxes in LDS; four lane groups
-// of a wave march over the 32 face rows in runs of kLineRun, and with A = 32
-// lanes 0..159 take the 33rd row, one face each; each own cell's lane forms
-// its divergence.  D is loaded before the march (LAST: folded into the
-// combine's p = w + dt D, rk_pre), to hide its latency; x is the first axis
-// and assigns D.  x tiles load along x (coalesced) and keep a pitch of 17
+// Line tiles: a workgroup owns A = 31 or 32 cells (A = 15, in half a workgroup,
+// where the axis has no more) along AX by 16 lines (y and z: 16 cells along x at
+// one value of the remaining axis; x: 16 rows in memory order, whatever their y
+// and z: x at 256x1x256 31 -> 9 us).  One lane per own cell, and 128 lanes for the 4 ghost slots on each
+// side, recover the points and store their split AX-fluxes in LDS; four lane
+// groups of a wave march over the line_rows(A) face rows in runs of a quarter of
+// them, and with A = 32 lanes 0..159 take the 33rd row, one face each; each own
+// cell's lane forms its divergence.  D is loaded before the march (LAST: folded
+// into the combine's p = w + dt D, rk_pre), to hide its latency; x is the first
+// axis and assigns D.  x tiles load along x (coalesced) and keep a pitch of 17
 // words, so that their stores do not meet in a bank.
-constexpr int kLineRun = 8;
-
 template <class R, int S, int AX, bool LAST, int A>
 __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by, int bz, R* s) {
   constexpr bool kM = (S & kMusta) != 0, kL = (S & kPP) != 0;
   constexpr int kP = A + 8;  // points of a line
+  constexpr int kRows = line_rows(A), kWaves = kRows / 4, kHalves = kRows / 16;
   constexpr int kRow = AX == 0 ? kLineX + 1 : kLineX;
   constexpr int kArea = kP * kRow;  // one (field, split): area 2 field + split
   const int nx = a.g.n[0], ny = a.g.n[1];
   const int n = a.g.n[AX];
-  const int no = a.g.n[AX == 0 ? 1 : 0];  // extent over the lines
+  const unsigned no = AX == 0 ? (unsigned)ny * (unsigned)a.g.n[2] : (unsigned)nx;  // lines that bx counts
   const int bc = a.g.bc[AX];
   const long long nc = a.g.nc;
   const int stride = AX == 0 ? 1 : (AX == 1 ? nx : nx * ny);
@@ -236,15 +237,16 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
   const int w = t >> 6;
   const int a0 = by * A;
   const int len = min(A, n - a0);
-  const long long base = AX == 0 ? ((long long)bz * ny + bx * kLineX) * nx
-                                 : (AX == 1 ? (long long)bz * nx * ny + bx * kLineX : (long long)bz * nx + bx * kLineX);
+  const unsigned line0 = (unsigned)bx * kLineX;
+  const long long base = AX == 0 ? (long long)line0 * nx
+                                 : (AX == 1 ? (long long)bz * nx * ny + line0 : (long long)bz * nx + line0);
   const int lstep = AX == 0 ? nx : 1;  // cells between lines
   unsigned fix = 0;
 
   // own cell of the lane: line tx, cell ta of the tile (lanes run along x in memory)
-  const int tx = AX == 0 ? t >> 5 : t & (kLineX - 1);
-  const int ta = AX == 0 ? t & 31 : t >> 4;
-  const bool own = bx * kLineX + tx < no && ta < len;
+  const int tx = AX == 0 ? (unsigned)t / kRows : t & (kLineX - 1);
+  const int ta = AX == 0 ? t & (kRows - 1) : t >> 4;
+  const bool own = line0 + tx < no && ta < len;
   const long long cell = base + tx * lstep + (long long)(a0 + ta) * stride;
   R dpre[5];
   auto point = [&](int line, int slot, const R u[5]) {
@@ -258,13 +260,13 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
       if (!kM) sm[2 * c * kArea] = Fm[c];
     }
   };
-  // waves 6 and 7 also take ghost slots 0..3 and len + 4..len + 7; their loads
-  // go first, so that their latency overlaps the own cells' recovery
-  const int gq = t - 384;
+  // the last two waves also take ghost slots 0..3 and len + 4..len + 7; their
+  // loads go first, so that their latency overlaps the own cells' recovery
+  const int gq = t - (kWaves - 2) * 64;
   const int gl = AX == 0 ? gq >> 3 : gq & (kLineX - 1);
   const int gh = AX == 0 ? gq & 7 : gq >> 4;
   const int gslot = gh < 4 ? gh : gh + len;
-  const bool ghost = w >= 6 && bx * kLineX + gl < no;
+  const bool ghost = w >= kWaves - 2 && line0 + gl < no;
   R ug[5];
   if (ghost) {
     int p = a0 - 4 + gslot;
@@ -291,27 +293,27 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
     // MUSTA-FORCE: points in area 2 field; window q (slots q..q+6, cell slot
     // q + 3) gives uL of face row q (right value) and uR of face row q - 1
     // (left value).  Waves 2c and 2c + 1 march over rows 0..15 and 16..31 of
-    // field c = 0..3, every lane takes one window of N, and lanes of the first
-    // waves the windows from 32 on; the results wait in registers until all
+    // field c = 0..3 (A = 15: wave c over its 16 rows), every lane takes one
+    // window of N, and lanes of the first waves the windows from kRows on; the results wait in registers until all
     // points are read, then uL goes to area 2 field and uR to the next.
     // One window per cell and field instead of two per face, and then one lane
     // per face with its 3 k recoveries, which bound the kernel: ~112 registers,
     // so 4 waves a SIMD (6 would spill).  At 128^3 in double precision, k = 2:
     // 106 to 114 us a launch, a step 1170 -> 895 us.
-    const R* v4 = s + 2 * (w >> 1) * kArea + ((w & 1) * 16 + grp * 4) * kRow + xl;
+    const int c4 = w / kHalves, q4 = (w % kHalves) * 16 + grp * 4, qn = t >> 4;
+    const R* v4 = s + 2 * c4 * kArea + q4 * kRow + xl;
     R ur[4], ul[4], nr, nl, xr = R(0), xm = R(0);
     weno_line<R, (S & 7), 4, true>([&](int m) { return v4[m * kRow]; }, a.eps, [&](int k, R r, R l) {
       ur[k] = r;
       ul[k] = l;
     });
-    const int q4 = (w & 1) * 16 + grp * 4, qn = t >> 4;
     const R* vn = s + 8 * kArea + qn * kRow + xl;
     weno_line<R, (S & 7), 1, true>([&](int m) { return vn[m * kRow]; }, a.eps, [&](int, R r, R l) {
       nr = r;
       nl = l;
     });
-    // windows 32 .. A + 1
-    const int xc = (t >> 4) % 5, xq = 32 + (t >> 4) / 5;
+    // windows kRows .. A + 1
+    const int xc = (t >> 4) % 5, xq = kRows + (t >> 4) / 5;
     const bool extra = xq <= A + 1;
     const R* vx = s + 2 * xc * kArea + xq * kRow + xl;
     if (extra) {
@@ -327,7 +329,7 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
       if (q > 0) d[kArea - kRow] = l;
     };
 #pragma unroll
-    for (int k = 0; k < 4; ++k) store(w >> 1, q4 + k, ur[k], ul[k]);
+    for (int k = 0; k < 4; ++k) store(c4, q4 + k, ur[k], ul[k]);
     store(4, qn, nr, nl);
     if (extra) store(xc, xq, xr, xm);
     __syncthreads();
@@ -344,21 +346,21 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
       for (int c = 0; c < 5; ++c) d[2 * c * kArea] = F[c];
     };
-    const bool line_in = bx * kLineX + xl < no;
+    const bool line_in = line0 + xl < no;
     if (line_in && qn <= len) flux(qn);
     if (A == 32 && t < kLineX && line_in && len == 32) flux(32);
     __syncthreads();
   } else if constexpr (kL) {
     // Limiter: it reads the split fluxes of the two cells next to a face, so
     // the points stay and the face fluxes get rows of their own.  Waves 2c and
-    // 2c + 1 march over rows 0..15 and 16..31 of field c = 0..3, F+ and then F-
+    // 2c + 1 (A = 15: wave c) march over the rows of field c = 0..3, F+ and then F-
     // (its run starts at the last face); every lane takes one face of N, and
     // the first lanes row 32.  The rows of their own bring the tile to 72 KB in
     // FP64, two workgroups a CU, which its registers (82) allow as well: 4 waves
     // a SIMD still issue at the peak rate.  Against tiles of whole faces per
     // lane, us a step without jets: FP64 128^3 989 -> 815, 31^3 99 -> 85; FP32
     // 128^3 623 -> 515; batches of 16 x 64^3 2542 -> 1732 (FP64), 1644 -> 1017.
-    const int c4 = w >> 1, q4 = (w & 1) * 16 + grp * 4, qn = t >> 4;
+    const int c4 = w / kHalves, q4 = (w % kHalves) * 16 + grp * 4, qn = t >> 4;
     auto rowp = [&](int c, int q) { return s + 2 * c * kArea + q * kRow + xl; };
     auto rowm = [&](int c, int q) { return s + (2 * c + 1) * kArea + (A - q) * kRow + xl; };
     auto flux = [&](int c, int q) { return s + 10 * kArea + (c * (A + 1) + q) * kRow + xl; };
@@ -394,23 +396,28 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 #pragma unroll
       for (int c = 0; c < 5; ++c) *flux(c, q) = H[c];
     };
-    const bool line_in = bx * kLineX + xl < no;
+    const bool line_in = line0 + xl < no;
     if (line_in && qn <= len) limit(qn);
     if (A == 32 && t < kLineX && line_in && len == 32) limit(32);
     __syncthreads();
   } else {
     // face row f: face (a0 - 1 + f) + 1/2; F+ at slots f..f+6, its result in
     // row f; F- at slots f+7..f+1, stored from row A - f on, its result there
-    {
-      R* area = s + w * kArea + grp * kLineRun * kRow + xl;
+    constexpr int kRun = kRows / 4;
+    // 8 face rows or fewer: runs of two (F-: in the upper half of the area)
+    const bool few = A == 15 && len < 8;
+    const int up = few && (w & 1) ? 8 : 0;
+    R* area = s + w * kArea + (up + grp * (few ? 2 : kRun)) * kRow + xl;
 #pragma unroll 1
-      for (int u = 0; u < 32; u += 4 * kLineRun, area += 4 * kLineRun * kRow)
-        line_faces<R, S, kLineRun>(area, [](int m) { return m * kRow; }, a.eps);
+    for (int c = 0; c < 8; c += kWaves, area += kWaves * kArea) {
+      if (few) line_faces<R, S, 2>(area, [](int m) { return m * kRow; }, a.eps);
+      else line_faces<R, S, kRun>(area, [](int m) { return m * kRow; }, a.eps);
     }
     // N: split w & 1, rows 2q and 2q + 1, q = 4 (w >> 1) + grp
-    R* const nrow = s + (8 + (w & 1)) * kArea + ((w >> 1) * 8 + grp * 2) * kRow + xl;
-    R nf[2];
-    weno_line<R, S, 2>([&](int m) { return nrow[m * kRow]; }, a.eps, [&](int k, R v) { nf[k] = v; });
+    R* const nrow = s + (8 + (w & 1)) * kArea + (up + (w >> 1) * 8 + grp * 2) * kRow + xl;
+    R nf[2] = {R(0), R(0)};
+    if (!few || w < 2)
+      weno_line<R, S, 2>([&](int m) { return nrow[m * kRow]; }, a.eps, [&](int k, R v) { nf[k] = v; });
     R ex = R(0);
     const bool extra = A == 32 && t < 160;  // row 32 of area t / 16
     R* const xrow = s + (t >> 4) * kArea + 32 * kRow + xl;
@@ -418,8 +425,10 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
       weno_line<R, S, 1>([&](int m) { return xrow[m * kRow]; }, a.eps, [&](int, R v) { ex = v; });
     }
     __syncthreads();  // the points of N and of row 32 are no longer read
-    nrow[0] = nf[0];
-    nrow[kRow] = nf[1];
+    if (!few || w < 2) {
+      nrow[0] = nf[0];
+      nrow[kRow] = nf[1];
+    }
     if (extra) *xrow = ex;
     __syncthreads();
   }
@@ -429,9 +438,9 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
   // scratch a launch at 256^3; three steps 18.08 -> 17.69 ms)
   int t2 = threadIdx.x;
   if (sizeof(R) == 8) __asm__ __volatile__("" : "+v"(t2));
-  const int tx2 = AX == 0 ? t2 >> 5 : t2 & (kLineX - 1);
-  const int ta2 = AX == 0 ? t2 & 31 : t2 >> 4;
-  if (bx * kLineX + tx2 < no && ta2 < len) {
+  const int tx2 = AX == 0 ? (unsigned)t2 / kRows : t2 & (kLineX - 1);
+  const int ta2 = AX == 0 ? t2 & (kRows - 1) : t2 >> 4;
+  if (line0 + tx2 < no && ta2 < len) {
     const long long cell2 = base + tx2 * lstep + (long long)(a0 + ta2) * stride;
     // LAST, stages 2 and 3: the five U^n values are read before any output
     // is stored (out may be U^n itself, so the compiler would otherwise keep
@@ -462,21 +471,26 @@ __device__ __forceinline__ void line_body(const StageArgs<R>& a, int bx, int by,
 }
 
 template <class R, int S, int AX, bool LAST, int A>
-__global__ void __launch_bounds__(kLineBlock, (S & (kMusta | kPP)) ? 4 : 6) k_line(StageArgs<R> a) {
+__global__ void __launch_bounds__(kLineX * line_rows(A), (S & (kMusta | kPP)) ? 4 : 6) k_line(StageArgs<R> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // blockIdx.x: 16 lines; tile along AX and transverse index in either order
-  unsigned b0 = blockIdx.x, b1 = blockIdx.y;
-  if (a.seg != 0) {  // a.seg = ceil(2^32 / gridDim.x): neighbours on one XCD
-    const unsigned id = b0 + gridDim.x * b1, per = (gridDim.x * gridDim.y) >> 3;
-    if (id < 8 * per) {
-      const unsigned to = (id & 7) * per + (id >> 3);
-      b1 = __umulhi(to, (unsigned)a.seg);
-      b0 = to - b1 * gridDim.x;
+  R* const s = reinterpret_cast<R*>(smem_raw);
+  if constexpr (AX == 0) {
+    line_body<R, S, AX, LAST, A>(a, blockIdx.x + gridDim.x * blockIdx.z, blockIdx.y, 0, s);
+  } else {
+    // blockIdx.x: 16 lines; tile along AX and transverse index in either order
+    unsigned b0 = blockIdx.x, b1 = blockIdx.y;
+    if (a.seg != 0) {  // a.seg = ceil(2^32 / gridDim.x): neighbours on one XCD
+      const unsigned id = b0 + gridDim.x * b1, per = (gridDim.x * gridDim.y) >> 3;
+      if (id < 8 * per) {
+        const unsigned to = (id & 7) * per + (id >> 3);
+        b1 = __umulhi(to, (unsigned)a.seg);
+        b0 = to - b1 * gridDim.x;
+      }
     }
+    const int by = a.order ? blockIdx.z : b1;
+    const int bz = a.order ? b1 : blockIdx.z;
+    line_body<R, S, AX, LAST, A>(a, b0, by, bz, s);
   }
-  const int by = a.order ? blockIdx.z : b1;
-  const int bz = a.order ? b1 : blockIdx.z;
-  line_body<R, S, AX, LAST, A>(a, b0, by, bz, reinterpret_cast<R*>(smem_raw));
 }
 
 // ---------------------------------------------------------------------------
@@ -797,9 +811,9 @@ template <class R, int S, int AX, int A>
 __device__ __forceinline__ void bline_item(const BatchArgs<R>& b, const BatchEvent& ev, long long local, R* s) {
   const StageArgs<R> a = batch_stage_args<R, S>(ev, b.stage, b.eps, AX);
   const int T = (ev.g.n[AX] + A - 1) / A;
-  const int gx = (ev.g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX;
+  const int gx = AX == 0 ? ev.xside : (ev.g.n[0] + kLineX - 1) / kLineX;
   const int bx = (int)(local % gx), by = (int)((local / gx) % T), bz = (int)(local / ((long long)gx * T));
-  line_body<R, S, AX, AX == 2, A>(a, bx, by, bz, s);
+  line_body<R, S, AX, AX == 2, A>(a, AX == 0 ? bx + gx * bz : bx, by, bz, s);
 }
 
 // A: the tile length of every event along the axis, 0 where they differ.
@@ -877,11 +891,14 @@ void launch_line_t(const StageArgs<R>& base, hipStream_t st) {
   StageArgs<R> a = base;
   face_scale<R, S>(a, 1.0 / a.g.dx[AX]);
   const int n = a.g.n[AX];
-  const int A = tile_len(n);
+  // Up to 15 cells, tiles of 15: marching 32 face rows for a few of them took,
+  // us a launch in FP64, z at 256x256x1 52 (30 with a lane per face), x at
+  // 1x256x256 59 (27); tiles of 15 take 22 and 24.
+  const int A = n <= 15 ? 15 : tile_len(n);
   a.order = AX == 0 ? 0 : (base.order >> (AX - 1)) & 1;
-  const int no = AX == 2 ? a.g.n[1] : a.g.n[2];
-  dim3 grid((a.g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX, (n + A - 1) / A, no);
-  if (a.order) grid = dim3(grid.x, no, grid.y);
+  const LineGroups lg = line_groups(AX, a.g);
+  dim3 grid(lg.x, (n + A - 1) / A, lg.z);
+  if (a.order) grid = dim3(grid.x, grid.z, grid.y);
   // FP32: 16 cells are half a cache line, so the workgroups that share lines,
   // dealt round-robin over the eight XCDs as they are, fetch them into several
   // L2s; a plane's workgroups go to the XCDs in contiguous parts instead (z at
@@ -890,7 +907,8 @@ void launch_line_t(const StageArgs<R>& base, hipStream_t st) {
   const bool xcd = sizeof(R) == 4 && AX == 2 && grid.x > 1 && (unsigned long long)grid.x * grid.x * grid.y < 0xffffffffULL;
   a.seg = xcd ? (int)((0x100000000ULL + grid.x - 1) / grid.x) : 0;
   const size_t lds = line_lds_bytes(AX, A, S, (int)sizeof(R));
-  if (A == 31) hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 31>), grid, dim3(kLineBlock), lds, st, a);
+  if (A == 15) hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 15>), grid, dim3(kLineBlock / 2), lds, st, a);
+  else if (A == 31) hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 31>), grid, dim3(kLineBlock), lds, st, a);
   else hipLaunchKernelGGL((k_line<R, S, AX, AX == 2, 32>), grid, dim3(kLineBlock), lds, st, a);
 }
 
@@ -967,8 +985,9 @@ hipError_t launch_primitives(const R* U, R* prim, long long nc, double g, double
 
 // Work items of one event for the batched launches: the tiles of an axis.
 long long batch_items(int AX, const Grid& g) {
-  const int A = tile_len(g.n[AX]), no = AX == 2 ? g.n[1] : g.n[2];
-  return (long long)((g.n[AX] + A - 1) / A) * ((g.n[AX == 0 ? 1 : 0] + kLineX - 1) / kLineX) * no;
+  const int A = tile_len(g.n[AX]);
+  const LineGroups lg = line_groups(AX, g);
+  return (long long)((g.n[AX] + A - 1) / A) * lg.x * lg.z;
 }
 
 template <class R, int S, int AX>

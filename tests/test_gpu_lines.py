@@ -189,3 +189,55 @@ def test_freezeout_range_of_p_t():
         assert np.abs(spec[r] - rs[r]).max() <= 1e-12 * np.abs(rs[r]).max(), r
     assert np.all(rs[4] == 0.0) and np.all(spec[4] == 0.0) and np.all(harm[4] == 0.0)
     h.close()
+
+
+# axes shorter than a half tile (15 cells), at its edges and at those of runs of two
+THIN = [(7, 19, 8), (8, 5, 14), (14, 8, 7), (15, 33, 1), (1, 15, 16), (16, 14, 15), (3, 1, 50)]
+
+
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", THIN)
+def test_rhs_of_thin_grids(n, bc):
+    test_rhs_at_tile_edges(n, bc)
+    test_musta_rhs_at_tile_edges(n, bc)
+    test_limited_rhs_at_tile_edges_is_bitwise(n, bc)
+
+
+def kernel_us(n, kernel):
+    """Mean time of one launch of a kernel class in a right-hand side, best of five."""
+    h = H().from_workload(W.small_event(1, n=n, with_jet=False))
+    U = torch.from_numpy(rough_state(n, 1)).cuda()
+    best = 1e30
+    for _ in range(5):
+        h.profile(True)
+        for _ in range(10):
+            h.rhs(U, 1.0)
+        torch.cuda.synchronize()
+        ms, launches = h.profile_read()[kernel]
+        h.profile(False)
+        best = min(best, 1e3 * ms / launches)
+    h.close()
+    return best
+
+
+def test_x_faces_of_thin_planes_cost_what_their_rows_do():
+    """The same 256 rows of 256 cells as one row of each plane and as one plane:
+    the x faces take their rows 16 at a time either way (one at a time: 31 against
+    10 us)."""
+    thin, flat = kernel_us((256, 1, 256), "xface"), kernel_us((256, 256, 1), "xface")
+    print("x faces of 256x1x256 %.1f us, 256x256x1 %.1f us" % (thin, flat), flush=True)
+    assert thin <= 2.0 * flat
+
+
+@pytest.mark.parametrize("axis,kernel", [(0, "xface"), (1, "ymarch"), (2, "zmarch")])
+def test_a_thin_axis_does_not_pay_for_a_full_tile(axis, kernel):
+    """15 cells along an axis against 31, the same number of tiles: half the face
+    rows (all 32 for both: 0.9 of the time)."""
+    n = [512, 512, 512]
+    times = []
+    for m in (15, 31):
+        n[axis] = m
+        n[(axis + 1) % 3] = 320
+        times.append(kernel_us(tuple(n), kernel))
+    print("axis %d: 15 cells %.1f us, 31 cells %.1f us" % (axis, *times), flush=True)
+    assert times[0] <= 0.75 * times[1]
