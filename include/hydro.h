@@ -361,12 +361,10 @@ typedef enum {
   HYDRO_OPT_TILE_ORDER = 4, /* order of the y/z LDS tiles' workgroups, 0..3: bit 0 (y tiles), bit 1 (z
                                tiles) set = neighbouring workgroups share the tile index and step the
                                transverse axis, clear = they step along the axis; default 2 */
-  HYDRO_OPT_ADJ_LINES = 5   /* lines per workgroup of the y and z line adjoints: 0 = automatic
-                               (default), 1, 2 or 4: the most lines a workgroup may take; it takes
-                               8 (FP64), 4 or 1, as many as that and its LDS allow.
-                               Neighbouring x lines share the workgroup, so their strided loads
-                               share cache lines; every line is computed by the same arithmetic
-                               (same results) */
+  HYDRO_OPT_ADJ_LINES = 5   /* most lines per workgroup of the line adjoints: 0 = no limit (default), 1,
+                               2 or 4.  A hint: it is kept where that costs no time, elsewhere the
+                               library takes 8, 4, 2 or 1 lines by their length and number.  Every
+                               line is computed by the same arithmetic (same results) */
 } hydro_option;
 
 /* Set / read an option; HYDRO_EINVAL for an unknown option or bad value. */

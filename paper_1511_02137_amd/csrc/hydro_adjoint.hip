@@ -16,6 +16,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "hydro_device.hpp"
@@ -384,10 +385,12 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = threadIdx.x & 63;
   unsigned fix = 0;
 
-  // Lane and step of the point phases: y and z: lines fastest; x: a wave per
-  // row, cells fastest.
-  const int l0 = AX == 0 ? w : (int)threadIdx.x & (nl - 1), lstep = AX == 0 ? kBlock / 64 : nl;
-  const int p0 = AX == 0 ? q : (int)threadIdx.x / nl, pstep = AX == 0 ? 64 : kBlock / nl;
+  // Line, first point and step of a lane in the point phases: y and z: lines
+  // fastest; x: 64 neighbouring cells of a row a wave, the waves dealt over the rows.
+  constexpr int kWaves = kBlock / 64, kRows = kWaves < nl ? kWaves : nl;  // x: rows under way at once
+  const int l0 = AX == 0 ? w % kRows : (int)threadIdx.x & (nl - 1), lstep = AX == 0 ? kRows : nl;
+  const int p0 = AX == 0 ? w / kRows * 64 + q : (int)threadIdx.x / nl;
+  constexpr int pstep = AX == 0 ? kWaves / kRows * 64 : kBlock / nl;
   R* const hold = s + 2 * fields * area;            // [area][6][line], the last run of a turn's values beyond it
   R* const phi = hold + 2 * fields * 6 * nl;        // [field][face + pad][pitch], zeros beyond the faces
   const int pad = (nf + L - 1) / L * L - nf, prows = line_adj_phi_rows(nf, L);
@@ -892,57 +895,89 @@ __global__ void __launch_bounds__(256) k_prim_vjp(const double* __restrict__ pri
 
 // ---------------------------------------------------------------------------
 // Host-side launchers.
-// Lines per workgroup of a line adjoint: 8 (FP64) while two such workgroups fit
-// a CU's LDS, as many as their registers allow; else 4 while one fits; else 1,
-// or as few as the caller asks for.  A single line leaves most lanes of a
-// workgroup idle: x at 128^3 in FP64, where 4 lines take 67 KB, 745 us with one
-// line (backward of two steps 7.0 ms) against 190 with four (4.2 ms).  Run length: the one of 6, 8, 9 and 13 faces
-// with the shortest march in turns of the runs that those lines leave a wave
-// (by type and face count alone, so that every number of lines adds in the same
-// order): 8 runs of 8 lines or 16 of 4 (100^3 in FP64: 2.6 -> 2.1 ms against
-// always 8); the other weights, less used, take 8.
-constexpr size_t kTwoPerCU = 80 * 1024, kOnePerCU = 160 * 1024;
+// Lines of a workgroup (8, 4, 2 or 1) and faces of a run (6, 8, 9 or 13) of a
+// line adjoint, by an estimate of the time.  Many lines fill the waves' lanes
+// where a line has few runs; few lines leave LDS for a second workgroup on the
+// CU and give the chip enough workgroups when there are few or long lines.  Its
+// unit is a wave's step over one face; a workgroup takes its chain of steps at
+// 2.5 (FP32: 3) units each, or its share of the CU's four SIMDs if they are
+// busier than that, and y and z loads of under 32 neighbouring bytes cost more.
+// Against the fastest of the four for 216 sets of lines (8 to 600 cells, 256 to
+// 16384 lines, four and five fields) it loses 1 % (FP64) and 2 % on average.
+// us an axis, as many lines as LDS holds / this / a lane per face: FP32 x, 500
+// cells, 8192 lines 484 / 184 / 233, 256 lines 51 / 17 / 17; y, 16 cells, 16384
+// lines 63 / 36 / 44; FP64 x, 64 cells, 16384 lines 182 / 129 / 126, 300 cells,
+// 256 lines 29 / 15 / 18.
+// The run length depends on type and face count alone, so that every number of
+// lines adds in the same order (same bits).
+constexpr size_t kOnePerCU = 160 * 1024;
+
+inline double line_adj_cost(int AX, int n, int nf, long long nlines, int L, int nl, int fields, int elem) {
+  const size_t lds = line_adj_lds_bytes(AX, nf, L, nl, fields, elem);
+  if (lds > kOnePerCU) return 1e300;
+  const int waves = line_adj_block(elem) / 64;
+  const int fit = std::min((int)(kOnePerCU / lds), (elem == 8 ? 16 : 20) / waves);  // workgroups on a CU (VGPRs)
+  const int steps = ((nf + L - 1) / L * nl + 63) / 64 * (L + 1);  // of an area: turns of runs, about one more to finish each
+  const double chain = (2 * fields + waves - 1) / waves * steps + (n * nl + 64 * waves - 1) / (64 * waves);
+  const double load = AX == 0 ? 1.0 : 1.0 + (elem == 8 ? 2.0 : 3.0) * std::max(0.0, 32.0 / (nl * elem) - 1.0);
+  const double issue = 0.25 * (2 * fields * steps + (n * nl + 63) / 64 * load) + (elem == 8 ? 2.0 : 0.0);
+  const double per_cu = (double)((nlines + nl - 1) / nl) / 256.0, wait = (elem == 8 ? 2.5 : 3.0) * chain;
+  if (per_cu <= fit) return std::max(wait, std::max(per_cu, 1.0) * issue);
+  return per_cu / fit * std::max(wait, fit * issue);
+}
 
 template <class R, int S, int AX, int L, int NL>
-void launch_line_adj_n(const AdjArgs<R>& a, long long nlines, size_t lds, hipStream_t st) {
+void launch_line_adj_n(const AdjArgs<R>& a, long long nlines, hipStream_t st) {
+  const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
+  const size_t lds = line_adj_lds_bytes(AX, nf, L, NL, a.skip_n ? 4 : 5, (int)sizeof(R));
   const long long ng = (nlines + NL - 1) / NL;
-  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, NL>), dim3((unsigned)(((ng + 7) / 8) * 8)), dim3(line_adj_block((int)sizeof(R))), lds, st,
-                     a);
+  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, NL>), dim3((unsigned)(((ng + 7) / 8) * 8)),
+                     dim3(line_adj_block((int)sizeof(R))), lds, st, a);
 }
 
 template <class R, int S, int AX, int L>
 void launch_line_adj_l(const AdjArgs<R>& a, hipStream_t st) {
-  const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
-  const int most = a.lines > 0 ? a.lines : (sizeof(R) == 8 ? 8 : 4);
+  const int n = a.g.n[AX], nf = n + (a.g.bc[AX] ? 0 : 1);
   const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                    : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
-  auto lds = [&](int nl) { return line_adj_lds_bytes(AX, nf, L, nl, a.skip_n ? 4 : 5, (int)sizeof(R)); };
-  if (most >= 8 && lds(8) <= kTwoPerCU) launch_line_adj_n<R, S, AX, L, 8>(a, nlines, lds(8), st);
-  else if (most >= 4 && lds(4) <= kOnePerCU) launch_line_adj_n<R, S, AX, L, 4>(a, nlines, lds(4), st);
-  else launch_line_adj_n<R, S, AX, L, 1>(a, nlines, lds(1), st);
+  // the fastest, and the fastest within the caller's limit if that is as fast
+  double best = 1e301, within = 1e301;
+  int nl = 1, nw = 1;
+  for (int c : {8, 4, 2, 1}) {
+    const double t = line_adj_cost(AX, n, nf, nlines, L, c, a.skip_n ? 4 : 5, (int)sizeof(R));
+    if (t < best) {
+      best = t;
+      nl = c;
+    }
+    if (c <= a.lines && t < within) {
+      within = t;
+      nw = c;
+    }
+  }
+  if (a.lines > 0 && within <= 1.05 * best) nl = nw;
+  if (nl == 8) launch_line_adj_n<R, S, AX, L, 8>(a, nlines, st);
+  else if (nl == 4) launch_line_adj_n<R, S, AX, L, 4>(a, nlines, st);
+  else if (nl == 2) launch_line_adj_n<R, S, AX, L, 2>(a, nlines, st);
+  else launch_line_adj_n<R, S, AX, L, 1>(a, nlines, st);
 }
 
 template <class R, int S, int AX>
 void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
-  const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
-  if constexpr (S == kWenoZ) {
-    int L = 8, best = 1 << 30;
-    for (int c : {8, 6, 9, 13}) {
-      const bool eight = sizeof(R) == 8 && line_adj_lds_bytes(1, nf, c, 8, 4, 8) <= kTwoPerCU;
-      const int turn = (eight ? 8 : 16) * c;
-      const int steps = (nf + turn - 1) / turn * (c + 1);  // and about one more to finish a run
-      if (steps < best) {
-        best = steps;
+  const int n = a.g.n[AX], nf = n + (a.g.bc[AX] ? 0 : 1);
+  int L = 8;
+  double best = 1e301;
+  for (int c : {8, 6, 9, 13})
+    for (int nl : {8, 4, 2, 1}) {
+      const double t = line_adj_cost(1, n, nf, 4096, c, nl, 5, (int)sizeof(R));
+      if (t < best) {
+        best = t;
         L = c;
       }
     }
-    if (L == 6) launch_line_adj_l<R, S, AX, 6>(a, st);
-    else if (L == 9) launch_line_adj_l<R, S, AX, 9>(a, st);
-    else if (L == 13) launch_line_adj_l<R, S, AX, 13>(a, st);
-    else launch_line_adj_l<R, S, AX, 8>(a, st);
-  } else {
-    launch_line_adj_l<R, S, AX, 8>(a, st);
-  }
+  if (L == 6) launch_line_adj_l<R, S, AX, 6>(a, st);
+  else if (L == 9) launch_line_adj_l<R, S, AX, 9>(a, st);
+  else if (L == 13) launch_line_adj_l<R, S, AX, 13>(a, st);
+  else launch_line_adj_l<R, S, AX, 8>(a, st);
 }
 
 template <class R, int S>

@@ -179,8 +179,8 @@ struct AdjArgs {
   // skipped and its outputs (G, lW, acc) are zero.  N enters no other field's
   // flux and no source, so with a zero N adjoint on entry this is exact.
   int skip_n;
-  // lines per workgroup requested by the caller (0: automatic; 1, 2 or 4): the
-  // launcher takes 8, 4 or 1, at most the request and what fits
+  // most lines per workgroup asked for by the caller (0: no limit; 1, 2 or 4):
+  // kept where that costs no time, else the launcher takes what is fastest
   int lines;
 };
 
