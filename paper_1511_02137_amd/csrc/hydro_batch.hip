@@ -140,7 +140,7 @@ hipError_t capture(hydro_batch* b) {
 
 // Form of the batched face kernels that cached launch shapes were timed with:
 // raised whenever their tiles or work items change, so that older lines miss.
-constexpr int kTuneForm = 3;  // line tiles, x in groups of rows (2: of rows of one plane; before: whole-face tiles)
+constexpr int kTuneForm = 4;  // line tiles, their lengths as tile_len has them
 
 // 64-bit FNV-1a of the batch's tuning key.
 std::string tune_key(const hydro_batch* b) {

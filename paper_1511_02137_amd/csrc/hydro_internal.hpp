@@ -85,9 +85,11 @@ struct JetArgs {
 
 // Cells per LDS tile along the reconstructed axis: 31 (32 face rows, four runs of
 // eight) unless 32-cell tiles (33 face rows, the last one by lanes beside the
-// runs, measured ~12 % slower per tile) cover n with less waste.
+// runs) are fewer by more than they cost: 3 to 8 % a tile, MUSTA-FORCE 13 %
+// (FP64, z at 128 x 128 x n, us with 31 and with 32: n = 62 37.1 and 37.8, n = 64
+// 48.1 and 38.4; MUSTA-FORCE 42.5 and 46.1, 55.1 and 47.9).
 __host__ __device__ constexpr int tile_len(int n) {
-  return ((n + 30) / 31) * 31 * 100 < 112 * (((n + 31) / 32) * 32) ? 31 : 32;
+  return (n + 30) / 31 * 100 > 109 * ((n + 31) / 32) ? 32 : 31;
 }
 
 // Line tiles: 16 lines of A + 8 points for each (field, split), and with the
