@@ -36,21 +36,20 @@ if ROOT not in sys.path:
 METRIC = "cell-updates/s per RK3 stage at 256^3 (% of roofline); adjoint/forward time"
 
 # Algorithmic flops per cell and kernel (adds and multiplies 1, fma 2,
-# divide and square root 1), minimal form of the scheme:
-#   one WENO7-Z reconstruction: candidates 28, smoothness 92, tau 4,
-#   weights 20, sum 3, combination 7, normalisation 1 = 155;
-#   per face 10 reconstructions (5 fields x 2 splits) = 1550;
-#   flux and Lax-Friedrichs split per cell and axis 25;
-#   divergence 10 per axis; conserved->primitive 25 (counted once, x);
+# divide and square root 1), counted from the library's double-precision form,
+# whose differences and their indicator terms are formed once per point of a line:
+#   one WENO7-Z reconstruction: differences of the point 7, slopes and
+#   curvatures 16, candidates 8, indicators 16, tau 4, squares and weights over
+#   the common denominator 16, sums 18, quotient and result 3 = 88;
+#   per face 10 reconstructions (5 fields x 2 splits) = 880;
+#   flux and Lax-Friedrichs split per cell and axis 19;
+#   divergence 10 per axis; conserved->primitive 19 (counted once, x);
 #   RK combine 15 (z).
-# Flops per reconstruction for the other schemes, same accounting: WENO7-JS
-# drops tau (151); linear weights: candidates + combination (35 for WENO7, 20
-# for WENO5).  For WENO5-Z/JS the plain formulation (counted operation by
-# operation by the oracle's counting scalar: 78 and 71) needs fewer than the
-# library's form (85, 83), so the smaller count is used: the algorithmic count
-# is never taken above what a plain implementation needs (the test of the
-# counts checks this for every scheme).
-RECON_FLOPS = {"z": 155, "js": 151, "linear": 35, "z5": 78, "js5": 71, "linear5": 20}
+# The other schemes in the same accounting: WENO7-JS drops tau and the Z weights
+# (75); linear weights 36; WENO5-Z 51, JS 43, linear 20.  A plain formulation,
+# counted operation by operation by the oracle's counting scalar, needs 168,
+# 155, 39, 78, 71 and 23 (the test of the counts holds these below it).
+RECON_FLOPS = {"z": 88, "js": 75, "linear": 36, "z5": 51, "js5": 43, "linear5": 20}
 
 
 SCHEME_NAMES = {"z": "WENO7-Z", "js": "WENO7-JS", "linear": "WENO7 linear weights", "z5": "WENO5-Z",
@@ -68,11 +67,11 @@ def flops_per_cell(weno: str = "z", flux: str = "weno", musta_k: int = 2):
     if flux == "musta":  # reconstructions of the two states, stages, divergence (+ combine in z)
         f = r + MUSTA_STAGE_FLOPS * musta_k + MUSTA_UPDATE_FLOPS * (musta_k - 1) + 10
         return {"xface": f, "ymarch": f, "zmarch": f + 15}
-    return {"xface": r + 25 + 10 + 25, "ymarch": r + 25 + 10, "zmarch": r + 25 + 10 + 15}
+    return {"xface": r + 19 + 10 + 19, "ymarch": r + 19 + 10, "zmarch": r + 19 + 10 + 15}
 
 
 FLOPS_PER_CELL = flops_per_cell("z")
-FLOPS_PER_CELL_UPDATE = sum(FLOPS_PER_CELL.values())  # 4795
+FLOPS_PER_CELL_UPDATE = sum(FLOPS_PER_CELL.values())  # 2761
 # Algorithmic words moved per cell by each kernel (W read + D read/write;
 # z: + U^n read in stages 2-3 (2/3 on average) + output write).
 BYTES_PER_CELL = {"xface": 10, "ymarch": 15, "zmarch": 5 + 5 + 5 * 2 / 3 + 5}
@@ -184,13 +183,12 @@ def precision_check(n: int, steps: int):
     return out
 
 
-# Algorithmic flops of one reconstruction's adjoint (WENO7-Z; add and
-# multiply 1, fma 2): the forward recomputed (155, as in FLOPS_PER_CELL) and
-# the reverse sweep (122: the partials of the normalised sum in the weights
-# and candidates 6, through the Z weights to tau and the indicators 34, the
-# indicators to the nested differences 34, the candidates to the first
-# differences 24, the transposed differences to the seven points 24).
-ADJ_FLOPS_RECON = 155 + 122
+# Flops of one reconstruction's adjoint (WENO7-Z, the library's double-precision
+# form; add and multiply 1, fma 2): the forward recomputed down to the weights
+# and the normalised sum 88 (its differences 7 of these), the reverse sweep 99
+# (candidates, weights, tau and indicators 39, slopes and curvatures 21, the
+# differences 31, their adjoints passed on once per point 8).
+ADJ_FLOPS_RECON = 88 + 99
 
 
 def adjoint_ratio(precision: str, n: int, steps: int, ckpt: int, repeats: int = 3):
@@ -373,7 +371,7 @@ def batch_throughput(precision: str, steps: int, warmup: int, cache, limiter: st
            "unit": "cell-updates/s", "limiter": limiter,
            "alu_frac": FLOPS_PER_CELL_UPDATE * value / 1e12 / PEAK_TFLOPS[precision],
            "blocks_per_axis": [b.get_option(a) for a in (0, 1, 2)],
-           "x_form": "rows" if b.get_option(H.BOPT_X_ROWS) else "tiles",
+           "x_form": "tiles",
            "tuned_from_cache": from_cache, "fixups": b.fixups()}
     b.close()
     return out
@@ -413,7 +411,7 @@ def main():
     ap.add_argument("--cpu-seconds", type=float, default=15.0, help="target length of the CPU oracle sample")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--yz", choices=["tile", "march"], default="tile", help="y/z face kernels")
-    ap.add_argument("--x", choices=["row", "tile"], default="row", help="x face kernel")
+    ap.add_argument("--x", choices=["row", "tile"], default="row", help="kept for callers that pass it: x faces have one kernel")
     ap.add_argument("--tile-order", type=int, default=2, choices=[0, 1, 2, 3],
                     help="workgroup order of the y/z LDS tiles (HYDRO_OPT_TILE_ORDER)")
     ap.add_argument("--limiter", choices=["none", "pp"], default="none",
@@ -468,7 +466,6 @@ def main():
     fpc = flops_per_cell(args.weno, args.flux, args.musta_k)  # the limiter's own arithmetic is not counted
     fpc_update = sum(fpc.values())
     h.set_option(H.OPT_YZ_KERNEL, 0 if args.yz == "tile" else 1)
-    h.set_option(H.OPT_X_KERNEL, 0 if args.x == "row" else 1)
     h.set_option(H.OPT_TILE_ORDER, args.tile_order)
     nc = w.n[0] * w.n[1] * w.n[2]
     if args.log:

@@ -44,3 +44,15 @@ def test_roofline_counts_do_not_exceed_the_plain_formulation():
     for scheme, (w, s) in plain.items():
         assert b.RECON_FLOPS[scheme] <= total(O.count_flops(w, s)), scheme
     assert b.FLOPS_PER_CELL_UPDATE <= 30 * total(O.count_flops("weno7", "z")) + total(O.count_flops("c2p")) + 3 * 35 + 15
+
+
+def test_roofline_counts_are_those_of_the_shared_form():
+    """One reconstruction of a line: every difference and indicator term once per
+    point, one division: the counts are far below the plain ones, and the adjoint's
+    holds the forward's."""
+    b = bench_module()
+    plain = {"z": 168, "js": 155, "linear": 39, "z5": 78, "js5": 71, "linear5": 23}
+    for scheme in ("z", "js", "z5", "js5"):
+        assert b.RECON_FLOPS[scheme] <= 0.7 * plain[scheme], scheme
+    assert b.FLOPS_PER_CELL_UPDATE == sum(b.flops_per_cell("z").values()) <= 30 * b.RECON_FLOPS["z"] + 130
+    assert b.RECON_FLOPS["z"] < b.ADJ_FLOPS_RECON <= 2.2 * b.RECON_FLOPS["z"]
