@@ -373,8 +373,8 @@ int hydro_get_option(hydro_ctx* ctx, int option, int* value);
 
 /* Kernel classes of a step, for hydro_profile_read. */
 typedef enum {
-  HYDRO_K_XFACE = 0,   /* x-faces of every row */
-  HYDRO_K_XBOUND = 1,  /* right boundary x-face of every row (outflow) */
+  HYDRO_K_XFACE = 0,   /* x-faces (LDS tiles) */
+  HYDRO_K_XBOUND = 1,  /* kept for the numbering: no kernel has this class, its counts are 0 */
   HYDRO_K_YMARCH = 2,  /* y-faces (LDS tiles or marches along y) */
   HYDRO_K_JET = 3,     /* jet source */
   HYDRO_K_ZMARCH = 4,  /* z-faces (LDS tiles or marches along z) and the RK combine */
