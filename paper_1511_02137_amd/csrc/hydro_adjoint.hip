@@ -364,7 +364,10 @@ __device__ __forceinline__ long long xcd_group(long long groups) {
   return (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
 }
 
-template <class R, int S, int AX, int L, int NL>
+// SEG: a workgroup owns a segment of its lines, cells c0..c1-1, and reverses
+// the faces c0-3..c1+3 (face f lies between cells f-1 and f) that touch them,
+// from the points seven cells further out on each side.
+template <class R, int S, int AX, int L, int NL, bool SEG>
 __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8 ? 4 : 5) k_line_adj(AdjArgs<R> a) {
   constexpr int kBlock = line_adj_block((int)sizeof(R));
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -376,10 +379,18 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
   const long long nc = a.g.nc;
   const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                    : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
-  const long long grp = xcd_group((nlines + nl - 1) / nl);
+  const int segs = SEG ? (n + a.seglen - 1) / a.seglen : 1;
+  const long long item = xcd_group((nlines + nl - 1) / nl * segs);
+  const long long grp = SEG ? item / segs : item;
   const long long line0 = grp * nl;
   if (line0 >= nlines) return;  // whole workgroup
-  const int nf = n + (bc ? 0 : 1);
+  // own cells c0..c1-1; faces f0..f0+nf-1; slot j holds position f0 - 4 + j
+  const int c0 = SEG ? (int)(item - grp * segs) * a.seglen : 0, c1 = SEG ? min(n, c0 + a.seglen) : n;
+  const int f0 = SEG ? (bc ? c0 - 3 : max(0, c0 - 3)) : 0;
+  const int nf = SEG ? (bc ? c1 + 3 : min(n, c1 + 3)) - f0 + 1 : n + (bc ? 0 : 1);
+  // cells that the points f0 - 4..f0 + nf + 2 are, those beyond outflow ends not
+  const int x0 = SEG ? (bc ? f0 - 4 : max(0, f0 - 4)) : 0, x1 = SEG ? (bc ? f0 + nf + 3 : min(n, f0 + nf + 3)) : n;
+  auto wrap = [&](int x) { return SEG && bc ? (x < 0 ? x + n : (x >= n ? x - n : x)) : x; };
   const int area = line_adj_slots(nf, L) * pitch;
   const int fields = a.skip_n ? 4 : 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), q = threadIdx.x & 63;
@@ -402,15 +413,15 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
     long long stride;
     const long long base = line_base(AX, line0 + l, a.g, stride);
 #pragma unroll 1
-    for (int x = p0; x < n; x += pstep) {
-      long long cell = base + x * stride;
+    for (int x = x0 + p0; x < x1; x += pstep) {
+      long long cell = base + wrap(x) * stride;
       __asm__ __volatile__("" : "+v"(cell));  // as in (3)
       R u[5], Fp[5], Fm[5];
       load5(a.W, nc, cell, u);
       const PrimV pv = c2p(u, fix);
       split_flux<R, AX>(u, pv, Fp, Fm);
-      R* sp = s + (x + 4) * pitch + l;
-      R* sm = s + area + (nf + 2 - x) * pitch + l;
+      R* sp = s + (x - f0 + 4) * pitch + l;
+      R* sm = s + area + (nf + 2 - x + f0) * pitch + l;
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
         if (c < fields) {
@@ -426,8 +437,8 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
     // beyond the ends
 #pragma unroll 1
     for (int k = p0; k < prows; k += pstep) {
-      const int f = k - pad;
-      const bool face = f >= 0 && f < nf;
+      const bool face = k >= pad && k - pad < nf;
+      const int f = SEG ? wrap(f0 + k - pad) : k - pad;
       const int fl = f == 0 ? (bc ? n - 1 : -1) : f - 1;
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
@@ -456,8 +467,14 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
       auto at = [&](int slot) { return ((ar & 1) ? nf + 6 - slot : slot) * pitch; };
       // ghost slots: copies of their cells
       const int h = qa / nl;
-      const int gj = h < 4 ? h : n + h;
-      if (h < 8 && gj <= nf + 6) line[at(gj)] = line[at(map_idx(gj - 4, n, bc) + 4)];
+      if constexpr (SEG) {  // points beyond outflow ends
+        const int left = bc ? 0 : max(0, 4 - f0), end = n - f0 + 4, right = bc ? 0 : max(0, nf + 7 - end);
+        if (h < left) line[at(h)] = line[at(left)];
+        if (h >= 4 && h - 4 < right) line[at(end + h - 4)] = line[at(end - 1)];
+      } else {
+        const int gj = h < 4 ? h : n + h;
+        if (h < 8 && gj <= nf + 6) line[at(gj)] = line[at(map_idx(gj - 4, n, bc) + 4)];
+      }
       __asm__ __volatile__("" ::: "memory");
       for (int r0 = 0; r0 < runs; r0 += rpt) {
         int qr = qa;
@@ -468,8 +485,8 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
         R beyond[6];
         if (act) {
           // faces r L.. of the area's order: F- runs from face nf - 1 down
-          const int f0 = (ar & 1) ? nf - 1 - r * L : r * L;
-          const R* ph = phi + (ar >> 1) * parea + (f0 + pad) * pitch + l;
+          const int fr = (ar & 1) ? nf - 1 - r * L : r * L;
+          const R* ph = phi + (ar >> 1) * parea + (fr + pad) * pitch + l;
           const int pstep1 = (ar & 1) ? -pitch : pitch;
           R next = t[0];
           R late[L + 6];
@@ -520,7 +537,14 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
       const int gh = qg / nl, gs = gh < 4 ? gh : n + gh;
       if (gh == 0) gl[(nf + 6) * pitch] = R(0);
       __asm__ __volatile__("" ::: "memory");
-      if (bc && n >= 8) {
+      if constexpr (SEG) {
+        if (!bc && gh < 2) {
+          const int left = max(0, 4 - f0), end = n - f0 + 4, right = max(0, nf + 7 - end);
+          const int j0 = gh == 0 ? 0 : end, count = gh == 0 ? left : right;
+          R* d = gl + at(gh == 0 ? left : end - 1);
+          for (int k = 0; k < count; ++k) *d = *d + gl[at(j0 + k)];
+        }
+      } else if (bc && n >= 8) {
         if (gh < 8 && gs <= nf + 6) {
           R* d = gl + at(map_idx(gs - 4, n, bc) + 4);
           *d = *d + gl[at(gs)];
@@ -554,7 +578,7 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
       long long stride;
       const long long base = line_base(AX, line0 + l, a.g, stride);
 #pragma unroll 1
-      for (int x = p0; x < n; x += pstep) {
+      for (int x = c0 + p0; x < c1; x += pstep) {
         long long cell = base + x * stride;
         // opaque: the loop keeps one index, not a pointer per array and field
         __asm__ __volatile__("" : "+v"(cell));
@@ -565,8 +589,8 @@ __global__ void __launch_bounds__(line_adj_block((int)sizeof(R)), sizeof(R) == 8
         const PrimV pv = c2p(u, f1);
         any = any || f1 != 0;
         if (SLOW != (f1 != 0)) continue;
-        const R* sp = s + (x + 4) * pitch + l;
-        const R* sm = s + area + (nf + 2 - x) * pitch + l;
+        const R* sp = s + (x - f0 + 4) * pitch + l;
+        const R* sm = s + area + (nf + 2 - x + f0) * pitch + l;
         double dp[5], dm[5], ub[5];
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
@@ -931,7 +955,23 @@ void launch_line_adj_n(const AdjArgs<R>& a, long long nlines, hipStream_t st) {
   const int nf = a.g.n[AX] + (a.g.bc[AX] ? 0 : 1);
   const size_t lds = line_adj_lds_bytes(AX, nf, L, NL, a.skip_n ? 4 : 5, (int)sizeof(R));
   const long long ng = (nlines + NL - 1) / NL;
-  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, NL>), dim3((unsigned)(((ng + 7) / 8) * 8)),
+  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, NL, false>), dim3((unsigned)(((ng + 7) / 8) * 8)),
+                     dim3(line_adj_block((int)sizeof(R))), lds, st, a);
+}
+
+// Segments of at most seglen cells of long y and z lines, four lines a workgroup.
+// Of the face counts that take as many runs as seglen + 7, the most LDS: phi has
+// a row more for every face fewer.
+constexpr int seg_faces(int seglen, int L) { return (seglen + 6) / L * L + 1; }
+
+template <class R, int S, int AX, int L>
+void launch_line_adj_seg(AdjArgs<R> a, int seglen, hipStream_t st) {
+  const int segs = (a.g.n[AX] + seglen - 1) / seglen;
+  const long long nlines = (long long)a.g.n[0] * a.g.n[AX == 1 ? 2 : 1];
+  const size_t lds = line_adj_lds_bytes(AX, seg_faces(seglen, L), L, 4, a.skip_n ? 4 : 5, (int)sizeof(R));
+  const long long ng = (nlines + 3) / 4 * segs;
+  a.seglen = seglen;
+  hipLaunchKernelGGL((k_line_adj<R, S, AX, L, 4, true>), dim3((unsigned)(((ng + 7) / 8) * 8)),
                      dim3(line_adj_block((int)sizeof(R))), lds, st, a);
 }
 
@@ -961,12 +1001,20 @@ void launch_line_adj_l(const AdjArgs<R>& a, hipStream_t st) {
   else launch_line_adj_n<R, S, AX, L, 1>(a, nlines, st);
 }
 
+// Run length, and segments of long y and z lines where they are cheaper by the
+// same estimate (of 4096 lines with five fields, whatever the call's are, so that
+// the form and with it every bit depend on the line's length alone). A whole line
+// of 256 FP64 cells fills the LDS with one workgroup; its segments leave room for
+// two, for 13 cells computed twice at each cut. Whole lines -> segments, us:
+// y 64x256x256 525 -> 441 (FP64, four fields), 607 -> 539 (five); y 64x300x216 604
+// -> 487; z 64x256x256 727 -> 545, FP32 547 -> 426; y 64x500x128 FP32 384 -> 230.
+// Dearer where few lines leave the chip idle either way: y 16x400x16 FP32 23.7 -> 26.4.
 template <class R, int S, int AX>
 void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
   const int n = a.g.n[AX], nf = n + (a.g.bc[AX] ? 0 : 1);
-  int L = 8;
+  int L = 8, seglen = n;
   double best = 1e301;
-  for (int c : {8, 6, 9, 13})
+  for (int c : {8, 6, 9, 13}) {
     for (int nl : {8, 4, 2, 1}) {
       const double t = line_adj_cost(1, n, nf, 4096, c, nl, 5, (int)sizeof(R));
       if (t < best) {
@@ -974,6 +1022,27 @@ void launch_line_adj(const AdjArgs<R>& a, hipStream_t st) {
         L = c;
       }
     }
+  }
+  if constexpr (AX != 0) {
+    for (int k = 2; n / k >= 64; ++k) {
+      const int m = (n + k - 1) / k;
+      for (int c : {8, 6, 9, 13}) {
+        const double t = line_adj_cost(1, m + 13, seg_faces(m, c), 4096LL * k, c, 4, 5, (int)sizeof(R));
+        if (t < best) {
+          best = t;
+          L = c;
+          seglen = m;
+        }
+      }
+    }
+    if (seglen < n) {
+      if (L == 6) launch_line_adj_seg<R, S, AX, 6>(a, seglen, st);
+      else if (L == 9) launch_line_adj_seg<R, S, AX, 9>(a, seglen, st);
+      else if (L == 13) launch_line_adj_seg<R, S, AX, 13>(a, seglen, st);
+      else launch_line_adj_seg<R, S, AX, 8>(a, seglen, st);
+      return;
+    }
+  }
   if (L == 6) launch_line_adj_l<R, S, AX, 6>(a, st);
   else if (L == 9) launch_line_adj_l<R, S, AX, 9>(a, st);
   else if (L == 13) launch_line_adj_l<R, S, AX, 13>(a, st);

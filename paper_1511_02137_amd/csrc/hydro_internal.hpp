@@ -184,6 +184,7 @@ struct AdjArgs {
   // most lines per workgroup asked for by the caller (0: no limit; 1, 2 or 4):
   // kept where that costs no time, else the launcher takes what is fastest
   int lines;
+  int seglen;  // cells of a line's segments (set by the launcher for the SEG form)
 };
 
 // Bound on the adjoint's axis lengths (hydro_workspace_bytes): elements of the

@@ -126,3 +126,20 @@ def test_a_limit_on_the_lines_costs_no_time(precision, lines):
     free, limited = step_us(n, precision, 0), step_us(n, precision, lines)
     print("%s: no limit %.0f us, %d lines %.0f us" % (precision, free, lines, limited), flush=True)
     assert limited <= 1.3 * free
+
+
+# y and z lines in segments: two and three, even and with a shorter last one
+SEGMENTED = [(3, 161, 2), (2, 200, 3), (4, 256, 3), (2, 3, 257), (3, 5, 163), (5, 328, 2)]
+
+
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", SEGMENTED)
+def test_lines_in_segments(n, bc):
+    for weno in ("z", "js", "linear"):
+        test_runs_and_turns_of_every_weight(n, weno, bc)
+
+
+@pytest.mark.parametrize("bc", ["outflow", "periodic"])
+@pytest.mark.parametrize("n", [(3, 256, 2), (2, 3, 257), (4, 401, 2), (2, 500, 3), (3, 2, 670)])
+def test_single_precision_lines_in_segments(n, bc):
+    test_single_precision_turns(n, bc)
