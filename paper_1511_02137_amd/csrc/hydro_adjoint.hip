@@ -980,16 +980,19 @@ void launch_line_adj_l(const AdjArgs<R>& a, hipStream_t st) {
   const int n = a.g.n[AX], nf = n + (a.g.bc[AX] ? 0 : 1);
   const long long nlines = AX == 0 ? (long long)a.g.n[1] * a.g.n[2]
                                    : (AX == 1 ? (long long)a.g.n[0] * a.g.n[2] : (long long)a.g.n[0] * a.g.n[1]);
-  // the fastest, and the fastest within the caller's limit if that is as fast
+  // the fastest, and the fastest within the caller's limit if that is as fast; of
+  // equals the fewer lines where the chip is full (FP32 x at 96^3: 89 -> 58 us),
+  // the more where it is not (FP64 at 24^3: 22 -> 17 us)
+  auto fewer = [&](int lines) { return (nlines + lines - 1) / lines > 256; };
   double best = 1e301, within = 1e301;
   int nl = 1, nw = 1;
   for (int c : {8, 4, 2, 1}) {
     const double t = line_adj_cost(AX, n, nf, nlines, L, c, a.skip_n ? 4 : 5, (int)sizeof(R));
-    if (t < best) {
+    if (t < best || (t == best && fewer(nl))) {
       best = t;
       nl = c;
     }
-    if (c <= a.lines && t < within) {
+    if (c <= a.lines && (t < within || (t == within && fewer(nw)))) {
       within = t;
       nw = c;
     }

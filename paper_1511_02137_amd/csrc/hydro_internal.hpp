@@ -191,8 +191,10 @@ struct AdjArgs {
 // field type that must fit 64 KiB.
 constexpr long long line_adj_lds_elems(int n) { return 10LL * (n + 8) + 14LL * (n + 16); }
 // Line adjoint: LDS slots of a line of nf faces in runs of L (the last run's
-// values included), words between slots (x: one more, so that a wave's cells of
-// a row fall in different banks), bytes of the two areas of each field, of the
+// values included), words between slots (x from four lines: one more, so that a
+// wave's cells of a row fall in different banks; two lines are level without it
+// and then two workgroups of 256 FP64 cells share a CU, 738 -> 556 us at
+// 256x64x256), bytes of the two areas of each field, of the
 // six values a line that pass from a turn to the next, and of phi.
 // Workgroups: with 128 VGPRs in FP64 two of eight waves share a CU (four lines
 // in four waves, with half the LDS and loads half as wide, were 1.2x slower at
@@ -200,7 +202,7 @@ constexpr long long line_adj_lds_elems(int n) { return 10LL * (n + 8) + 14LL * (
 // lines: 112 against 107 us an axis at 128^3).
 __host__ __device__ constexpr int line_adj_block(int elem) { return elem == 8 ? 512 : 256; }
 __host__ __device__ constexpr int line_adj_slots(int nf, int L) { return (nf + L - 1) / L * L + 7; }
-__host__ __device__ constexpr int line_adj_pitch(int AX, int lines) { return AX == 0 && lines > 1 ? lines + 1 : lines; }
+__host__ __device__ constexpr int line_adj_pitch(int AX, int lines) { return AX == 0 && lines > 2 ? lines + 1 : lines; }
 // phi rows: the faces and zeros up to a run's length less one on each side
 __host__ __device__ constexpr int line_adj_phi_rows(int nf, int L) { return 2 * ((nf + L - 1) / L * L) - nf; }
 __host__ __device__ constexpr size_t line_adj_lds_bytes(int AX, int nf, int L, int lines, int fields, int elem) {
