@@ -191,10 +191,11 @@ struct AdjArgs {
 // field type that must fit 64 KiB.
 constexpr long long line_adj_lds_elems(int n) { return 10LL * (n + 8) + 14LL * (n + 16); }
 // Line adjoint: LDS slots of a line of nf faces in runs of L (the last run's
-// values included), words between slots (x from four lines: one more, so that a
-// wave's cells of a row fall in different banks; two lines are level without it
-// and then two workgroups of 256 FP64 cells share a CU, 738 -> 556 us at
-// 256x64x256), bytes of the two areas of each field, of the
+// values included), words between slots (x with eight lines: one more, so that a
+// wave's cells of a row fall in different banks, 25.7 -> 24.6 us at 60x52x66 in
+// FP64; two and four lines lose nothing without it and more workgroups share a CU:
+// with five fields 256x64x256 FP64 738 -> 556 us, 128x128x128 FP64 380 -> 267, FP32
+// 166 -> 140), bytes of the two areas of each field, of the
 // six values a line that pass from a turn to the next, and of phi.
 // Workgroups: with 128 VGPRs in FP64 two of eight waves share a CU (four lines
 // in four waves, with half the LDS and loads half as wide, were 1.2x slower at
@@ -202,7 +203,7 @@ constexpr long long line_adj_lds_elems(int n) { return 10LL * (n + 8) + 14LL * (
 // lines: 112 against 107 us an axis at 128^3).
 __host__ __device__ constexpr int line_adj_block(int elem) { return elem == 8 ? 512 : 256; }
 __host__ __device__ constexpr int line_adj_slots(int nf, int L) { return (nf + L - 1) / L * L + 7; }
-__host__ __device__ constexpr int line_adj_pitch(int AX, int lines) { return AX == 0 && lines > 2 ? lines + 1 : lines; }
+__host__ __device__ constexpr int line_adj_pitch(int AX, int lines) { return AX == 0 && lines > 4 ? lines + 1 : lines; }
 // phi rows: the faces and zeros up to a run's length less one on each side
 __host__ __device__ constexpr int line_adj_phi_rows(int nf, int L) { return 2 * ((nf + L - 1) / L * L) - nf; }
 __host__ __device__ constexpr size_t line_adj_lds_bytes(int AX, int nf, int L, int lines, int fields, int elem) {
